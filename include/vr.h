@@ -349,11 +349,17 @@ VR_API int vr_pairs_dim1_apparent(const vr_result *res, int32_t *tri_of_edge, vo
  * the pivot of an edge's column is its oldest cofacet (the smallest
  * triangle key).  Edges paired with a vertex are cleared (their columns
  * reduce to zero); an edge with triangles of its own value pairs with the
- * first of them (as in vr_pairs_dim1_apparent); the other edge columns are
- * reduced in rounds: every unsettled column at once (one work-group each)
- * adds the apparent coboundaries and the stored columns of owners before it
- * that its pivots meet, then each pivot goes to its first claimant in the
- * order, displacing a later owner; every round settles at least one column.
+ * first of them (as in vr_pairs_dim1_apparent); the other edges, and of the
+ * other triangles those that can pair with one (of each component of an
+ * edge's common older neighbours, joined by older edges, the first), form a
+ * far smaller matrix once every other edge is replaced by older ones, and
+ * that is reduced, a wave per column, in one launch.  When a limit of that
+ * is passed (2^22 such triangles, 2^24 entries, 2048 in one column, 2^25
+ * words of stored columns), the edge columns themselves are reduced in
+ * rounds: every unsettled column at once (one work-group each) adds the
+ * apparent coboundaries and the stored columns of owners before it that its
+ * pivots meet, then each pivot goes to its first claimant in the order,
+ * displacing a later owner; every round settles at least one column.
  * The pairs equal those of the column algorithm on the whole boundary
  * matrix (Section 2.2.2), whose pairs do not depend on the column
  * operations that reached them.
@@ -365,11 +371,11 @@ VR_API int vr_pairs_dim1_apparent(const vr_result *res, int32_t *tri_of_edge, vo
  *               length zero when its value is r), or -1: edge r is paired
  *               with a vertex (e_low[r] >= 0), or else starts a class of
  *               dimension 1 that never dies.
- * The working column is a base list in device memory plus a short sorted
- * delta in LDS that takes the additions and is folded into the base when
- * full.  Synchronises `stream` once per round (the number of unsettled
- * columns and a status word are read back).  Scratch from the library's
- * cache: 4 n^2 + 48 K + 32 H bytes (H = 2K rounded up to a power of two)
+ * Synchronises `stream` once, and when a limit is passed once more per round
+ * (the number of unsettled columns and a status word are read back).
+ * Scratch from the library's cache: 4 n^2 + 28 K + 20 min(T, 2^22) bytes plus
+ * 384 MiB (column entries and stored columns); when a limit is passed
+ * instead 4 n^2 + 48 K + 32 H bytes (H = 2K rounded up to a power of two)
  * plus 1 GiB (the stored columns and rewritten bases, 2^27 keys), and when
  * 3 T <= 2^25 another 8 K + 24 T bytes: the apparent edges' coboundaries,
  * generated once, all at once, so that a long chain of additions copies

@@ -28,6 +28,7 @@
 
 #include "vr.h"
 #include "vr_cache.h"
+#include "vr_morse.h"
 
 #define PD_T 64      // tile edge
 #define PD_BLOCK 256  // 16 x 16 threads, 4 x 4 entries each
@@ -1646,16 +1647,28 @@ extern "C" VR_API int vr_pairs_dim1(const vr_result *res, const int32_t *e_low, 
     if (K == 0) return VR_OK;
     if (!tri_of_edge || !e_low || !res->edge_ij || (T > 0 && !res->tri_key)) return VR_EINVAL;
     const hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_pd_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K);
-    if (T == 0) return hipGetLastError() == hipSuccess ? VR_OK : VR_EHIP;  // no triangles: nothing dies
-    hipLaunchKernelGGL(k_pd_apparent, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, (const unsigned long long *)res->tri_key,
-                       T, tri_of_edge, K);
+    if (T == 0) {  // no triangles: nothing dies
+        hipLaunchKernelGGL(k_pd_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K);
+        return hipGetLastError() == hipSuccess ? VR_OK : VR_EHIP;
+    }
     // scratch, from the library's cache
+    int32_t *R = (int32_t *)cache_get(4 * (size_t)n * (size_t)n, s);
+    if (!R) return VR_ENOMEM;
+    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, R, n);
+    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, R, n, (const int32_t *)res->edge_ij, K, n);
+    bool done = false;
+    const int mst = morse_pairs_dim1(R, (const int32_t *)res->edge_ij, (const unsigned long long *)res->tri_key, e_low,
+                                     n, K, T, tri_of_edge, &done, s);
+    if (mst != VR_OK || done) {
+        cache_put(R, s);
+        return mst;
+    }
+    // a limit of that method was passed (tri_of_edge holds the apparent
+    // pairs): the edge columns themselves
     long long H = 2;
     while (H < 2 * K) H <<= 1;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t o = 0;
-    const size_t o_R = o; o = up(o + 4 * (size_t)n * (size_t)n);
     const size_t o_rem = o; o = up(o + 4 * (size_t)K);
     const size_t o_tab = o; o = up(o + sizeof(RdSlot) * (size_t)H);
     const size_t o_app = o; o = up(o + 8 * (size_t)K);
@@ -1678,9 +1691,12 @@ extern "C" VR_API int vr_pairs_dim1(const vr_result *res, const int32_t *e_low, 
     const size_t o_sr = o; o = up(o + 16 * (size_t)K);
     const size_t o_epos = o; o = up(o + 8 * (size_t)K);
     char *ws = (char *)cache_get(o, s);
-    if (!ws) return VR_ENOMEM;
+    if (!ws) {
+        cache_put(R, s);
+        return VR_ENOMEM;
+    }
     RdBufs B{};
-    B.R = (const int32_t *)(ws + o_R);
+    B.R = R;
     B.ij = (const int32_t *)res->edge_ij;
     B.app = (const unsigned long long *)(ws + o_app);
     B.rem = (const int32_t *)(ws + o_rem);
@@ -1696,9 +1712,6 @@ extern "C" VR_API int vr_pairs_dim1(const vr_result *res, const int32_t *e_low, 
     B.K = K;
     hipLaunchKernelGGL(k_rd_list, dim3(1), dim3(RD_BLOCK), 0, s, (const int32_t *)tri_of_edge, e_low, K,
                        (int32_t *)(ws + o_rem), B.ctl);
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, (int32_t *)(ws + o_R), n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (int32_t *)(ws + o_R), n,
-                       (const int32_t *)res->edge_ij, K, n);
     hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(RD_SLOT_WORDS * H)), dim3(PD_BLOCK), 0, s, (unsigned long long *)B.tab,
                        RD_SLOT_WORDS * H);
     hipLaunchKernelGGL(k_rd_app, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (const int32_t *)tri_of_edge,
@@ -1733,6 +1746,7 @@ extern "C" VR_API int vr_pairs_dim1(const vr_result *res, const int32_t *e_low, 
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     cache_put(ws, s);
+    cache_put(R, s);
     if (st != VR_OK) return st;
     return e == hipSuccess ? VR_OK : VR_EHIP;
 }
