@@ -354,8 +354,8 @@ VR_API int vr_pairs_dim1_apparent(const vr_result *res, int32_t *tri_of_edge, vo
  * edge's common older neighbours, joined by older edges, the first), form a
  * far smaller matrix once every other edge is replaced by older ones, and
  * that is reduced, a wave per column, in one launch.  When a limit of that
- * is passed (2^22 such triangles, 2^24 entries, 2048 in one column, 2^25
- * words of stored columns), the edge columns themselves are reduced in
+ * is passed (2^22 such triangles, 2^24 entries, 2^26 words of stored
+ * columns, the first two in 16 shares), the edge columns themselves are reduced in
  * rounds: every unsettled column at once (one work-group each) adds the
  * apparent coboundaries and the stored columns of owners before it that its
  * pivots meet, then each pivot goes to its first claimant in the order,
@@ -373,8 +373,8 @@ VR_API int vr_pairs_dim1_apparent(const vr_result *res, int32_t *tri_of_edge, vo
  *               dimension 1 that never dies.
  * Synchronises `stream` once, and when a limit is passed once more per round
  * (the number of unsettled columns and a status word are read back).
- * Scratch from the library's cache: 4 n^2 + 28 K + 20 min(T, 2^22) bytes plus
- * 384 MiB (column entries and stored columns); when a limit is passed
+ * Scratch from the library's cache: at most 8 n^2 + 33 K bytes plus 496 MiB
+ * (critical triangles, column entries and stored columns); when a limit is passed
  * instead 4 n^2 + 48 K + 32 H bytes (H = 2K rounded up to a power of two)
  * plus 1 GiB (the stored columns and rewritten bases, 2^27 keys), and when
  * 3 T <= 2^25 another 8 K + 24 T bytes: the apparent edges' coboundaries,

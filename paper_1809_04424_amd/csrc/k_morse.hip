@@ -33,17 +33,22 @@
 // triangles above it in order; its pivot is the oldest.
 //
 //   k_mo_range   the triangles of each edge's value, from one pass over the keys
-//   k_mo_link    per edge, a wave: L(r)'s components, the replacement edges,
-//                the critical triangles
+//   k_mo_snap    the neighbours of every vertex by edges older than each of
+//                up to 32 ranks, as bits
+//   k_mo_link    per edge, a wave: the edges that replace it, where the
+//                snapshots show L(r) to be connected
+//   k_mo_split   the other edges: L(r)'s components, the critical triangles
+//   k_mo_order   the critical cells' places in filtration order
 //   k_mo_expand  per critical triangle, a wave: its boundary in critical edges
 //   k_mo_scan    starts of the columns
 //   k_mo_scatter the columns' entries
 //   k_mo_reduce  the reduction, a wave per column, without rounds or locks
 //   k_mo_emit    the pairs
 //
-// On the circle and the mixture vr_pairs_dim1 took 28.4 and 36.5 ms as a
+// On the circle and the mixture vr_pairs_dim1 took 28.2 and 36.6 ms as a
 // reduction of the full edge columns, a work-group each: one column's chain
-// of thousands of additions.  The chains here are a few additions long.
+// of thousands of additions.  The chains here are a few additions long, and
+// it takes 0.15 and 1.7 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -58,42 +63,53 @@
 #define MO_GEN (VR_MAX_POINTS / VR_WAVE)  // pieces of the largest L(r)
 #define MO_STACK 1024               // edges a wave is replacing, and critical edges it found
 #define MO_STEPS 1024               // replacement steps of one triangle (64 edges each)
-#define MO_QBITS 27                 // critical triangles: index bits of a column entry
 #define MO_QCAP (1ll << 22)         // critical triangles at most
 #define MO_ENT (1ll << 24)          // column entries at most
-#define MO_POOL (1ll << 25)         // words of stored columns at most
-#define MO_CAP 1024                 // entries of a column held in LDS
+#define MO_POOL (1ll << 26)         // words of stored columns at most
+#define MO_EB 16                    // edges a wave of k_mo_link takes, in order
+#define MO_SNAPS 32                 // ranks with a snapshot at most
+#define MO_LDS_Q (1u << 17)         // critical triangles whose bits a wave holds in LDS
+#define MO_GWAVES 256               // waves reducing with their bits in device memory
 #define MO_NONE 0xFFFFFFFFu
 
+// Counters that waves all over the chip add to come MO_REG times, a cache
+// line each, with a share of the array they number: atomics on one address
+// follow one another at about 10 ns.
+#define MO_REG 16
 struct MoCtl {
+    uint32_t err;   // a limit was passed
     uint32_t q;     // critical triangles
     uint32_t m;     // critical edges
-    uint32_t nent;  // column entries
-    uint32_t err;   // a limit was passed
-    uint32_t next;  // columns taken
-    uint32_t pad;
+    uint32_t pad0;
     unsigned long long ptop;  // pool words taken
+    uint32_t pad1[26];
+    uint32_t rec[MO_REG][32];  // [i][0]: critical triangles found, in share i
+    uint32_t ent[MO_REG][32];  // [i][0]: column entries, in share i
 };
 
-// A column entry orders critical triangles as the filtration does and names
-// one: edge rank (24 bits) | third vertex (13) | index (27).
 struct MoBufs {
     const int32_t *R, *ij, *e_low;
     const unsigned long long *key;
     int64_t n, K, T;
     int32_t *first, *end;           // K: the triangles of value r are [first, end); first -1: none
-    int2 *fg;                       // K: the two edges that replace r; x = -1: none, y = its column or -1
+    int2 *fg;                       // K: the two edges that replace r; x = -1: none, and y = its place
+                                    // among its block's critical edges, or -1
+    unsigned long long *snap;       // snapshot s >= 1 of vertex v: words [((s - 1) n + v) W, + W), the
+                                    // neighbours joined by an edge of rank < s << sb
+    int W, sb;
+    uint32_t *blk, *blkm;           // per MO_EB edges: their critical triangles (edges), then the first's place
+    uint32_t *mask;                 // per MO_EB edges: those left to k_mo_split
+    uint32_t *ecnt;                 // K, for the edges left to k_mo_split: their critical triangles
     uint32_t *crit;                 // column -> edge
     uint32_t *cnt, *fill;           // column -> entries, entries placed
     uint32_t *start;                // column -> its first pool word (the length, then the entries)
-    unsigned long long *cent;       // critical triangle -> its entry
-    uint32_t *ctri;                 // critical triangle -> its index among the keys
+    uint4 *rec;                     // critical triangle as found: edge, vertex, index among the keys, place in its edge
+    uint32_t *ctri;                 // critical triangle (by place) -> its index among the keys
     unsigned long long *owner;      // critical triangle -> (edge + 1) << 32 | pool word of its column; 0: none
-    uint2 *ent;                     // (column, critical triangle) pairs
-    unsigned long long *pool;
+    uint2 *ent;                     // (column, critical triangle) pairs; later the bits of k_mo_reduce's waves
+    uint32_t *pool;                 // columns: the length, then the critical triangles in any order
     MoCtl *ctl;
-    uint32_t qcap, ecap;
-    unsigned long long pcap;
+    uint32_t qcap, ecap, pcap;
 };
 
 // Orders a wave's LDS (and, for later loads of its own, global) accesses.
@@ -134,23 +150,22 @@ __device__ __forceinline__ uint32_t mo_third(unsigned long long w, uint32_t a, u
     return i != a ? i : (j != b ? j : k);
 }
 
-// A wave's lanes append the critical triangles of edge r marked by `on`.
-__device__ __forceinline__ void mo_append(const MoBufs &B, uint32_t r, uint32_t k, uint32_t tri, bool on) {
-    const unsigned long long m = ballot64(on);
-    if (!m) return;
-    uint32_t q0 = 0;
-    if (lane_id() == 0) q0 = atomicAdd(&B.ctl->q, (uint32_t)__popcll(m));
-    q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)q0);
-    const uint32_t q = q0 + mo_before(m);
-    if (!on) return;
-    if (q >= B.qcap) {
-        B.ctl->err = 1u;
-        return;
-    }
-    B.cent[q] = ((unsigned long long)r << (13 + MO_QBITS)) | ((unsigned long long)k << MO_QBITS) | q;
-    B.ctri[q] = tri;
-    B.owner[q] = 0ull;
+// Lane 0 records the critical triangle {r, k}, the place-th of its edge.
+__device__ __forceinline__ void mo_append(const MoBufs &B, uint32_t r, uint32_t k, uint32_t tri, uint32_t place) {
+    if (lane_id() != 0) return;
+    const uint32_t i = blockIdx.x % MO_REG, share = B.qcap / MO_REG;
+    const uint32_t q = atomicAdd(&B.ctl->rec[i][0], 1u);
+    if (q < share) B.rec[(size_t)i * share + q] = make_uint4(r, k, tri, place);
+    else B.ctl->err = 1u;
 }
+
+// The critical triangles of one edge, in the order of their vertices: the
+// components come with rising first vertices but for the one the search
+// began with, which waits for its turn.
+struct MoPending {
+    uint32_t x;  // its first vertex (position in L(r)), MO_NONE: none
+    uint32_t k;
+};
 
 // The least (rank, position) over the wave of the lanes' ranks x (INT_MAX:
 // none) at positions i: the rank; *at = its position.
@@ -165,8 +180,9 @@ __device__ __forceinline__ int32_t mo_wave_min(int32_t x, uint32_t i, uint32_t *
 
 // L(r) of any size: its pieces read again from the keys at each step, the
 // sets as bit masks in the wave's LDS (reached, to expand, this component).
-__device__ void mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b, int32_t f0, uint32_t m,
-                            unsigned long long *reach, unsigned long long *open, unsigned long long *comp) {
+__device__ int2 mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b, int32_t f0, uint32_t m,
+                            unsigned long long *reach, unsigned long long *open, unsigned long long *comp,
+                            uint32_t &place) {
     const uint32_t lane = lane_id();
     const uint32_t np = (m + VR_WAVE - 1) / VR_WAVE;
     const int32_t *Ra = B.R + (int64_t)a * B.n, *Rb = B.R + (int64_t)b * B.n;
@@ -198,6 +214,7 @@ __device__ void mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
     mo_wave_sync();
     uint32_t left = m;
     bool first_comp = true;
+    MoPending pend{MO_NONE, 0u};
     while (left > 0) {
         for (uint32_t p = lane; p < np; p += VR_WAVE) open[p] = comp[p] = 0ull;
         mo_wave_sync();
@@ -236,10 +253,16 @@ __device__ void mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
         uint32_t lo = 0;
         while (!comp[lo]) lo++;
         const uint32_t x0 = lo * VR_WAVE + (uint32_t)__builtin_ctzll(comp[lo]);
+        if (pend.x < x0 && x0 != 0) {
+            mo_append(B, r, pend.k, (uint32_t)f0 + pend.x, place++);
+            pend.x = MO_NONE;
+        }
         if (x0 == 0) {
             if (!first_comp) (void)nearest(false, &fx, &fy);
+        } else if (first_comp) {
+            pend = MoPending{x0, vertex(x0)};
         } else {
-            mo_append(B, r, vertex(x0), (uint32_t)f0 + x0, lane == 0);
+            mo_append(B, r, vertex(x0), (uint32_t)f0 + x0, place++);
         }
         first_comp = false;
         if (left > 0) {
@@ -255,37 +278,250 @@ __device__ void mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
         }
         mo_wave_sync();
     }
-    if (lane == 0) B.fg[r] = make_int2(fx, fy);
+    if (pend.x != MO_NONE) mo_append(B, r, pend.k, (uint32_t)f0 + pend.x, place++);
+    return make_int2(fx, fy);
 }
 
-// One wave per edge.  The search starts at the vertex nearest both ends,
-// which mostly joins every other vertex of L(r) at once: 1.2 (circle) to
-// about 2 (mixture) rows of R are read per edge.  Latency-bound: a chain of
-// about eight dependent loads per edge.
+// Up to MO_SNAPS snapshots of every vertex's older neighbours, one work-group
+// per vertex: the row's ranks set bits by the snapshot they first appear in,
+// and the snapshots are the running unions.  Bound by writing them: 4 n^2
+// bytes at 32 snapshots.
+__global__ __launch_bounds__(MO_BLOCK) void k_mo_snap(MoBufs B, int S) {
+    extern __shared__ uint32_t sbits[];  // S x 2 W
+    const int64_t v = blockIdx.x;
+    const int32_t *row = B.R + v * B.n;
+    const int w2 = 2 * B.W;
+    for (int x = threadIdx.x; x < S * w2; x += MO_BLOCK) sbits[x] = 0u;
+    __syncthreads();
+    for (int64_t k = threadIdx.x; k < B.n; k += MO_BLOCK) {
+        const int32_t r = row[k];
+        if (k != v && r != INT32_MAX && (r >> B.sb) < S)
+            atomicOr(&sbits[(r >> B.sb) * w2 + (int)(k >> 5)], 1u << (k & 31));
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < B.W; x += MO_BLOCK) {
+        unsigned long long u = 0;
+        for (int s = 0; s < S; s++) {
+            u |= ((unsigned long long)sbits[s * w2 + 2 * x + 1] << 32) | sbits[s * w2 + 2 * x];
+            B.snap[((int64_t)s * B.n + v) * B.W + x] = u;
+        }
+    }
+}
+
+// Whether L(r) is connected by the edges of a snapshot older than r: bits
+// of L(r) in the lanes (l0, l1: words lane and 64 + lane), searched on, four
+// rows at a time, from the vertices reached (g) of which some were expanded
+// (e).  Fewer edges than r allows, so "no" only means that it must be
+// looked at again.
+template <int NW>
+__device__ __forceinline__ bool mo_connected(const MoBufs &B, uint32_t snap, unsigned long long l0,
+                                             unsigned long long l1, unsigned long long g0, unsigned long long g1,
+                                             unsigned long long e0, unsigned long long e1) {
+    const uint32_t lane = lane_id();
+    const unsigned long long *rows = B.snap + (int64_t)(snap - 1) * B.n * B.W;
+    constexpr bool two = NW > 1;
+    const bool w0 = (int)lane < B.W, w1 = two && (int)lane + VR_WAVE < B.W;
+    for (;;) {
+        const unsigned long long o0 = g0 & ~e0, o1 = g1 & ~e1;  // reached, not expanded
+        const unsigned long long b0 = ballot64(o0 != 0ull), b1 = two ? ballot64(o1 != 0ull) : 0ull;
+        if (!(b0 | b1)) return false;
+        uint32_t v[4];
+        unsigned long long x0 = b0, x1 = b1;
+        int nv = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            v[i] = i ? v[0] : 0u;
+            if (x0) {
+                const int src = __builtin_ctzll(x0);
+                x0 &= x0 - 1;
+                const unsigned long long word =
+                    ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(o0 >> 32), src) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)o0, src);
+                v[i] = (uint32_t)src * 64 + (uint32_t)__builtin_ctzll(word);
+                if ((int)lane == src) e0 |= 1ull << (v[i] & 63);
+                nv = i + 1;
+            } else if (x1) {
+                const int src = __builtin_ctzll(x1);
+                x1 &= x1 - 1;
+                const unsigned long long word =
+                    ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(o1 >> 32), src) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)o1, src);
+                v[i] = (uint32_t)(src + VR_WAVE) * 64 + (uint32_t)__builtin_ctzll(word);
+                if ((int)lane == src) e1 |= 1ull << (v[i] & 63);
+                nv = i + 1;
+            }
+        }
+        unsigned long long a0 = 0, a1 = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (i < nv) {
+                const unsigned long long *row = rows + (int64_t)v[i] * B.W;
+                if (w0) a0 |= row[lane];
+                if (two && w1) a1 |= row[VR_WAVE + lane];
+            }
+        g0 |= a0 & l0;
+        if (two) g1 |= a1 & l1;
+        if (!ballot64((l0 & ~g0) != 0ull || (l1 & ~g1) != 0ull)) return true;
+    }
+}
+
+// A wave takes MO_EB edges.  The vertices of L(r) come from the triangles
+// of value r.  Nearly every L(r) is connected by the edges of the last
+// snapshot before r, which a few rows of 8 W bytes show: those of its first
+// vertex and of three others, then four at a time (2.4 steps of one row and
+// then four at the mixture).  The others, and the edges before the first
+// snapshot, go to k_mo_split: one in 20 there.  k* is the nearest to both
+// ends of 32 vertices, four runs of eight spread over L(r): a run's ranks
+// lie in few cache lines (32 single vertices took 1015 us at the mixture,
+// bound by 7.4 GB of lines), and the nearest of all shortens little.  Two
+// edges at a time, their loads issued together.  With exact searches in the
+// rank matrix, a line per vertex and row, it took 3890 us.
+template <int NW>
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
-    __shared__ unsigned long long masks[MO_WPB][3][MO_GEN];
+    constexpr int U = 2;
+    __shared__ unsigned long long sbits[MO_WPB][U][NW * VR_WAVE];
     const uint32_t lane = lane_id(), w = threadIdx.x / VR_WAVE;
-    const int64_t stride = (int64_t)gridDim.x * MO_WPB;
-    for (int64_t rr = (int64_t)blockIdx.x * MO_WPB + w; rr < B.K; rr += stride) {
-        const uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int)rr);
-        const int32_t f0 = B.first[r];
-        if (f0 < 0) {
-            int32_t c = -1;
-            if (B.e_low[r] < 0) {
-                if (lane == 0) {
-                    c = (int32_t)atomicAdd(&B.ctl->m, 1u);
-                    B.crit[c] = r;
-                    B.cnt[c] = 0u;
-                    B.fill[c] = 0u;
+    const int64_t blk = (int64_t)blockIdx.x * MO_WPB + w;
+    const int64_t r0 = blk * MO_EB;
+    if (r0 >= B.K) return;
+    // the block's edges, one a lane
+    const int64_t rl = r0 + lane;
+    const bool in = lane < MO_EB && rl < B.K;
+    int32_t f0 = -1, f1 = -1, ea = 0, eb = 0;
+    bool crit = false;
+    if (in) {
+        f0 = B.first[rl];
+        f1 = B.end[rl];
+        ea = B.ij[2 * rl];
+        eb = B.ij[2 * rl + 1];
+        crit = f0 < 0 && B.e_low[rl] < 0;
+    }
+    const unsigned long long mc = ballot64(crit), mt = ballot64(in && f0 >= 0);
+    if (in && f0 < 0) B.fg[rl] = make_int2(-1, crit ? (int32_t)mo_before(mc) : -1);
+    // edges before the first snapshot
+    const unsigned long long early = mt & ballot64(in && (rl >> B.sb) == 0);
+    unsigned long long todo = mt & ~early, left = early;
+    while (todo) {
+        uint32_t ix[U], sk[U], r[U], m[U], v[U][4];
+        int32_t f[U], sr[U], xa[U], xb[U];
+        unsigned long long row[U][4][NW];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            ix[u] = todo ? (uint32_t)__builtin_ctzll(todo) : ix[0];
+            todo &= todo - 1;  // 0 stays 0
+            r[u] = (uint32_t)r0 + ix[u];
+            f[u] = __builtin_amdgcn_readlane(f0, (int)ix[u]);
+            m[u] = (uint32_t)(__builtin_amdgcn_readlane(f1, (int)ix[u]) - f[u]);
+            xa[u] = __builtin_amdgcn_readlane(ea, (int)ix[u]);
+            xb[u] = __builtin_amdgcn_readlane(eb, (int)ix[u]);
+        }
+        unsigned long long ks[U], k0[U], k1[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            ks[u] = B.key[f[u] + (int32_t)min(((lane >> 3) & 3u) * (m[u] / 4) + (lane & 7u), m[u] - 1)];
+            k0[u] = B.key[f[u] + (int32_t)min(lane, m[u] - 1)];
+            k1[u] = B.key[f[u] + (int32_t)min(lane + VR_WAVE, m[u] - 1)];
+        }
+        mo_wave_sync();  // the bits of the edges before have been read
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int i = 0; i < NW; i++) sbits[w][u][i * VR_WAVE + lane] = 0ull;
+        mo_wave_sync();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            sk[u] = mo_third(ks[u], (uint32_t)xa[u], (uint32_t)xb[u]);
+            sr[u] = B.R[(int64_t)(lane < 32 ? xa[u] : xb[u]) * B.n + sk[u]];
+            const unsigned long long *rows = B.snap + (int64_t)((r[u] >> B.sb) - 1) * B.n * B.W;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                v[u][i] = (uint32_t)__builtin_amdgcn_readlane((int)sk[u], 8 * i);
+#pragma unroll
+                for (int j = 0; j < NW; j++)
+                    row[u][i][j] = (int)lane + j * VR_WAVE < B.W ? rows[(int64_t)v[u][i] * B.W + j * VR_WAVE + lane] : 0ull;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t a = (uint32_t)xa[u], b = (uint32_t)xb[u];
+            // positions past the list repeat its last vertex
+            uint32_t k = mo_third(k0[u], a, b);
+            atomicOr(&sbits[w][u][k >> 6], 1ull << (k & 63));
+            k = mo_third(k1[u], a, b);
+            if (m[u] > VR_WAVE) atomicOr(&sbits[w][u][k >> 6], 1ull << (k & 63));
+            for (uint32_t x = 2 * VR_WAVE; x < m[u]; x += VR_WAVE) {
+                k = mo_third(B.key[f[u] + (int32_t)min(x + lane, m[u] - 1)], a, b);
+                atomicOr(&sbits[w][u][k >> 6], 1ull << (k & 63));
+            }
+        }
+        mo_wave_sync();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            if (u > 0 && ix[u] == ix[0]) continue;
+            const unsigned long long l0 = sbits[w][u][lane], l1 = NW > 1 ? sbits[w][u][(NW - 1) * VR_WAVE + lane] : 0ull;
+            auto bit = [&](uint32_t k, int j) {
+                return lane + (uint32_t)j * VR_WAVE == (k >> 6) ? 1ull << (k & 63) : 0ull;
+            };
+            unsigned long long g0 = bit(v[u][0], 0), g1 = NW > 1 ? bit(v[u][0], 1) : 0ull, e0 = g0, e1 = g1;
+            g0 |= row[u][0][0] & l0;
+            if (NW > 1) g1 |= row[u][0][NW - 1] & l1;
+#pragma unroll
+            for (int i = 1; i < 4; i++) {
+                const unsigned long long b0 = bit(v[u][i], 0), b1 = NW > 1 ? bit(v[u][i], 1) : 0ull;
+                if (ballot64(((g0 & b0) | (g1 & b1)) != 0ull)) {  // reached: its row counts too
+                    g0 |= row[u][i][0] & l0;
+                    if (NW > 1) g1 |= row[u][i][NW - 1] & l1;
+                    e0 |= b0;
+                    e1 |= b1;
                 }
             }
-            if (lane == 0) B.fg[r] = make_int2(-1, c);
-            continue;
+            bool all = !ballot64((l0 & ~g0) != 0ull || (l1 & ~g1) != 0ull);
+            if (!all) all = mo_connected<NW>(B, r[u] >> B.sb, l0, l1, g0, g1, e0, e1);
+            if (!all) {
+                left |= 1ull << ix[u];
+                continue;
+            }
+            const int32_t own = max(sr[u], __shfl_xor(sr[u], 32, VR_WAVE));
+            int32_t best = own;
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, VR_WAVE));
+            const int at = __builtin_ctzll(ballot64(own == best));  // below 32
+            const int32_t fx = __builtin_amdgcn_readlane(sr[u], at), fy = __builtin_amdgcn_readlane(sr[u], at + 32);
+            if (lane == 0) B.fg[r[u]] = make_int2(fx, fy);
         }
+    }
+    if (lane == 0) {
+        B.mask[blk] = (uint32_t)left;
+        B.blk[blk] = 0u;
+        B.blkm[blk] = (uint32_t)__popcll(mc);
+    }
+}
+
+// The edges whose L(r) no snapshot showed to be connected, a block's by the
+// waves of a work-group in turn: searched in the rank matrix from the vertex
+// nearest both ends, component after component.
+__global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
+    __shared__ unsigned long long masks[MO_WPB][3][MO_GEN];
+    const uint32_t lane = lane_id(), w = threadIdx.x / VR_WAVE;
+    const int64_t blk = blockIdx.x;
+    uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.mask[blk]), turn = 0;
+    for (; left; left &= left - 1, turn++) {
+        if (turn % MO_WPB != w) continue;
+        const uint32_t r = (uint32_t)(blk * MO_EB) + (uint32_t)__builtin_ctz(left);
+        const int32_t f0 = B.first[r];
+        uint32_t place = 0;  // critical triangles of the edge so far
+        auto done = [&](int32_t fx, int32_t fy) {
+            if (lane == 0) {
+                B.fg[r] = make_int2(fx, fy);
+                B.ecnt[r] = place;
+                if (place) atomicAdd(&B.blk[blk], place);
+            }
+        };
         const uint32_t m = (uint32_t)(B.end[r] - f0);
         const uint32_t a = (uint32_t)B.ij[2 * (int64_t)r], b = (uint32_t)B.ij[2 * (int64_t)r + 1];
         if (m > MO_NC * VR_WAVE) {
-            mo_link_any(B, r, a, b, f0, m, masks[w][0], masks[w][1], masks[w][2]);
+            const int2 f = mo_link_any(B, r, a, b, f0, m, masks[w][0], masks[w][1], masks[w][2], place);
+            done(f.x, f.y);
             continue;
         }
         const int32_t *Ra = B.R + (int64_t)a * B.n, *Rb = B.R + (int64_t)b * B.n;
@@ -327,6 +563,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
         };
         uint32_t kstar = vertex(seed);
         bool first_comp = true;
+        MoPending pend{MO_NONE, 0u};
         for (;;) {
             unsigned long long open[MO_NC], comp[MO_NC];
 #pragma unroll
@@ -360,8 +597,13 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
 #pragma unroll
             for (int i = MO_NC - 1; i >= 0; i--)
                 if (comp[i]) x0 = (uint32_t)i * VR_WAVE + (uint32_t)__builtin_ctzll(comp[i]);
+            if (pend.x < x0 && x0 != 0) {
+                mo_append(B, r, pend.k, (uint32_t)f0 + pend.x, place++);
+                pend.x = MO_NONE;
+            }
             if (x0 != 0) {
-                mo_append(B, r, vertex(x0), (uint32_t)f0 + x0, lane == 0);
+                if (first_comp) pend = MoPending{x0, vertex(x0)};
+                else mo_append(B, r, vertex(x0), (uint32_t)f0 + x0, place++);
             } else if (!first_comp) {
                 best = INT32_MAX;
                 bx = 0;
@@ -381,25 +623,88 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
             for (int i = MO_NC - 1; i >= 0; i--)
                 if (todo[i]) seed = (uint32_t)i * VR_WAVE + (uint32_t)__builtin_ctzll(todo[i]);
         }
-        if (lane == 0) B.fg[r] = make_int2(Ra[kstar], Rb[kstar]);
+        if (pend.x != MO_NONE) mo_append(B, r, pend.k, (uint32_t)f0 + pend.x, place++);
+        done(Ra[kstar], Rb[kstar]);
     }
+}
+
+// Exclusive scan by one work-group of 1024 threads, four values a thread:
+// v(x) is value x of n, put(x, s) takes the sum before it.  Returns the total.
+template <typename V, typename P>
+__device__ __forceinline__ uint32_t mo_scan(uint32_t n, V v, P put) {
+    __shared__ uint32_t wt[16];
+    __shared__ uint32_t carry;
+    const uint32_t t = threadIdx.x, wv = t >> 6;
+    if (t == 0) carry = 0;
+    __syncthreads();
+    for (uint32_t base = 0; base < n; base += 4096) {
+        uint32_t e[4], own = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) {
+            const uint32_t x = base + 4 * t + u;
+            e[u] = x < n ? v(x) : 0u;
+            own += e[u];
+        }
+        const uint32_t inc = wave_incl_scan_dpp(own);
+        if ((t & 63) == 63) wt[wv] = inc;
+        __syncthreads();
+        uint32_t at = carry + inc - own, tot = 0;
+        for (uint32_t i = 0; i < 16; i++) {
+            if (i < wv) at += wt[i];
+            tot += wt[i];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) {
+            const uint32_t x = base + 4 * t + u;
+            if (x < n) put(x, at);
+            at += e[u];
+        }
+        __syncthreads();
+        if (t == 0) carry += tot;
+        __syncthreads();
+    }
+    return carry;
+}
+
+// Places: the blocks' critical triangles (work-group 0) and edges (1).
+__global__ __launch_bounds__(1024) void k_mo_order(MoBufs B) {
+    const uint32_t nb = (uint32_t)((B.K + MO_EB - 1) / MO_EB);
+    uint32_t *p = blockIdx.x == 0 ? B.blk : B.blkm;
+    const uint32_t tot = mo_scan(nb, [&](uint32_t x) { return p[x]; }, [&](uint32_t x, uint32_t s) { p[x] = s; });
+    if (threadIdx.x == 0) *(blockIdx.x == 0 ? &B.ctl->q : &B.ctl->m) = tot;
 }
 
 // One wave per critical triangle {r, k}: the edges ak, bk and r's two
 // replacements go on a stack; each lane takes one off it, and its two
 // replacements go back, or the critical edge it is into a list.  Edges an
 // even number of times in the list cancel.  Any order does, since every
-// replacement is older.
+// replacement is older.  The waves take the entries' slots MO_SLOTS at a
+// time (one atomic for each triangle, all at one address, took most of 207
+// us at the mixture) and mark those they leave.
+#define MO_SLOTS 128
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_expand(MoBufs B) {
     __shared__ uint32_t s_stack[MO_WPB][MO_STACK];
     __shared__ uint32_t s_list[MO_WPB][MO_STACK];
     const uint32_t lane = lane_id(), w = threadIdx.x / VR_WAVE;
     uint32_t *st = s_stack[w], *li = s_list[w];
-    const uint32_t nq = min(B.ctl->q, B.qcap);
-    for (uint32_t qq = blockIdx.x * MO_WPB + w; qq < nq; qq += gridDim.x * MO_WPB) {
-        const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane((int)qq);
-        const unsigned long long e = B.cent[q];
-        const uint32_t r = (uint32_t)(e >> (13 + MO_QBITS)), k = (uint32_t)(e >> MO_QBITS) & 0x1FFFu;
+    if (B.ctl->err) return;
+    // work-group b takes share b % MO_REG of the critical triangles
+    const uint32_t i = blockIdx.x % MO_REG, nq = B.ctl->rec[i][0];
+    const uint4 *recs = B.rec + (size_t)i * (B.qcap / MO_REG);
+    uint32_t slot = 0, slots = 0;  // entries' slots at hand
+    const uint32_t eshare = B.ecap / MO_REG;
+    uint2 *ent = B.ent + (size_t)i * eshare;
+    for (uint32_t qq = blockIdx.x / MO_REG * MO_WPB + w; qq < nq; qq += gridDim.x / MO_REG * MO_WPB) {
+        const uint4 rec = recs[(uint32_t)__builtin_amdgcn_readfirstlane((int)qq)];
+        const uint32_t r = rec.x, k = rec.y, r0 = r / MO_EB * MO_EB;
+        // its place: after those of the edges before r in the block
+        const uint32_t lt = B.mask[r / MO_EB] & ((1u << (r - r0)) - 1);
+        const uint32_t q = B.blk[r / MO_EB] + rec.w +
+                           wave_sum<uint32_t>(lane < MO_EB && ((lt >> lane) & 1u) ? B.ecnt[r0 + lane] : 0u);
+        if (lane == 0) {
+            B.ctri[q] = rec.z;
+            B.owner[q] = 0ull;
+        }
         const int64_t a = B.ij[2 * (int64_t)r], b = B.ij[2 * (int64_t)r + 1];
         const int2 f = B.fg[r];
         mo_wave_sync();  // the list of the previous triangle has been read
@@ -422,7 +727,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_expand(MoBufs B) {
                 over = true;
                 break;
             }
-            if (isc) li[nl + mo_before(mc)] = (uint32_t)g.y;
+            if (isc) li[nl + mo_before(mc)] = B.blkm[x / MO_EB] + (uint32_t)g.y;
             if (isn) {
                 const uint32_t at = sp + 2 * mo_before(mn);
                 st[at] = (uint32_t)g.x;
@@ -447,121 +752,52 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_expand(MoBufs B) {
             const bool keep = x < nl && (all & 1u) && before == 0;
             const unsigned long long mk = ballot64(keep);
             if (!mk) continue;
-            uint32_t e0 = 0;
-            if (lane == 0) e0 = atomicAdd(&B.ctl->nent, (uint32_t)__popcll(mk));
-            e0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)e0);
-            const uint32_t at = e0 + mo_before(mk);
-            if (keep) {
-                if (at < B.ecap) {
-                    B.ent[at] = make_uint2(c, q);
-                    atomicAdd(&B.cnt[c], 1u);
-                } else {
-                    B.ctl->err = 1u;
+            const uint32_t nk = (uint32_t)__popcll(mk);
+            if (nk > slots) {
+                for (uint32_t y = lane; y < slots; y += VR_WAVE) ent[slot + y] = make_uint2(MO_NONE, 0u);
+                if (lane == 0) slot = atomicAdd(&B.ctl->ent[i][0], (uint32_t)MO_SLOTS);
+                slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+                slots = MO_SLOTS;
+                if (slot + MO_SLOTS > eshare) {
+                    if (lane == 0) B.ctl->err = 1u;
+                    return;
                 }
             }
+            if (keep) {
+                ent[slot + mo_before(mk)] = make_uint2(c, q);
+                atomicAdd(&B.cnt[c], 1u);
+            }
+            slot += nk;
+            slots -= nk;
         }
     }
+    for (uint32_t y = lane; y < slots; y += VR_WAVE) ent[slot + y] = make_uint2(MO_NONE, 0u);
 }
 
 // Column c takes cnt[c] + 1 pool words (its length first), back to back.
 __global__ __launch_bounds__(1024) void k_mo_scan(MoBufs B) {
-    __shared__ uint32_t wt[16];
-    __shared__ uint32_t carry;
-    const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6, m = B.ctl->m;
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < m; base += 1024) {
-        const uint32_t c = base + t, len = c < m ? B.cnt[c] : 0u, x = c < m ? len + 1 : 0u;
-        const uint32_t inc = wave_incl_scan_dpp(x);
-        if (lane == 63) wt[wv] = inc;
-        __syncthreads();
-        uint32_t off = carry, tot = 0;
-        for (uint32_t i = 0; i < 16; i++) {
-            if (i < wv) off += wt[i];
-            tot += wt[i];
-        }
-        if (c < m) {
-            const uint32_t s0 = off + inc - x;
-            B.start[c] = s0;
-            if (s0 < B.pcap) B.pool[s0] = len;
-        }
-        __syncthreads();
-        if (t == 0) carry += tot;
-        __syncthreads();
-    }
-    if (t == 0) {
-        B.ctl->ptop = carry;
-        if (carry > B.pcap) B.ctl->err = 1u;
-    }
+    const uint32_t m = B.ctl->m;
+    const uint32_t tot = mo_scan(m, [&](uint32_t c) { return B.cnt[c] + 1u; },
+                                 [&](uint32_t c, uint32_t s0) {
+                                     B.start[c] = s0;
+                                     B.pool[s0] = B.cnt[c];  // m + nent words: always room
+                                 });
+    if (threadIdx.x == 0) B.ctl->ptop = tot;
 }
 
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_scatter(MoBufs B) {
     if (B.ctl->err) return;
-    const uint32_t ne = B.ctl->nent;
-    for (uint32_t x = blockIdx.x * MO_BLOCK + threadIdx.x; x < ne; x += gridDim.x * MO_BLOCK) {
-        const uint2 e = B.ent[x];
-        B.pool[B.start[e.x] + 1 + atomicAdd(&B.fill[e.x], 1u)] = B.cent[e.y];
+    const uint32_t x0 = blockIdx.x * MO_BLOCK + threadIdx.x;
+    const uint32_t i = blockIdx.x % MO_REG, ne = B.ctl->ent[i][0];
+    const uint2 *ent = B.ent + (size_t)i * (B.ecap / MO_REG);
+    for (uint32_t x = blockIdx.x / MO_REG * MO_BLOCK + threadIdx.x; x < ne; x += gridDim.x / MO_REG * MO_BLOCK) {
+        const uint2 e = ent[x];
+        if (e.x != MO_NONE) B.pool[B.start[e.x] + 1 + atomicAdd(&B.fill[e.x], 1u)] = e.y;
     }
-}
-
-// Ascending bitonic sort of n entries in LDS by one wave, padded to a power
-// of two (the buffer holds that many).
-__device__ void mo_sort(unsigned long long *g, uint32_t n) {
-    const uint32_t lane = lane_id();
-    uint32_t P = 1;
-    while (P < n) P <<= 1;
-    for (uint32_t x = n + lane; x < P; x += VR_WAVE) g[x] = ~0ull;
-    mo_wave_sync();
-    for (uint32_t kk = 2; kk <= P; kk <<= 1)
-        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-            for (uint32_t i = lane; i < P / 2; i += VR_WAVE) {
-                const uint32_t lo = 2 * i - (i & (j - 1)), hi = lo + j;
-                const unsigned long long x0 = g[lo], x1 = g[hi];
-                if ((x0 > x1) == ((lo & kk) == 0)) {
-                    g[lo] = x1;
-                    g[hi] = x0;
-                }
-            }
-            mo_wave_sync();
-        }
-}
-
-// o = a + b over F2 by one wave (sorted entries, na + nb of room in o):
-// merge path, a run of the merged list per lane, then the entries in both
-// (next to each other) are dropped in place.  Returns the length.
-template <typename PA, typename PB, typename PO>
-__device__ __forceinline__ uint32_t mo_add(PA a, uint32_t na, PB b, uint32_t nb, PO o) {
-    const uint32_t lane = lane_id(), L = na + nb, S = (L + VR_WAVE - 1) / VR_WAVE;
-    const uint32_t d0 = min(L, lane * S), d1 = min(L, d0 + S);
-    uint32_t lo = d0 > nb ? d0 - nb : 0u, hi = min(d0, na);
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] <= b[d0 - 1 - mid]) lo = mid + 1;
-        else hi = mid;
+    for (int64_t r = x0; r < B.K; r += (int64_t)gridDim.x * MO_BLOCK) {
+        const int2 g = B.fg[r];
+        if (g.x < 0 && g.y >= 0) B.crit[B.blkm[r / MO_EB] + (uint32_t)g.y] = (uint32_t)r;
     }
-    uint32_t i = lo, j = d0 - lo;
-    for (uint32_t d = d0; d < d1; d++) {
-        const bool ta = j >= nb || (i < na && a[i] <= b[j]);
-        o[d] = ta ? a[i++] : b[j++];
-    }
-    mo_wave_sync();
-    // a kept entry never moves up, and an entry moved over is the one it was
-    uint32_t run = 0;
-    for (uint32_t x0 = 0; x0 < L; x0 += VR_WAVE) {
-        const uint32_t x = x0 + lane;
-        unsigned long long v = 0;
-        bool keep = false;
-        if (x < L) {
-            v = o[x];
-            keep = (x == 0 || o[x - 1] != v) && (x + 1 == L || o[x + 1] != v);
-        }
-        const unsigned long long mk = ballot64(keep);
-        mo_wave_sync();
-        if (keep) o[run + mo_before(mk)] = v;
-        mo_wave_sync();
-        run += (uint32_t)__popcll(mk);
-    }
-    return run;
 }
 
 // The reduction: one wave per column at a time, columns from the youngest
@@ -577,116 +813,134 @@ __device__ __forceinline__ uint32_t mo_add(PA a, uint32_t na, PB b, uint32_t nb,
 // (the pivot moves to a younger triangle), takes a free pivot, or hands a
 // pivot to a younger edge.  (The lock-free reduction of Morozov and
 // Nigmetov, "Towards lockfree persistent homology", 2020.)
-__global__ __launch_bounds__(VR_WAVE) void k_mo_reduce(MoBufs B) {
-    __shared__ unsigned long long buf[3 * MO_CAP];
+//
+// The working column is a bit per critical triangle (in LDS up to MO_LDS_Q
+// of them, else in device memory): an addition flips the added entries'
+// bits, and the pivot is the first set bit from the last one on.  Latency
+// bounds it: an addition is two dependent reads from memory.  As sorted
+// lists merged in LDS it took 1776 us at the mixture.
+template <bool LDS>
+__device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *bits, uint32_t nw) {
     const uint32_t lane = lane_id();
-    if (B.ctl->err) return;
     const uint32_t m = B.ctl->m;
-    // n pool words for the wave; ~0 (and the error flagged) when there is no room
-    auto take = [&](uint32_t words) -> unsigned long long {
-        unsigned long long p = 0;
-        if (lane == 0) {
-            p = atomicAdd(&B.ctl->ptop, (unsigned long long)words);
-            if (p + words > B.pcap) {
-                p = ~0ull;
-                B.ctl->err = 1u;
-            }
-        }
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
-        return ((unsigned long long)hi << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    // bits in device memory are flipped in L2: they are read and cleared there
+    auto get = [&](uint32_t x) { return x >= nw ? 0ull : LDS ? bits[x] : st_load64(bits + x); };
+    auto clear = [&](uint32_t x) {
+        if (LDS) bits[x] = 0ull;
+        else st_store64(bits + x, 0ull);
     };
-    for (;;) {
-        uint32_t nx = 0;
-        if (lane == 0) nx = atomicAdd(&B.ctl->next, 1u);
-        nx = (uint32_t)__builtin_amdgcn_readfirstlane((int)nx);
-        if (nx >= m) return;
+    auto sync = [&] {
+        if (LDS) mo_wave_sync();
+        else __threadfence();
+    };
+    for (uint32_t x = lane; x < nw; x += VR_WAVE) clear(x);
+    sync();
+    auto flip = [&](const uint32_t *e, uint32_t len) {
+        for (uint32_t x = lane; x < len; x += VR_WAVE) {
+            const uint32_t q = e[x];
+            atomicXor(&bits[q >> 6], 1ull << (q & 63));
+        }
+    };
+    // a column stored from pool word p: its length and first entries in one read
+    auto add = [&](uint32_t p) {
+        const uint32_t e = p + lane < B.pcap ? B.pool[p + lane] : 0u;
+        const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)e);
+        if (lane > 0 && lane <= len) atomicXor(&bits[e >> 6], 1ull << (e & 63));
+        if (len >= VR_WAVE) flip(B.pool + p + VR_WAVE, len - (VR_WAVE - 1));
+    };
+    const uint32_t nwaves = LDS ? gridDim.x : MO_GWAVES;
+    for (uint32_t nx = blockIdx.x; nx < m; nx += nwaves) {
         const uint32_t c = m - 1 - nx;
-        uint32_t r = B.crit[c], len = B.cnt[c], pub = B.start[c];
-        if (len == 0) continue;  // in no boundary: a class that never dies
-        if (len > 2 * MO_CAP) {
-            if (lane == 0) B.ctl->err = 1u;
-            continue;
-        }
-        // the column's entries, sorted, back to their place
-        unsigned long long *cur = buf;  // the column lies here (LDS), or in the pool from gcur (gcur != null)
-        const unsigned long long *gcur = nullptr;
-        for (uint32_t x = lane; x < len; x += VR_WAVE) buf[x] = B.pool[pub + 1 + x];
-        mo_wave_sync();
-        if (len > 1) {
-            mo_sort(buf, len);
-            for (uint32_t x = lane; x < len; x += VR_WAVE) B.pool[pub + 1 + x] = buf[x];
-        }
-        if (len > MO_CAP) gcur = B.pool + pub + 1;
-        mo_wave_sync();
+        uint32_t r = B.crit[c], pub = B.start[c];
+        uint32_t wi = 0;  // no bit is set before this word
         bool dirty = false;
-        while (len > 0) {
-            const unsigned long long p = gcur ? gcur[0] : cur[0];
-            const uint32_t q = (uint32_t)p & ((1u << MO_QBITS) - 1);
+        add(pub);
+        for (;;) {
+            sync();
+            // the pivot: the first set bit
+            uint32_t q = MO_NONE;
+            for (; wi < nw; wi += VR_WAVE) {
+                const unsigned long long v = get(wi + lane);
+                const unsigned long long any = ballot64(v != 0ull);
+                if (any) {
+                    const int src = __builtin_ctzll(any);
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, src);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), src);
+                    wi += (uint32_t)src;
+                    q = wi * 64 + (lo ? (uint32_t)__builtin_ctz(lo) : 32u + (uint32_t)__builtin_ctz(hi));
+                    break;
+                }
+            }
+            if (q == MO_NONE) break;  // zero: a class that never dies
             const unsigned long long wv = __hip_atomic_load(&B.owner[q], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t whi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(wv >> 32));
             const uint32_t wlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)wv);
-            if (whi == 0 || whi - 1 < r) {
-                if (dirty) {
-                    const unsigned long long o = take(len + 1);
-                    if (o == ~0ull) break;
-                    pub = (uint32_t)o;
-                    if (lane == 0) B.pool[pub] = len;
-                    for (uint32_t x = lane; x < len; x += VR_WAVE) B.pool[pub + 1 + x] = gcur ? gcur[x] : cur[x];
-                    dirty = false;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                uint32_t won = 0;
-                if (lane == 0) {
-                    unsigned long long want = ((unsigned long long)whi << 32) | wlo;
-                    won = __hip_atomic_compare_exchange_strong(&B.owner[q], &want,
-                                                               ((unsigned long long)(r + 1) << 32) | pub,
-                                                               __ATOMIC_RELEASE, __ATOMIC_RELAXED,
-                                                               __HIP_MEMORY_SCOPE_AGENT)
-                              ? 1u
-                              : 0u;
-                }
-                won = (uint32_t)__builtin_amdgcn_readfirstlane((int)won);
-                if (!won) continue;  // the owner changed: look again
-                if (whi == 0) break;
-                // the displaced column goes on from its stored entries
-                r = whi - 1;
-                pub = wlo;
-                len = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)B.pool[pub]);
-                gcur = B.pool + pub + 1;
-                if (len <= MO_CAP) {
-                    mo_wave_sync();
-                    for (uint32_t x = lane; x < len; x += VR_WAVE) cur[x] = gcur[x];
-                    gcur = nullptr;
-                }
-                mo_wave_sync();
+            if (whi != 0 && whi - 1 > r) {
+                add(wlo);
+                dirty = true;
                 continue;
             }
-            const uint32_t nb = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)B.pool[wlo]);
-            const unsigned long long *gb = B.pool + wlo + 1;
-            dirty = true;
-            if (!gcur && len + nb <= MO_CAP) {
-                unsigned long long *sb = buf + 2 * MO_CAP, *o = cur == buf ? buf + MO_CAP : buf;
-                for (uint32_t x = lane; x < nb; x += VR_WAVE) sb[x] = gb[x];
-                mo_wave_sync();
-                len = mo_add(cur, len, sb, nb, o);
-                cur = o;
-            } else {
-                // a long column: the sum in the pool
-                const unsigned long long o = take(len + nb);
-                if (o == ~0ull) break;
-                unsigned long long *go = B.pool + o;
-                len = gcur ? mo_add(gcur, len, gb, nb, go) : mo_add(cur, len, gb, nb, go);
-                gcur = go;
-                if (len <= MO_CAP) {
-                    for (uint32_t x = lane; x < len; x += VR_WAVE) cur[x] = go[x];
-                    gcur = nullptr;
+            if (dirty) {  // store the column
+                uint32_t len = 0;
+                for (uint32_t x = wi; x < nw; x += VR_WAVE)
+                    len += (uint32_t)__popcll(get(x + lane));
+                len = wave_sum<uint32_t>(len);
+                unsigned long long p = 0;
+                if (lane == 0) p = atomicAdd(&B.ctl->ptop, (unsigned long long)(len + 1));
+                const bool room = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) == 0 &&
+                                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) + len + 1 <= B.pcap;
+                if (!room) {
+                    if (lane == 0) B.ctl->err = 1u;
+                    return;
                 }
-                mo_wave_sync();
+                pub = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+                if (lane == 0) B.pool[pub] = len;
+                uint32_t at = pub + 1;
+                for (uint32_t x = wi; x < nw; x += VR_WAVE) {
+                    unsigned long long v = get(x + lane);
+                    const uint32_t pc = (uint32_t)__popcll(v), inc = wave_incl_scan_dpp(pc);
+                    uint32_t o = at + inc - pc;
+                    while (v) {
+                        B.pool[o++] = (x + lane) * 64 + (uint32_t)__builtin_ctzll(v);
+                        v &= v - 1;
+                    }
+                    at += wave_last(inc);
+                }
+                dirty = false;
             }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            uint32_t won = 0;
+            if (lane == 0) {
+                unsigned long long want = ((unsigned long long)whi << 32) | wlo;
+                won = __hip_atomic_compare_exchange_strong(&B.owner[q], &want,
+                                                           ((unsigned long long)(r + 1) << 32) | pub, __ATOMIC_RELEASE,
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          ? 1u
+                          : 0u;
+            }
+            won = (uint32_t)__builtin_amdgcn_readfirstlane((int)won);
+            if (!won) continue;  // the owner changed: look again
+            for (uint32_t x = wi + lane; x < nw; x += VR_WAVE) clear(x);
+            if (whi == 0) break;
+            // the displaced column goes on from its stored entries
+            r = whi - 1;
+            pub = wlo;
+            sync();
+            add(pub);
         }
-        mo_wave_sync();  // the buffers are reused by the next column
+        sync();
     }
 }
+
+__global__ __launch_bounds__(VR_WAVE) void k_mo_reduce(MoBufs B) {
+    __shared__ unsigned long long bits[MO_LDS_Q / 64];
+    if (B.ctl->err) return;
+    const uint32_t nq = B.ctl->q, nw = (nq + 63) / 64;
+    if (nq <= MO_LDS_Q) mo_reduce<true>(B, bits, nw);
+    else if (blockIdx.x < MO_GWAVES)  // the entries' array is free by now
+        mo_reduce<false>(B, (unsigned long long *)B.ent + (size_t)blockIdx.x * (MO_QCAP / 64), nw);
+}
+static_assert(8 * MO_ENT >= MO_GWAVES * (MO_QCAP / 8), "the bits of k_mo_reduce's waves fit the entries' array");
 
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_emit(MoBufs B) {
     if (B.ctl->err) return;
@@ -699,8 +953,11 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_emit(MoBufs B) {
 
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_init(MoBufs B) {
     const int64_t x = (int64_t)blockIdx.x * MO_BLOCK + threadIdx.x;
-    if (x == 0) *B.ctl = MoCtl{};
-    for (int64_t r = x; r < B.K; r += (int64_t)gridDim.x * MO_BLOCK) B.first[r] = -1;
+    for (int64_t i = x; i < (int64_t)(sizeof(MoCtl) / 4); i += (int64_t)gridDim.x * MO_BLOCK) ((uint32_t *)B.ctl)[i] = 0u;
+    for (int64_t r = x; r < B.K; r += (int64_t)gridDim.x * MO_BLOCK) {
+        B.first[r] = -1;
+        B.cnt[r] = B.fill[r] = 0u;
+    }
 }
 
 static unsigned mo_grid(int64_t items, int64_t most) {
@@ -720,9 +977,13 @@ int morse_pairs_dim1(const int32_t *R, const int32_t *ij, const unsigned long lo
     B.K = K;
     B.T = T;
     B.first = tri_of_edge;
-    B.qcap = (uint32_t)(T < MO_QCAP ? T : MO_QCAP);
+    B.qcap = (uint32_t)MO_QCAP;
     B.ecap = (uint32_t)MO_ENT;
-    B.pcap = (unsigned long long)MO_POOL;
+    B.pcap = (uint32_t)MO_POOL;
+    B.W = (int)((n + 63) / 64);
+    while ((K >> B.sb) > MO_SNAPS) B.sb++;  // snapshots at ranks 1 << sb, 2 << sb, ...
+    const int S = (int)(K >> B.sb);
+    const int64_t nblk = (K + MO_EB - 1) / MO_EB;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t o = 0;
     auto part = [&](size_t bytes) {
@@ -732,8 +993,9 @@ int morse_pairs_dim1(const int32_t *R, const int32_t *ij, const unsigned long lo
     };
     const size_t o_end = part(4 * (size_t)K), o_fg = part(8 * (size_t)K), o_crit = part(4 * (size_t)K);
     const size_t o_cnt = part(4 * (size_t)K), o_fill = part(4 * (size_t)K), o_start = part(4 * (size_t)K);
-    const size_t o_cent = part(8 * (size_t)B.qcap), o_ctri = part(4 * (size_t)B.qcap), o_own = part(8 * (size_t)B.qcap);
-    const size_t o_ent = part(8 * (size_t)B.ecap), o_pool = part(8 * (size_t)B.pcap), o_ctl = part(sizeof(MoCtl));
+    const size_t o_rec = part(16 * (size_t)B.qcap), o_ctri = part(4 * (size_t)B.qcap), o_own = part(8 * (size_t)B.qcap);
+    const size_t o_ent = part(8 * (size_t)B.ecap), o_pool = part(4 * (size_t)B.pcap), o_ctl = part(sizeof(MoCtl));
+    const size_t o_snap = part(8 * (size_t)S * (size_t)n * (size_t)B.W), o_blk = part(12 * (size_t)nblk), o_ecnt = part(4 * (size_t)K);
     char *ws = (char *)cache_get(o, s);
     if (!ws) return VR_ENOMEM;
     B.end = (int32_t *)(ws + o_end);
@@ -742,27 +1004,36 @@ int morse_pairs_dim1(const int32_t *R, const int32_t *ij, const unsigned long lo
     B.cnt = (uint32_t *)(ws + o_cnt);
     B.fill = (uint32_t *)(ws + o_fill);
     B.start = (uint32_t *)(ws + o_start);
-    B.cent = (unsigned long long *)(ws + o_cent);
+    B.rec = (uint4 *)(ws + o_rec);
     B.ctri = (uint32_t *)(ws + o_ctri);
     B.owner = (unsigned long long *)(ws + o_own);
     B.ent = (uint2 *)(ws + o_ent);
-    B.pool = (unsigned long long *)(ws + o_pool);
+    B.pool = (uint32_t *)(ws + o_pool);
     B.ctl = (MoCtl *)(ws + o_ctl);
-    const int64_t wg = (K + MO_WPB - 1) / MO_WPB;
+    B.snap = (unsigned long long *)(ws + o_snap);
+    B.blk = (uint32_t *)(ws + o_blk);
+    B.blkm = B.blk + nblk;
+    B.mask = B.blkm + nblk;
+    B.ecnt = (uint32_t *)(ws + o_ecnt);
+    const int64_t wg = (nblk + MO_WPB - 1) / MO_WPB;
     hipLaunchKernelGGL(k_mo_init, dim3(mo_grid(K, 4096)), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_range, dim3(mo_grid((T + 1) / 2, 65536)), dim3(MO_BLOCK), 0, s, B);
-    hipLaunchKernelGGL(k_mo_link, dim3((unsigned)(wg < 8192 ? wg : 8192)), dim3(MO_BLOCK), 0, s, B);
-    hipLaunchKernelGGL(k_mo_expand, dim3((unsigned)(wg < 2048 ? wg : 2048)), dim3(MO_BLOCK), 0, s, B);
+    hipLaunchKernelGGL(k_mo_snap, dim3((unsigned)n), dim3(MO_BLOCK), 8 * (size_t)S * (size_t)B.W, s, B, S);
+    if (B.W > VR_WAVE) hipLaunchKernelGGL(k_mo_link<2>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);
+    else hipLaunchKernelGGL(k_mo_link<1>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);
+    hipLaunchKernelGGL(k_mo_split, dim3((unsigned)nblk), dim3(MO_BLOCK), 0, s, B);
+    hipLaunchKernelGGL(k_mo_order, dim3(2), dim3(1024), 0, s, B);
+    hipLaunchKernelGGL(k_mo_expand, dim3(2048), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_scan, dim3(1), dim3(1024), 0, s, B);
     hipLaunchKernelGGL(k_mo_scatter, dim3(512), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_reduce, dim3(1280), dim3(VR_WAVE), 0, s, B);
     hipLaunchKernelGGL(k_mo_emit, dim3(256), dim3(MO_BLOCK), 0, s, B);
-    MoCtl hc{};
+    uint32_t err = 0;
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&hc, B.ctl, sizeof(hc), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&err, &B.ctl->err, sizeof(err), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     cache_put(ws, s);
     if (e != hipSuccess) return VR_EHIP;
-    *done = hc.err == 0;
+    *done = err == 0;
     return VR_OK;
 }
