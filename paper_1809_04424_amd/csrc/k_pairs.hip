@@ -10,19 +10,11 @@
 // largest edge rank on the path (+inf when no path exists); v with no
 // finite death is the oldest vertex of its component and never dies.
 //
-// minimax over all pairs is the closure of the rank matrix in the (min, max)
-// semiring: a blocked Floyd-Warshall in 64 x 64 tiles.
+// The edges that give those deaths are the spanning forest in rank order.
 //   k_pd_fill     D = +inf off the diagonal, -1 on it
 //   k_pd_edges    D[i][j] = D[j][i] = r per kept edge
-//   k_pd_diag     phase 1: the diagonal tile, pivots in order
-//   k_pd_cross    phase 2: the tiles in the pivot's row and column, each a
-//                 (min, max) product with the closed diagonal tile
-//   k_pd_rest     phase 3: every other tile, the product of a column tile
-//                 and a row tile
-//   k_pd_death    death(v): a wave takes the minimum of row v left of v
-//   k_pd_clear, k_pd_emit   e_low[r] = v for death(v) = r, else -1
-// D is (nb * 64)^2 with the padding vertices isolated, so the tile kernels
-// need no bounds tests.
+//   k_pf_filter   the edges of a stretch of ranks that join two components
+//   k_pf_join     those edges, in rank order, into a union-find
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -30,13 +22,8 @@
 #include "vr_cache.h"
 #include "vr_morse.h"
 
-#define PD_T 64      // tile edge
-#define PD_BLOCK 256  // 16 x 16 threads, 4 x 4 entries each
+#define PD_BLOCK 256
 #define PD_INF 0x7FFFFFFF
-// Largest point count whose dimension-0 pairs come from the (min, max)
-// closure; larger clouds use the spanning forest.
-#define PD_CLOSURE_MAX 512
-
 __global__ void __launch_bounds__(PD_BLOCK) k_pd_fill(int32_t *D, int64_t m) {
     const int64_t ld = m;
     for (int64_t x = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; x < ld * ld; x += (int64_t)gridDim.x * PD_BLOCK)
@@ -53,217 +40,222 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_edges(int32_t *D, int64_t ld, c
     }
 }
 
-// In the tile kernels thread (ty, tx) owns rows 4ty..4ty+3 and columns
-// 4tx..4tx+3 of a tile.
-
-// phase 1: D_kk closed over its own 64 pivots, in order, by 1024 threads of
-// 2 x 2 entries each (thread (ty, tx) of 32 x 32: rows 2ty, 2ty+1, columns
-// 2tx, 2tx+1), which keeps the work between two pivots short.  The entries
-// stay in registers; after pivot k the owners of row k+1 and column k+1
-// publish them to LDS for the next pivot.  Row k and column k do not change
-// at pivot k (D[k][k] = -1), and the entries written after pivot k are not
-// the ones read at pivot k, so one barrier per pivot suffices.
-#define PD_DIAG_BLOCK 1024
-__global__ void __launch_bounds__(PD_DIAG_BLOCK) k_pd_diag(int32_t *D, int64_t ld, int64_t kb) {
-    __shared__ __align__(16) int32_t s[PD_T][PD_T + 4];
-    const int ty = threadIdx.x >> 5, tx = threadIdx.x & 31;
-    int32_t acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; a++) {
-        const int2 v = *(const int2 *)(D + (kb * PD_T + 2 * ty + a) * ld + kb * PD_T + 2 * tx);
-        acc[a][0] = v.x;
-        acc[a][1] = v.y;
-        *(int2 *)&s[2 * ty + a][2 * tx] = v;
-    }
-    __syncthreads();
-    for (int k = 0; k < PD_T; k++) {
-        const int32_t c0 = s[2 * ty][k], c1 = s[2 * ty + 1][k];
-        const int2 r = *(const int2 *)&s[k][2 * tx];
-        acc[0][0] = min(acc[0][0], max(c0, r.x));
-        acc[0][1] = min(acc[0][1], max(c0, r.y));
-        acc[1][0] = min(acc[1][0], max(c1, r.x));
-        acc[1][1] = min(acc[1][1], max(c1, r.y));
-        const int k1 = k + 1;
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-            if (2 * ty + a == k1) *(int2 *)&s[k1][2 * tx] = make_int2(acc[a][0], acc[a][1]);
-#pragma unroll
-        for (int b = 0; b < 2; b++)
-            if (2 * tx + b == k1) {
-                s[2 * ty][k1] = acc[0][b];
-                s[2 * ty + 1][k1] = acc[1][b];
-            }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int a = 0; a < 2; a++)
-        *(int2 *)(D + (kb * PD_T + 2 * ty + a) * ld + kb * PD_T + 2 * tx) = make_int2(acc[a][0], acc[a][1]);
-}
-
-// out = min(out, A (min,max) B) for 64 x 64 tiles A = (ai, aj), B = (bi, bj),
-// out = (oi, oj); out may be A or B (all reads precede the writes)
-static __device__ __forceinline__ void pd_product(int32_t *D, int64_t ld, int64_t ai, int64_t aj, int64_t bi,
-                                                  int64_t bj, int64_t oi, int64_t oj) {
-    __shared__ __align__(16) int32_t at[PD_T][PD_T + 4];  // A transposed: at[m][i]
-    __shared__ __align__(16) int32_t bt[PD_T][PD_T + 4];  // B: bt[m][j]
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-        const int4 v = *(const int4 *)(D + (ai * PD_T + 4 * ty + a) * ld + aj * PD_T + 4 * tx);
-        at[4 * tx + 0][4 * ty + a] = v.x;
-        at[4 * tx + 1][4 * ty + a] = v.y;
-        at[4 * tx + 2][4 * ty + a] = v.z;
-        at[4 * tx + 3][4 * ty + a] = v.w;
-        *(int4 *)&bt[4 * ty + a][4 * tx] = *(const int4 *)(D + (bi * PD_T + 4 * ty + a) * ld + bj * PD_T + 4 * tx);
-    }
-    int32_t acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-        const int4 v = *(const int4 *)(D + (oi * PD_T + 4 * ty + a) * ld + oj * PD_T + 4 * tx);
-        acc[a][0] = v.x;
-        acc[a][1] = v.y;
-        acc[a][2] = v.z;
-        acc[a][3] = v.w;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int m = 0; m < PD_T; m++) {
-        const int4 c = *(const int4 *)&at[m][4 * ty];
-        const int4 r = *(const int4 *)&bt[m][4 * tx];
-        const int32_t cv[4] = {c.x, c.y, c.z, c.w}, rv[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int b = 0; b < 4; b++) acc[a][b] = min(acc[a][b], max(cv[a], rv[b]));
-    }
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-        *(int4 *)(D + (oi * PD_T + 4 * ty + a) * ld + oj * PD_T + 4 * tx) =
-            make_int4(acc[a][0], acc[a][1], acc[a][2], acc[a][3]);
-}
-
-// phase 2: with D_kk closed, the tiles of the pivot's row and column need
-// one product each: row tile (kb, o) = D_kk (min,max) itself, column tile
-// (o, kb) = itself (min,max) D_kk.  Work-group g < nb: row tile (kb, g);
-// nb <= g < 2 nb: column tile (g - nb, kb).
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_cross(int32_t *D, int64_t ld, int64_t kb, int64_t nb) {
-    const int64_t g = blockIdx.x;
-    const bool row = g < nb;
-    const int64_t o = row ? g : g - nb;
-    if (o == kb) return;
-    if (row) pd_product(D, ld, kb, kb, kb, o, kb, o);
-    else pd_product(D, ld, o, kb, kb, kb, o, kb);
-}
-
-// phase 3: tile (bi, bj) off the pivot's row and column takes the product
-// of column tile (bi, kb) and row tile (kb, bj)
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_rest(int32_t *D, int64_t ld, int64_t kb, int64_t nb) {
-    const int64_t bi = blockIdx.y, bj = blockIdx.x;
-    if (bi == kb || bj == kb) return;
-    pd_product(D, ld, bi, kb, kb, bj, bi, bj);
-}
-
-// death(v) = min over u < v of D[v][u]; -1 when none is finite
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_death(const int32_t *D, int64_t ld, int64_t n, int32_t *death) {
-    const int lane = threadIdx.x & 63;
-    const int64_t v = blockIdx.x * (int64_t)(PD_BLOCK / 64) + (threadIdx.x >> 6);
-    if (v >= n) return;
-    int32_t m = PD_INF;
-    for (int64_t u = lane; u < v; u += 64) m = min(m, D[v * ld + u]);
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) m = min(m, __shfl_xor(m, d, 64));
-    if (lane == 0) death[v] = m == PD_INF ? -1 : m;
-}
-
 __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K) {
     for (int64_t r = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; r < K; r += (int64_t)gridDim.x * PD_BLOCK)
         e_low[r] = -1;
 }
 
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_emit(const int32_t *death, int64_t n, int32_t *e_low, int64_t K) {
-    const int64_t v = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x;
-    if (v >= n) return;
-    const int32_t r = death[v];
-    if (r >= 0 && r < K) e_low[r] = (int32_t)v;
+// Dimension 0 by a spanning forest (Kruskal's order): a union-find whose
+// roots are the smallest vertex of each component (the larger root is linked
+// under the smaller), so the column algorithm's pair for an edge joining two
+// components is the larger of the two roots.
+//
+// The ranks are taken in stretches: the first 2n edges, then as many again
+// as came before.  All work-groups look every edge of a stretch up against
+// the components before it and mark those that join two (few, once the
+// first stretches have joined most vertices); one work-group then takes the
+// marked edges in rank order, PF_BATCH at a time.  Within a batch, an edge
+// that is the first of its batch at the larger of its two roots joins at
+// once: that component is still what it was, the other's root can only have
+// become smaller, so the larger root is the one that dies.  Each round joins
+// every such edge (the oldest left is one), mostly half of what is left and
+// all that lead to one large component with a small root; joining only edges
+// first at both ends left most of the mixture's to the one thread.  After
+// PF_ROUNDS rounds one thread takes what is left in order (chains of edges
+// in rank order towards smaller vertices settle one edge a round).
+//
+// One work-group looking up every edge and one thread joining took 2270 us
+// at the 4000-point mixture and 420 us at the 1000-point circle, and the
+// (min, max) closure of the rank matrix 210 us at 400 points.
+#define PF_BLOCK 1024
+#define PF_BATCH (2 * PF_BLOCK)
+#define PF_ROUNDS 24
+
+struct PfBufs {
+    const int32_t *ij;
+    int64_t K, n;
+    int32_t *root;              // n: the component of each vertex, its smallest vertex
+    unsigned long long *mark;   // a bit per edge of the stretch
+    int32_t *joined;            // unions made
+    int32_t *e_low, *death;
+};
+
+__global__ void __launch_bounds__(PD_BLOCK) k_pf_init(PfBufs P) {
+    const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, st = (int64_t)gridDim.x * PD_BLOCK;
+    if (x0 == 0) *P.joined = 0;
+    for (int64_t v = x0; v < P.n; v += st) {
+        P.root[v] = (int32_t)v;
+        P.death[v] = -1;
+    }
+    for (int64_t r = x0; r < P.K; r += st) P.e_low[r] = -1;
 }
 
-// Dimension 0 by a spanning forest (Kruskal's order): the edges in rank
-// order, a union-find whose roots are the smallest vertex of each component
-// (the larger root is linked under the smaller), so the column algorithm's
-// pair for an edge joining two components is the larger of the two roots.
-// One work-group takes the edges 1024 at a time: every thread finds the
-// roots of its edge's ends without writing, and only the edges whose ends
-// lie in different components (the candidates) go, in rank order, through
-// the serial union by one thread, which finds again (an earlier candidate
-// of the chunk may have joined the two).  Work: K reads and finds, plus the
-// serial step for at most n - 1 unions and the candidates that lost to an
-// earlier one; it stops once n - 1 unions are made.
-#define PF_BLOCK 1024
-__global__ void __launch_bounds__(PF_BLOCK) k_pd_forest(const int32_t *ij, int64_t K, int64_t n, int32_t *e_low,
-                                                       int32_t *death) {
-    __shared__ int32_t par[VR_MAX_POINTS];
-    __shared__ int32_t cand[PF_BLOCK], ca[PF_BLOCK], cb[PF_BLOCK];
-    __shared__ uint32_t wc[PF_BLOCK / 64];
-    __shared__ int32_t s_unions;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    for (int64_t v = t; v < n; v += PF_BLOCK) par[v] = (int32_t)v;
-    if (t == 0) s_unions = 0;
-    __syncthreads();
-    for (int64_t e0 = 0; e0 < K && s_unions < n - 1; e0 += PF_BLOCK) {
-        const int64_t e = e0 + t;
-        bool c = false;
-        int32_t ea = 0, eb = 0;
-        if (e < K) {
-            ea = ij[2 * e];
-            eb = ij[2 * e + 1];
-            if (ea >= 0 && eb >= 0 && ea < n && eb < n) {  // always for a library result
-                int32_t a = ea, b = eb;
-                while (par[a] != a) a = par[a];
-                while (par[b] != b) b = par[b];
-                c = a != b;
-            }
-        }
-        const unsigned long long m = __ballot(c);
-        if (lane == 0) wc[wv] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t before = 0, tot = 0;
-        for (int w = 0; w < PF_BLOCK / 64; w++) {
-            if (w < wv) before += wc[w];
-            tot += wc[w];
-        }
-        if (c) {
-            const uint32_t at = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            cand[at] = (int32_t)(e - e0);
-            ca[at] = ea;
-            cb[at] = eb;
-        }
-        __syncthreads();
-        if (t == 0) {
-            int32_t u = s_unions;
-            for (uint32_t i = 0; i < tot; i++) {
-                const int64_t f = e0 + cand[i];
-                int32_t a = ca[i], b = cb[i];
-                while (par[a] != a) {
-                    par[a] = par[par[a]];
-                    a = par[a];
-                }
-                while (par[b] != b) {
-                    par[b] = par[par[b]];
-                    b = par[b];
-                }
-                if (a != b) {
-                    const int32_t lo = min(a, b), hi = max(a, b);
-                    par[hi] = lo;
-                    e_low[f] = hi;
-                    death[hi] = (int32_t)f;
-                    u++;
-                }
-            }
-            s_unions = u;
-        }
-        __syncthreads();
+// The ends of edge e; false when they are no vertices (never for a library result).
+static __device__ __forceinline__ bool pf_ends(const PfBufs &P, int64_t e, int32_t &a, int32_t &b) {
+    a = P.ij[2 * e];
+    b = P.ij[2 * e + 1];
+    return a >= 0 && b >= 0 && a < P.n && b < P.n;
+}
+
+// mark: the edges of [e0, e1) whose ends lie in different components.
+__global__ void __launch_bounds__(PD_BLOCK) k_pf_filter(PfBufs P, int64_t e0, int64_t e1) {
+    if (*P.joined >= P.n - 1) return;  // k_pf_join then reads no mark
+    const int64_t len = (e1 - e0 + 63) & ~(int64_t)63;
+    for (int64_t x = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; x < len; x += (int64_t)gridDim.x * PD_BLOCK) {
+        int32_t a, b;
+        const bool on = e0 + x < e1 && pf_ends(P, e0 + x, a, b) && P.root[a] != P.root[b];
+        const unsigned long long m = __ballot(on);
+        if ((threadIdx.x & 63) == 0) P.mark[x >> 6] = m;
     }
 }
+
+// The marked edges of [e0, e1) (all of them when mark is null).
+__global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int64_t e1, const unsigned long long *mark) {
+    __shared__ uint16_t par[VR_MAX_POINTS];
+    __shared__ uint32_t touch[VR_MAX_POINTS];  // the first edge of the batch at each root
+    __shared__ uint32_t cand[PF_BATCH];        // the batch: edges - e0
+    __shared__ uint32_t wc[PF_BLOCK / 64];
+    __shared__ uint32_t s_n, s_next, s_left, s_joined;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const uint32_t joined0 = (uint32_t)*P.joined;
+    if (joined0 >= (uint32_t)(P.n - 1)) return;
+    for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)P.root[v];
+    if (t == 0) s_joined = joined0;
+    const uint32_t words = (uint32_t)((e1 - e0 + 63) / 64);
+    // roots, shortening the paths (an entry only ever moves up its own path)
+    auto find = [&](uint32_t v) {
+        for (uint32_t p = par[v]; p != v; p = par[v]) {
+            const uint32_t g = par[p];
+            if (g != p) par[v] = (uint16_t)g;
+            v = g;
+        }
+        return v;
+    };
+    auto join = [&](uint32_t a, uint32_t b, int64_t f) {
+        const uint32_t lo = min(a, b), hi = max(a, b);
+        par[hi] = (uint16_t)lo;
+        P.e_low[f] = (int32_t)hi;
+        P.death[hi] = (int32_t)f;
+    };
+    uint32_t w0 = 0;  // the next word of marks
+    __syncthreads();
+    while (w0 < words && s_joined < (uint32_t)(P.n - 1)) {
+        // the next words whose marks fit the batch, their edges in order
+        const uint32_t w = w0 + (uint32_t)t;
+        unsigned long long m = 0;
+        if (w < words) {
+            if (mark) m = mark[w];
+            else m = e1 - e0 - 64 * (int64_t)w >= 64 ? ~0ull : (1ull << (e1 - e0 - 64 * (int64_t)w)) - 1;
+        }
+        const uint32_t c = (uint32_t)__popcll(m);
+        uint32_t inc = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) wc[wv] = inc;
+        __syncthreads();
+        for (int x = 0; x < wv; x++) inc += wc[x];
+        if (t == 0) {
+            s_n = 0;
+            s_next = w0;
+        }
+        __syncthreads();
+        const bool fits = inc <= PF_BATCH;
+        // the last thread whose words fit ends the batch (a word holds 64 marks at most)
+        const unsigned long long fm = __ballot(fits);
+        if (lane == 0 && fm) atomicMax(&s_next, w0 + (uint32_t)(64 * wv + 64 - __clzll((long long)fm)));
+        if (fits) {
+            if (c) atomicMax(&s_n, inc);
+            uint32_t at = inc - c;
+            for (; m; m &= m - 1) cand[at++] = 64 * w + (uint32_t)__builtin_ctzll(m);
+        }
+        __syncthreads();
+        const uint32_t nc = s_n;
+        w0 = s_next;
+        // the thread's edges of the batch: t and PF_BLOCK + t
+        uint32_t A[2], Bv[2];
+        bool live[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const uint32_t i = (uint32_t)(u * PF_BLOCK + t);
+            int32_t a = 0, b = 0;
+            live[u] = i < nc && pf_ends(P, e0 + cand[i], a, b);
+            A[u] = (uint32_t)a;
+            Bv[u] = (uint32_t)b;
+        }
+        for (int round = 0;; round++) {
+            if (t == 0) s_left = 0;
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+                if (live[u]) {
+                    A[u] = find(A[u]);
+                    Bv[u] = find(Bv[u]);
+                    live[u] = A[u] != Bv[u];
+                    touch[A[u]] = touch[Bv[u]] = ~0u;
+                }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+                if (live[u]) {
+                    const uint32_t i = (uint32_t)(u * PF_BLOCK + t);
+                    atomicMin(&touch[A[u]], i);
+                    atomicMin(&touch[Bv[u]], i);
+                }
+            __syncthreads();
+            uint32_t won = 0, left = 0;
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+                if (live[u]) {
+                    const uint32_t i = (uint32_t)(u * PF_BLOCK + t);
+                    if (touch[max(A[u], Bv[u])] == i) {
+                        join(A[u], Bv[u], e0 + cand[i]);
+                        live[u] = false;
+                        won++;
+                    } else {
+                        left++;
+                    }
+                }
+            if (won) atomicAdd(&s_joined, won);
+            if (left) atomicAdd(&s_left, left);
+            __syncthreads();
+            const uint32_t rest = s_left;
+            __syncthreads();  // s_left is cleared by the next round
+            if (rest == 0) break;
+            if (round + 1 < PF_ROUNDS) continue;
+            // what is left, in order: marked in touch, by one thread
+#pragma unroll
+            for (int u = 0; u < 2; u++) touch[u * PF_BLOCK + t] = live[u] ? 1u : 0u;
+            __syncthreads();
+            if (t == 0) {
+                uint32_t k = 0;
+                for (uint32_t i = 0; i < nc; i++) {
+                    if (!touch[i]) continue;
+                    const int64_t f = e0 + cand[i];
+                    int32_t ea, eb;
+                    (void)pf_ends(P, f, ea, eb);
+                    uint32_t a = (uint32_t)ea, b = (uint32_t)eb;
+                    while (par[a] != a) a = par[a] = par[par[a]];
+                    while (par[b] != b) b = par[b] = par[par[b]];
+                    if (a != b) {
+                        join(a, b, f);
+                        k++;
+                    }
+                }
+                s_joined += k;
+            }
+            break;
+        }
+        __syncthreads();
+        // shorter paths for the next batch (a root stays a root)
+        for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)find((uint32_t)v);
+        __syncthreads();
+    }
+    for (int64_t v = t; v < P.n; v += PF_BLOCK) P.root[v] = (int32_t)find((uint32_t)v);
+    if (t == 0) *P.joined = (int32_t)s_joined;
+}
+static_assert(PF_BATCH <= VR_MAX_POINTS, "touch marks what is left of a batch");
 
 // Dimension 1, apparent pairs.  Triangles of value r are the cofacets of
 // edge r whose other two edges are older, and the writer emits them
@@ -293,39 +285,25 @@ extern "C" VR_API int vr_pairs_dim0(const vr_result *res, int32_t *e_low, int32_
     if ((K > 0 && (!e_low || !res->edge_ij)) || (n > 0 && !death)) return VR_EINVAL;
     if (n == 0) return VR_OK;
     const hipStream_t s = (hipStream_t)stream;
-    if (n > PD_CLOSURE_MAX) {
-        // the spanning forest: K finds and at most n - 1 serial unions
-        hipLaunchKernelGGL(k_pd_clear, dim3(grid_for(n)), dim3(PD_BLOCK), 0, s, death, n);
-        if (K > 0) {
-            hipLaunchKernelGGL(k_pd_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, e_low, K);
-            hipLaunchKernelGGL(k_pd_forest, dim3(1), dim3(PF_BLOCK), 0, s, (const int32_t *)res->edge_ij, K, n, e_low,
-                               death);
-        }
-        return hipGetLastError() == hipSuccess ? VR_OK : VR_EHIP;
-    }
-    const int64_t nb = (n + PD_T - 1) / PD_T, ld = nb * PD_T;
-    int32_t *D = (int32_t *)cache_get((size_t)ld * (size_t)ld * 4, s);
-    if (!D) return VR_ENOMEM;
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(ld * ld)), dim3(PD_BLOCK), 0, s, D, ld);
-    if (K > 0)
-        hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, ld,
-                           (const int32_t *)res->edge_ij, K, n);
-    if (K > 0)
-        for (int64_t kb = 0; kb < nb; kb++) {
-            hipLaunchKernelGGL(k_pd_diag, dim3(1), dim3(PD_DIAG_BLOCK), 0, s, D, ld, kb);
-            if (nb > 1) {
-                hipLaunchKernelGGL(k_pd_cross, dim3((unsigned)(2 * nb)), dim3(PD_BLOCK), 0, s, D, ld, kb, nb);
-                hipLaunchKernelGGL(k_pd_rest, dim3((unsigned)nb, (unsigned)nb), dim3(PD_BLOCK), 0, s, D, ld, kb, nb);
-            }
-        }
-    hipLaunchKernelGGL(k_pd_death, dim3((unsigned)((n + PD_BLOCK / 64 - 1) / (PD_BLOCK / 64))), dim3(PD_BLOCK), 0, s,
-                       (const int32_t *)D, ld, n, death);
-    if (K > 0) {
-        hipLaunchKernelGGL(k_pd_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, e_low, K);
-        hipLaunchKernelGGL(k_pd_emit, dim3(grid_for(n)), dim3(PD_BLOCK), 0, s, (const int32_t *)death, n, e_low, K);
+    PfBufs P{(const int32_t *)res->edge_ij, K, n, nullptr, nullptr, nullptr, e_low, death};
+    // stretches: [0, 2n), then as many edges as came before; marks of the longest
+    const size_t up_n = (4 * (size_t)n + 255) & ~(size_t)255;
+    char *ws = (char *)cache_get(up_n + 256 + 8 * (size_t)(K / 64 + 1), s);
+    if (!ws) return VR_ENOMEM;
+    P.root = (int32_t *)ws;
+    P.joined = (int32_t *)(ws + up_n);
+    P.mark = (unsigned long long *)(ws + up_n + 256);
+    hipLaunchKernelGGL(k_pf_init, dim3(grid_for(n > K ? n : K)), dim3(PD_BLOCK), 0, s, P);
+    for (int64_t e0 = 0; e0 < K;) {
+        const int64_t e1 = e0 ? (2 * e0 < K ? 2 * e0 : K) : (2 * n < K ? 2 * n : K);
+        if (e0)
+            hipLaunchKernelGGL(k_pf_filter, dim3(grid_for(e1 - e0)), dim3(PD_BLOCK), 0, s, P, e0, e1);
+        hipLaunchKernelGGL(k_pf_join, dim3(1), dim3(PF_BLOCK), 0, s, P, e0, e1,
+                           e0 ? (const unsigned long long *)P.mark : (const unsigned long long *)nullptr);
+        e0 = e1;
     }
     const hipError_t e = hipGetLastError();
-    cache_put(D, s);
+    cache_put(ws, s);
     return e == hipSuccess ? VR_OK : VR_EHIP;
 }
 
