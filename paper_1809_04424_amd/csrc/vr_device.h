@@ -18,7 +18,7 @@
 #define VR_NOT_KEPT 0xFFFFFFFFu
 // Prefix lists of the triangle writer: each star in neighbour order, whole
 // and cut at every (1 / VR_PLISTS)-th of its rank order; VR_PLIST_PER n +
-// 65 VR_PLISTS entries per vertex hold them with their sentinels.
+// 65 VR_PLISTS entries per vertex hold them, each from a 128-byte line on.
 #define VR_PLISTS 4
 #define VR_PLIST_PER ((VR_PLISTS + 2) / 2)
 
@@ -446,9 +446,8 @@ struct VrDev {
                             // then each row's star in rank order (local rank, tag 0)
     uint16_t *star_nbr;     // sum n^2: the other endpoint (local), rank order
     uint32_t *star_k;       // VR_PLIST_PER sum n^2 + 65 VR_PLISTS V: per vertex, its prefix lists (the
-                            // star in neighbour order, entries neighbour | rank-order position << 16,
-                            // whole and cut at each 1/VR_PLISTS of the rank order), each followed by
-                            // 64 sentinels
+                            // star in neighbour order, entries neighbour | (0xFFFF - rank-order
+                            // position) << 16, whole and cut at each 1/VR_PLISTS of the rank order)
     uint32_t *deg;          // V: star sizes
     uint16_t *epos;         // 2 Kmax: entry 2r + s = position of kept edge r in the rank-ordered star of its
                             // lower (s = 0) or upper (s = 1) endpoint
