@@ -615,20 +615,32 @@ __global__ __launch_bounds__(EB) void k_tri_count(VrDev D, int parts) {
 
 // Work-groups per vertex, the default when no tuned value is known: enough
 // groups to spread heavy vertices over many compute units when the cloud is
-// small.
-int enum_parts(long long V) {
-    long long p = 4096 / (V > 0 ? V : 1);
-    return p < 1 ? 1 : (p > 8 ? 8 : (int)p);
+// small, each with work enough for its setup.  Write, four and five a vertex:
+// 39 and 35 us (1000-point circle), 510 and 491 (1088 points, all edges), 42
+// and 41 (777 points); eight split by partner: 30 us against 21 with five on
+// 300 points; 2000 points: 79 with three, 84 with one of 512 threads.  Count: 21 us with four or five, 25 with eight on the circle.
+// Up to 128 points seven or eight are the same (7 and 8 us).
+static int enum_parts(long long V, long long groups, long long most) {
+    const long long p = groups / (V > 0 ? V : 1);
+    if (V <= 128) most = 7;
+    return p < 1 ? 1 : (int)(p > most ? most : p);
 }
+int enum_parts_count(long long V) { return enum_parts(V, 4096, 4); }
+int enum_parts_write(long long V, long long C) { return enum_parts(V, enum_block(V, C) == 256 ? 6144 : 3072, 5); }
 
 // Work-group size, the default: 256 threads for small clouds (more
-// work-groups in flight), 512 for large ones (fewer chunk barriers).
-int enum_block(long long V) { return V <= 2048 ? 256 : 512; }
+// work-groups in flight), 512 for large ones (fewer chunk barriers).  What
+// counts is the size of one cloud: 32 clouds of 50 to 2000 points took 138
+// (count) and 281 us (write) with 512 threads, 95 and 202 with 256; one
+// cloud of 8192 points 145 and 283 with 512, 160 and 295 with 256.
+int enum_block(long long V, long long C) { return V <= 2048 * C ? 256 : 512; }
 
-// Pieces loaded at a time, the defaults: 4 for the count (its candidates are
-// rank prefixes, often short), 8 for the write (whole stars).
-int enum_pieces_count(long long) { return 4; }
-int enum_pieces_write(long long) { return 8; }
+// Pieces loaded at a time, the defaults.  Count: its candidates are rank
+// prefixes, often short: 4, or 8 where K edges are known to give 768
+// neighbours a vertex (1088 points, all edges: 149 us with 8, 166 with 4;
+// 4000 points, 400 neighbours: 109 and 100).  Write (prefix lists): 8.
+int enum_pieces_count(long long V, long long K) { return K >= 384 * V ? 8 : 4; }
+int enum_pieces_write() { return 8; }
 
 template <int EB, int NP>
 static void count_at(const VrDev &D, dim3 grid, hipStream_t s) {

@@ -211,7 +211,7 @@ int bits_of(unsigned long long m);
 // Enumeration schedule picked by vr_autotune, per size class (bits of the
 // vertex count, bits of the mean degree): work-group size, work-groups per
 // vertex and candidate pieces loaded at a time, for the count and for the
-// write.  Builds of a class never tuned use enum_block, enum_parts and
+// write.  Builds of a class never tuned use enum_block, enum_parts_* and
 // enum_pieces_*.
 struct Sched {
     int eb_count, parts_count, pieces_count, eb_write, parts_write, pieces_write;
@@ -595,7 +595,8 @@ int build_impl(const vr_request *reqs, long long count, hipStream_t s, Owner &ow
         }
     }
     const Plan P = plan_of(S);
-    Sched sch{enum_block(V), enum_parts(V), enum_pieces_count(V), enum_block(V), enum_parts(V), enum_pieces_write(V)};
+    Sched sch{enum_block(V, C), enum_parts_count(V), enum_pieces_count(V, Khost),
+              enum_block(V, C), enum_parts_write(V, C), enum_pieces_write()};
     {
         Tuning &tu = tuning();
         std::lock_guard<std::mutex> g(tu.mu);

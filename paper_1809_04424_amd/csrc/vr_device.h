@@ -508,10 +508,11 @@ void launch_sort_pass(const SortJob &J, long long max_tiles, int pass, hipStream
 void launch_hist_fold(uint32_t *h0, int stride, int bins, hipStream_t s);
 void launch_edges(const VrDev &D, hipStream_t s);
 void launch_rows(const VrDev &D, hipStream_t s);
-int enum_parts(long long V);
-int enum_block(long long V);
-int enum_pieces_count(long long V);
-int enum_pieces_write(long long V);
+int enum_parts_count(long long V);
+int enum_parts_write(long long V, long long C);
+int enum_block(long long V, long long C);
+int enum_pieces_count(long long V, long long K);
+int enum_pieces_write();
 void launch_tri_count(const VrDev &D, hipStream_t s);
 void launch_scan(const VrDev &D, long long Kmax, hipStream_t s);
 void launch_tri_write(const VrDev &D, unsigned long long *tri_out, long long cap_k, unsigned long long cap_t,
