@@ -159,52 +159,78 @@ __global__ __launch_bounds__(VR_BLOCK) void k_rows(VrDev D) {
     uint32_t rr[S];
 #pragma unroll
     for (int s = 0; s < S; s++) rr[s] = row[min((w * per + s) * VR_WAVE + lane, n - 1)];
-    // keep an entry when it names a kept edge {v, k} of this cloud; rr = rank within the cloud
-    unsigned long long mk[S];  // kept entries of each step (wave-uniform)
-    uint32_t cw = 0;
+    // candidates: entries with the tag and a kept rank; rr = rank within the cloud
+    unsigned long long mk[S];  // entries taken in each step (wave-uniform)
 #pragma unroll
     for (int s = 0; s < S; s++) {
         const int k = (w * per + s) * VR_WAVE + lane;
         const uint32_t lr = rr[s] & 0xFFFFFFu;
-        const bool in = s < per && k < n && k != v && (rr[s] >> 24) == D.tag && (long long)lr < Kc;
-        const uint32_t ij = D.se_ij[kb + (in ? lr : 0u)];  // kept base itself when not in (se_ij has room)
-        const uint32_t want = (k < v) ? (((uint32_t)k << 16) | (uint32_t)v) : (((uint32_t)v << 16) | (uint32_t)k);
-        const bool kept = in && ij == want;
+        mk[s] = __builtin_amdgcn_ballot_w64(s < per && k < n && k != v && (rr[s] >> 24) == D.tag && (long long)lr < Kc);
         rr[s] = lr;
-        mk[s] = __builtin_amdgcn_ballot_w64(kept);
-        cw += (uint32_t)__popcll(mk[s]);
     }
-    if (lane == 0) sh_w[w] = cw;
-    __syncthreads();
-    uint32_t run = 0, deg = 0;
+    // sort keys: local ranks in neighbour order (entry x = x-th neighbour
+    // taken), padded, and the neighbours
+    uint32_t run, deg, P;
+    uint16_t *pk;
+    auto compact = [&]() {
+        uint32_t cw = 0;
 #pragma unroll
-    for (int i = 0; i < VR_WAVES; i++) {
-        const uint32_t t = sh_w[i];
-        if (i < w) run += t;
-        deg += t;
-    }
-    // sort keys: local ranks in neighbour order (entry x = x-th kept
-    // neighbour), padded; small stars are ranked by counting, larger ones
-    // sorted (bitonic)
-    uint32_t P = VR_WAVE;
-    while (P < deg) P <<= 1;
-    const bool by_count = deg <= VR_ROWS_COUNT_MAX;
-    // counting: the neighbour of entry x; bitonic: the position of neighbour k
-    uint16_t *pk = (uint16_t *)(lds + P);
-    for (uint32_t y = deg + threadIdx.x; y < P; y += VR_BLOCK) lds[y] = 0xFFFFFFFFu;
-    {
+        for (int s = 0; s < S; s++) cw += (uint32_t)__popcll(mk[s]);
+        if (lane == 0) sh_w[w] = cw;
+        __syncthreads();
+        run = deg = 0;
+#pragma unroll
+        for (int i = 0; i < VR_WAVES; i++) {
+            const uint32_t t = sh_w[i];
+            if (i < w) run += t;
+            deg += t;
+        }
+        P = VR_WAVE;
+        while (P < deg) P <<= 1;
+        pk = (uint16_t *)(lds + P);
+        for (uint32_t y = deg + threadIdx.x; y < P; y += VR_BLOCK) lds[y] = 0xFFFFFFFFu;
         uint32_t x = run;
 #pragma unroll
         for (int s = 0; s < S; s++) {
             const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk[s] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk[s], x));
             if ((mk[s] >> lane) & 1ull) {
                 lds[at] = rr[s];
-                if (by_count) pk[at] = (uint16_t)((w * per + s) * VR_WAVE + lane);
+                pk[at] = (uint16_t)((w * per + s) * VR_WAVE + lane);
             }
             x += (uint32_t)__popcll(mk[s]);
         }
+        __syncthreads();
+    };
+    auto endpoints = [&](uint32_t k) {
+        return (k < (uint32_t)v) ? ((k << 16) | (uint32_t)v) : (((uint32_t)v << 16) | k);
+    };
+    auto look_up = [&]() {
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            const bool in = (mk[s] >> lane) & 1ull;
+            const uint32_t ij = D.se_ij[kb + (in ? rr[s] : 0u)];  // kept base itself when not in (se_ij has room)
+            mk[s] = __builtin_amdgcn_ballot_w64(in && ij == endpoints((uint32_t)((w * per + s) * VR_WAVE + lane)));
+        }
+    };
+    // Beyond 2048 points the candidates are looked up in the sorted edge list
+    // after compaction, and nearly always all of them are edges; else each
+    // entry of the row is looked up by itself, as the steps are read.  The
+    // latter took 133 of 213 us on 8192 points with 270 neighbours each (160
+    // us now) and 19 of 85 on 4000 with 400 (84), but on 1088 points with all
+    // edges, few entries a lane and each one taken, it is faster (59, 61).
+    if constexpr (S <= 8) look_up();
+    compact();
+    if constexpr (S > 8) {
+        bool bad = false;
+        for (uint32_t x = threadIdx.x; x < deg; x += VR_BLOCK) bad |= D.se_ij[kb + lds[x]] != endpoints(pk[x]);
+        if (__syncthreads_or(bad)) {
+            look_up();
+            compact();
+        }
     }
-    __syncthreads();
+    // small stars are ranked by counting, larger ones sorted (bitonic, where
+    // pk becomes the position of neighbour k)
+    const bool by_count = deg <= VR_ROWS_COUNT_MAX;
     uint32_t *lb = D.star_k + plist_region((uint32_t)D.cl[c].mbase, (uint32_t)D.cl[c].vbase, n, v);
     uint32_t *sk = lb + plist_off(VR_PLISTS, deg);  // the last list: the whole star
     if (by_count) {

@@ -49,3 +49,29 @@ def test_lists(orc, shape, n):
                "edge_q": r.edge_q().cpu().numpy(), "tri": r.tri_key().cpu().numpy()}
         r.free()
         assert_matches_oracle(out, want)
+
+
+@pytest.mark.parametrize("n,K", [(90, 900), (640, 180000), (2100, 30000), (2100, 700000)])
+def test_entries_left_from_a_build_of_the_same_tag(n, K):
+    """Row entries that an earlier build left and that carry the same tag (one
+    build in 255) are candidates for a star and fail the look-up."""
+    import torch
+
+    import paper_1809_04424_amd as vr
+
+    g = np.random.default_rng(n)
+    a, b, small = (torch.from_numpy(g.integers(-90, 91, (m, 3)).astype(np.int8)).to("cuda:0") for m in (n, n, 9))
+
+    def out(p):
+        r = vr.build(p, ("count", K, 1))
+        o = [x.cpu().numpy() for x in (r.edge_ij(), r.edge_q(), r.tri_key())]
+        r.free()
+        return o
+
+    want = out(b)
+    for between in (253, 254, 255):
+        print(f"[gpu] same tag n={n} after {between}", flush=True)
+        out(a)
+        for _ in range(between):
+            vr.build(small).free()
+        assert all(np.array_equal(x, y) for x, y in zip(out(b), want))
