@@ -7,8 +7,9 @@
 // meets the window.
 //   k_co_first  per column: the windows whose first entry lies in it.
 //   k_co_local  per window: each entry's rank inside its segment (counting
-//               against the segment in LDS when every segment is short, an
-//               LDS bitonic sort otherwise), plus the column's first slot;
+//               against the segment in LDS when every segment is short,
+//               otherwise buckets of values, or an LDS bitonic sort where
+//               the values crowd), plus the column's first slot;
 //               the sorted values of segments whose column leaves the window
 //               are kept for the next kernel.
 //   k_co_merge  per window, only for the (at most two) columns that leave
@@ -19,6 +20,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "vr.h"
 #include "vr_cache.h"
@@ -28,6 +30,8 @@
 #define CO_PER (CO_WIN / CO_BLOCK)
 #define CO_COUNT_MAX 256  // longest segment ranked by counting
 #define CO_WAVE 64
+#define CO_SEGS 128  // segments of a window that is sorted into buckets
+#define CO_CROWD 24  // longest bucket
 
 static __device__ __forceinline__ int64_t clampi(int64_t x, int64_t lo, int64_t hi) {
     return x < lo ? lo : (x > hi ? hi : x);
@@ -74,16 +78,15 @@ static __device__ __forceinline__ int co_pos(int t, int g) {
     return LAY == 0 ? CO_PER * t + g : (LAY == 1 ? 256 * (t >> 4) + 16 * g + (t & 15) : 256 * g + t);
 }
 
-template <int LAY>
-static __device__ __forceinline__ void co_put(const unsigned long long (&r)[CO_PER], int t, unsigned long long *keys) {
+template <int LAY, typename KEY>
+static __device__ __forceinline__ void co_put(const KEY (&r)[CO_PER], int t, KEY *keys) {
 #pragma unroll
     for (int g = 0; g < CO_PER; g++) keys[co_phys(co_pos<LAY>(t, g))] = r[g];
 }
 
 // move the keys from layout cur to layout TO through LDS
-template <int TO>
-static __device__ __forceinline__ void co_to(unsigned long long (&r)[CO_PER], int &cur, int t,
-                                             unsigned long long *keys) {
+template <int TO, typename KEY>
+static __device__ __forceinline__ void co_to(KEY (&r)[CO_PER], int &cur, int t, KEY *keys) {
     if (cur == TO) return;  // uniform over the work-group
     __syncthreads();        // earlier reads of the buffer are done
     if (cur == 0) co_put<0>(r, t, keys);
@@ -97,8 +100,8 @@ static __device__ __forceinline__ void co_to(unsigned long long (&r)[CO_PER], in
 
 // the stages of one merge width kk on the position bits that layout LAY
 // holds in registers (bits 4*LAY .. 4*LAY+3, at most bhi), highest first
-template <int LAY>
-static __device__ __forceinline__ void co_stages(unsigned long long (&r)[CO_PER], int t, int kk, int bhi) {
+template <int LAY, typename KEY>
+static __device__ __forceinline__ void co_stages(KEY (&r)[CO_PER], int t, int kk, int bhi) {
 #pragma unroll
     for (int gb = 3; gb >= 0; gb--) {
         if (4 * LAY + gb > bhi) continue;
@@ -108,11 +111,41 @@ static __device__ __forceinline__ void co_stages(unsigned long long (&r)[CO_PER]
             if (g & j) continue;
             const int h = g | j;
             const bool up = (co_pos<LAY>(t, g) & kk) == 0;
-            const unsigned long long k0 = r[g], k1 = r[h];
-            const bool sw = (k0 > k1) == up;
-            r[g] = sw ? k1 : k0;
-            r[h] = sw ? k0 : k1;
+            const KEY k0 = r[g], k1 = r[h];
+            if constexpr (sizeof(KEY) == 4) {
+                const KEY lo = min(k0, k1), hi = max(k0, k1);
+                r[g] = up ? lo : hi;
+                r[h] = up ? hi : lo;
+            } else {
+                const bool sw = (k0 > k1) == up;
+                r[g] = sw ? k1 : k0;
+                r[h] = sw ? k0 : k1;
+            }
         }
+    }
+}
+
+// Bitonic sort of CO_WIN keys, a thread's 16 in layout L at first and in
+// layout C at the end.  Every compare-exchange happens in registers: a
+// thread holds 16 keys in one of three layouts, each owning four bits of the
+// position (C: bits 0-3, position 16t + g; S: bits 4-7, 256(t/16) + 16g +
+// t%16; L: bits 8-11, 256g + t), and the keys move between layouts through
+// LDS.
+template <typename KEY>
+static __device__ __forceinline__ void co_bitonic(KEY (&r)[CO_PER], int t, KEY *keys) {
+    int cur = 2;
+    for (int lk = 1; lk <= 12; lk++) {  // merge width 2^lk: stages on bits lk-1 .. 0
+        const int kk = 1 << lk;
+        if (lk - 1 >= 8) {
+            co_to<2>(r, cur, t, keys);
+            co_stages<2>(r, t, kk, lk - 1);
+        }
+        if (lk - 1 >= 4) {
+            co_to<1>(r, cur, t, keys);
+            co_stages<1>(r, t, kk, lk - 1);
+        }
+        co_to<0>(r, cur, t, keys);
+        co_stages<0>(r, t, kk, lk - 1);
     }
 }
 
@@ -123,10 +156,12 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
     // order); sorting path, the keys between layouts, then the slots
     __shared__ unsigned long long keys[CO_WIN + CO_WIN / 16];
     uint32_t *kv = (uint32_t *)keys;
-    __shared__ uint16_t segid[CO_WIN];  // first the segment-start flags
+    __shared__ __align__(16) uint16_t segid[CO_WIN];  // first the segment-start flags; at last the buckets' starts
     __shared__ uint16_t segstart[CO_WIN + 2];
     __shared__ uint32_t wsum[CO_BLOCK / CO_WAVE];
-    __shared__ uint32_t maxlen;
+    __shared__ uint32_t maxlen, few, longest, vbits;
+    __shared__ uint32_t smin[CO_SEGS], smax[CO_SEGS];
+    __shared__ uint4 seg[CO_SEGS];  // least value, buckets per value (float), first bucket, last bucket's index
 
     const int t = threadIdx.x, lane = t % CO_WAVE, wv = t / CO_WAVE;
     const CoWindow W = co_window(colptr, ncols, nnz, first, nwin, blockIdx.x);
@@ -142,7 +177,11 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         kv[t + m * CO_BLOCK] = (uint32_t)x[m] ^ 0x80000000u;
         segid[t + m * CO_BLOCK] = 0;
     }
-    if (t == 0) maxlen = 0;
+    if (t == 0) maxlen = few = longest = vbits = 0;
+    if (t < CO_SEGS) {
+        smin[t] = ~0u;
+        smax[t] = 0;
+    }
     __syncthreads();
     // segment starts: every column that begins strictly inside the window
     const int64_t cend = W.cl >= 0 ? W.cl : ncols - 1;
@@ -153,12 +192,16 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
     __syncthreads();
     // segment of every position: inclusive count of the starts up to it
     // (thread t scans positions CO_PER*t .. CO_PER*t + CO_PER-1)
-    uint32_t f[CO_PER], own = 0;
-#pragma unroll
-    for (int m = 0; m < CO_PER; m++) {
-        f[m] = segid[CO_PER * t + m];
-        own += f[m];
+    // wide LDS accesses: 2-byte ones 32 bytes apart would meet in one bank in eight
+    uint4 *f4 = (uint4 *)segid + 2 * t;
+    uint32_t f[CO_PER / 2], own = 0;
+    {
+        const uint4 f0 = f4[0], f1 = f4[1];
+        f[0] = f0.x, f[1] = f0.y, f[2] = f0.z, f[3] = f0.w, f[4] = f1.x, f[5] = f1.y, f[6] = f1.z, f[7] = f1.w;
     }
+#pragma unroll
+    for (int m = 0; m < CO_PER / 2; m++) own += f[m];
+    own = (own & 0xFFFFu) + (own >> 16);
     uint32_t incl = own;
 #pragma unroll
     for (int d = 1; d < CO_WAVE; d <<= 1) {
@@ -174,12 +217,15 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         total += wsum[i];
     }
 #pragma unroll
-    for (int m = 0; m < CO_PER; m++) {
-        const int p = CO_PER * t + m;
-        run += f[m];
-        segid[p] = (uint16_t)run;
-        if (f[m]) segstart[run] = (uint16_t)p;
+    for (int m = 0; m < CO_PER / 2; m++) {
+        const uint32_t r0 = run + (f[m] & 1u), r1 = r0 + (f[m] >> 16);
+        if (f[m] & 1u) segstart[r0] = (uint16_t)(CO_PER * t + 2 * m);
+        if (f[m] >> 16) segstart[r1] = (uint16_t)(CO_PER * t + 2 * m + 1);
+        f[m] = r0 | (r1 << 16);
+        run = r1;
     }
+    f4[0] = make_uint4(f[0], f[1], f[2], f[3]);
+    f4[1] = make_uint4(f[4], f[5], f[6], f[7]);
     const int nseg = (int)total + 1;
     if (t == 0) {
         segstart[0] = 0;
@@ -218,12 +264,213 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         return;
     }
 
+    // z of the thread's keys (segment << 44 | value << 12 | position), key g
+    // in sorted position CO_PER * t + g + mv[g]
+    auto finish = [&](const unsigned long long (&r)[CO_PER], const int (&mv)[CO_PER]) {
+        __syncthreads();  // every thread's last read of the keys is done
+#pragma unroll
+        for (int g = 0; g < CO_PER; g++) {
+            if (CO_PER * t + g < cnt) {
+                const int y = CO_PER * t + g + mv[g], sg = (int)(r[g] >> 44), idx = (int)(r[g] & 0xFFFu);
+                keys[co_phys(idx)] = (unsigned long long)(base_of(sg) + (y - segstart[sg]));
+                if (spans(sg)) vs[a + y] = (uint32_t)(r[g] >> 12);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < CO_PER; m++) {
+            const int p = t + m * CO_BLOCK;
+            if (p < cnt) z[a + p] = (int64_t)keys[co_phys(p)];
+        }
+    };
+
+    // Buckets: a segment of len entries takes len buckets, its values spread
+    // over them in order (float products, which round monotonically), so an
+    // entry shares its bucket with few others and its place is the bucket's
+    // start plus the smaller (value, position) there.  A bitonic sort of 4096
+    // 64-bit keys is bound by its 78 stages of compares (69 us for 2000
+    // columns of 1999 entries); the buckets take 41, with 2900 instructions a
+    // wave and half the time in waits for LDS: two work-groups fit a compute
+    // unit.  Capping the registers to fit three or four took 63 and 42 us.
+    // Where values crowd (24 or more in a bucket) the window is sorted after
+    // all, by 32-bit keys if they hold segment, value and position: 2000
+    // columns of 1000 entries and 10 values 61 -> 56 us; values so clustered
+    // that the buckets are tried in vain and the keys stay wide (twelfth
+    // powers of uniform numbers) 69 -> 80.
+    if (nseg <= CO_SEGS) {
+        uint32_t *cw = (uint32_t *)segid;
+        uint32_t sgw[CO_PER / 4];  // the entries' segments, four in a word
+        auto sg = [&](int m) { return (sgw[m / 4] >> (8 * (m % 4))) & 0xFFu; };
+        // Whole windows (all but the last) run without bounds tests, so that
+        // each step's LDS accesses are in flight together.
+        auto buckets = [&](auto whole) -> bool {
+            constexpr bool ALL = decltype(whole)::value;
+            auto in = [&](int m) { return ALL || t + m * CO_BLOCK < cnt; };
+#pragma unroll
+            for (int m = 0; m < CO_PER; m += 4)
+                sgw[m / 4] = segid[t + m * CO_BLOCK] | (uint32_t)segid[t + (m + 1) * CO_BLOCK] << 8 |
+                             (uint32_t)segid[t + (m + 2) * CO_BLOCK] << 16 | (uint32_t)segid[t + (m + 3) * CO_BLOCK] << 24;
+            // smallest and largest value of each segment
+            {
+                uint32_t lo = ~0u, hi = 0;
+                uint32_t cs = sg(0);
+#pragma unroll
+                for (int m = 0; m < CO_PER; m++) {
+                    const uint32_t u = (uint32_t)x[m] ^ 0x80000000u;
+                    if (in(m)) {
+                        if (sg(m) != cs) {
+                            atomicMin(&smin[cs], lo);
+                            atomicMax(&smax[cs], hi);
+                            cs = sg(m);
+                            lo = ~0u;
+                            hi = 0;
+                        }
+                        lo = min(lo, u);
+                        hi = max(hi, u);
+                    }
+                }
+                if (in(0)) {
+                    atomicMin(&smin[cs], lo);
+                    atomicMax(&smax[cs], hi);
+                }
+            }
+            __syncthreads();
+            if (t < nseg) {
+                const uint32_t st = segstart[t], len = segstart[t + 1] - st, range = smax[t] - smin[t];
+                const float scale = (float)len / ((float)range + 1.0f);
+                atomicMax(&vbits, range ? 32u - (uint32_t)__builtin_clz(range) : 0u);
+                if (len > CO_CROWD && scale >= (float)(CO_CROWD / 2)) few = 1;  // few values: sort
+                seg[t] = make_uint4(smin[t], __float_as_uint(scale), st, len - 1);
+            }
+            // segid becomes the buckets' counts, two in a word
+#pragma unroll
+            for (int m = 0; m < CO_PER / 2; m++) cw[t + m * CO_BLOCK] = 0;
+            __syncthreads();
+            if (few) return false;
+            uint32_t at[CO_PER];  // bucket, and the entry's place by arrival << 16
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++) {
+                const uint4 S = seg[sg(m)];
+                const uint32_t u = (uint32_t)x[m] ^ 0x80000000u;
+                at[m] = S.z + min((uint32_t)((float)(u - S.x) * __uint_as_float(S.y)), S.w);
+            }
+            uint32_t last = 0;
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++)
+                if (in(m)) {
+                    const uint32_t sh = (at[m] & 1) * 16;
+                    const uint32_t k = (atomicAdd(&cw[at[m] >> 1], 1u << sh) >> sh) & 0xFFFFu;
+                    at[m] |= k << 16;
+                    last = max(last, k);
+                }
+            if (last > longest) atomicMax(&longest, last);
+            __syncthreads();
+            const int far = (int)longest;
+            if (far >= CO_CROWD) return false;
+            // where each bucket starts (thread t: buckets 16t .. 16t + 15)
+            uint32_t w8[CO_PER / 2], sum = 0;
+            {
+                const uint4 f0 = f4[0], f1 = f4[1];
+                w8[0] = f0.x, w8[1] = f0.y, w8[2] = f0.z, w8[3] = f0.w, w8[4] = f1.x, w8[5] = f1.y, w8[6] = f1.z,
+                w8[7] = f1.w;
+            }
+#pragma unroll
+            for (int m = 0; m < CO_PER / 2; m++) sum += w8[m];
+            sum = (sum & 0xFFFFu) + (sum >> 16);
+            uint32_t inc = sum;
+#pragma unroll
+            for (int d = 1; d < CO_WAVE; d <<= 1) {
+                const uint32_t y = __shfl_up(inc, d, CO_WAVE);
+                if (lane >= d) inc += y;
+            }
+            if (lane == CO_WAVE - 1) wsum[wv] = inc;
+            __syncthreads();
+            uint32_t o = inc - sum;
+#pragma unroll
+            for (int i = 0; i < CO_BLOCK / CO_WAVE; i++)
+                if (i < wv) o += wsum[i];
+#pragma unroll
+            for (int m = 0; m < CO_PER / 2; m++) {
+                const uint32_t o1 = o + (w8[m] & 0xFFFFu);
+                const uint32_t o2 = o1 + (w8[m] >> 16);
+                w8[m] = o | (o1 << 16);
+                o = o2;
+            }
+            f4[0] = make_uint4(w8[0], w8[1], w8[2], w8[3]);
+            f4[1] = make_uint4(w8[4], w8[5], w8[6], w8[7]);
+            __syncthreads();
+            // the entries by bucket, then each entry's place in its own: the
+            // smaller values, and the equal ones before it
+            uint32_t qe[CO_PER], y[CO_PER];  // the bucket: its start, and its end << 16; the entry's place
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++) {
+                const uint32_t bk = at[m] & 0xFFFFu;
+                const uint32_t q0 = segid[bk], q1 = bk + 1 < CO_WIN ? segid[bk + 1] : (uint32_t)cnt;
+                qe[m] = q0 | (q1 << 16);
+                y[m] = q0;
+            }
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++)
+                if (in(m))
+                    keys[y[m] + (at[m] >> 16)] =
+                        ((unsigned long long)((uint32_t)x[m] ^ 0x80000000u) << 12) | (unsigned)(t + m * CO_BLOCK);
+            __syncthreads();
+            for (uint32_t d = 0; d <= (uint32_t)far; d++) {
+#pragma unroll
+                for (int m0 = 0; m0 < CO_PER; m0 += 8) {
+#pragma unroll
+                    for (int m = m0; m < m0 + 8; m++) {
+                        const uint32_t q = (qe[m] & 0xFFFFu) + d;
+                        const unsigned long long e = keys[q];  // reads past the bucket are not used
+                        const uint32_t u = (uint32_t)x[m] ^ 0x80000000u;
+                        const unsigned long long own = ((unsigned long long)u << 12) | (unsigned)(t + m * CO_BLOCK);
+                        y[m] += (q < (qe[m] >> 16)) & (e < own) ? 1u : 0u;
+                    }
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++)
+                if (in(m)) {
+                    const int sm = (int)sg(m);
+                    z[a + t + m * CO_BLOCK] = base_of(sm) + (int64_t)(y[m] - segstart[sm]);
+                    if (spans(sm)) vs[a + y[m]] = (uint32_t)x[m] ^ 0x80000000u;
+                }
+            return true;
+        };
+        if (cnt == CO_WIN ? buckets(std::true_type()) : buckets(std::false_type())) return;
+        // the segment, the value above the segment's least and the position
+        // in 32 bits
+        const uint32_t vb = vbits;
+        if (vb + 12 + (uint32_t)(32 - __builtin_clz((uint32_t)nseg)) <= 32) {
+            uint32_t r[CO_PER];
+#pragma unroll
+            for (int m = 0; m < CO_PER; m++) {
+                const int p = t + m * CO_BLOCK;
+                const uint32_t u = (uint32_t)x[m] ^ 0x80000000u;
+                r[m] = p < cnt ? ((sg(m) << vb | (u - smin[sg(m)])) << 12) | (unsigned)p : ~0u;
+            }
+            co_bitonic(r, t, kv);
+            unsigned long long rl[CO_PER];
+            const int still[CO_PER] = {};
+#pragma unroll
+            for (int g = 0; g < CO_PER; g++) {
+                const uint32_t s = min((r[g] >> 12) >> vb, (uint32_t)nseg - 1);
+                rl[g] = ((unsigned long long)s << 44) |
+                        ((unsigned long long)(smin[s] + ((r[g] >> 12) & ((1u << vb) - 1u))) << 12) | (r[g] & 0xFFFu);
+            }
+            finish(rl, still);
+            return;
+        }
+        // the segments again, for the keys below
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < CO_PER; m++)
+            if (t + m * CO_BLOCK < cnt) segid[t + m * CO_BLOCK] = (uint16_t)sg(m);
+        __syncthreads();
+    }
+
     // Bitonic sort of the keys (segment, value, position); pads sort last.
-    // Every compare-exchange happens in registers: a thread holds 16 keys in
-    // one of three layouts, each owning four bits of the position (C: bits
-    // 0-3, position 16t + g; S: bits 4-7, 256(t/16) + 16g + t%16; L: bits
-    // 8-11, 256g + t), and the keys move between layouts through LDS.  The
-    // keys start in layout L, which is how the values were loaded.
+    // The keys start in layout L, which is how the values were loaded.
     unsigned long long r[CO_PER];
 #pragma unroll
     for (int g = 0; g < CO_PER; g++) {
@@ -231,36 +478,9 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         const unsigned long long u = (uint32_t)x[g] ^ 0x80000000u;
         r[g] = p < cnt ? ((unsigned long long)segid[p] << 44) | (u << 12) | (unsigned)p : ~0ull;
     }
-    int cur = 2;
-    for (int lk = 1; lk <= 12; lk++) {  // merge width 2^lk: stages on bits lk-1 .. 0
-        const int kk = 1 << lk;
-        if (lk - 1 >= 8) {
-            co_to<2>(r, cur, t, keys);
-            co_stages<2>(r, t, kk, lk - 1);
-        }
-        if (lk - 1 >= 4) {
-            co_to<1>(r, cur, t, keys);
-            co_stages<1>(r, t, kk, lk - 1);
-        }
-        co_to<0>(r, cur, t, keys);
-        co_stages<0>(r, t, kk, lk - 1);
-    }
-    __syncthreads();  // every thread's last layout read is done
-#pragma unroll
-    for (int g = 0; g < CO_PER; g++) {
-        const int y = CO_PER * t + g;  // sorted position
-        if (y < cnt) {
-            const int s = (int)(r[g] >> 44), idx = (int)(r[g] & 0xFFFu);
-            keys[co_phys(idx)] = (unsigned long long)(base_of(s) + (y - segstart[s]));
-            if (spans(s)) vs[a + y] = (uint32_t)(r[g] >> 12);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < CO_PER; m++) {
-        const int p = t + m * CO_BLOCK;
-        if (p < cnt) z[a + p] = (int64_t)keys[co_phys(p)];
-    }
+    co_bitonic(r, t, keys);
+    const int still[CO_PER] = {};
+    finish(r, still);
 }
 
 // Per window, for the (at most two) columns that leave it: every other
