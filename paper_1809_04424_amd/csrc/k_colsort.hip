@@ -526,13 +526,14 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_merge(const int64_t *colptr, in
             for (int i = t; i < len; i += CO_BLOCK) run[i] = vs[rs + i];
             __syncthreads();
             const bool before = u < w;
+            // steps of at most the run's length (28 -> 24 us on 2000 columns of 1999)
             // branchless search, steps outermost so that the entries' LDS
             // reads of one step are in flight together: pos = the run's
             // entries that come first (a prefix, since the run is sorted)
             int pos[CO_PER];
 #pragma unroll
             for (int m = 0; m < CO_PER; m++) pos[m] = 0;
-            for (int step = CO_WIN; step > 0; step >>= 1) {
+            for (int step = 1 << (31 - __builtin_clz((unsigned)len)); step > 0; step >>= 1) {
 #pragma unroll
                 for (int m = 0; m < CO_PER; m++) {
                     if (m >= nm) break;
