@@ -435,16 +435,19 @@ VR_API int vr_tetra_offsets(const vr_result *res, int64_t *offsets, void *stream
 VR_API int vr_tetra_write(const vr_result *res, const int64_t *offsets, int64_t total, uint64_t *keys, void *stream);
 
 /* Persistence pairs of dimension 2: triangles with tetrahedra (Section
- * 2.2.1, Alg. 1, run as in Section 2.2.2 on the anti-transpose with
- * clearing, one dimension above vr_pairs_dim1; Section 3's bettimax = 2).
- * The triangle columns go from the youngest triangle to the oldest, and a
- * column's pivot is its oldest cofacet.  Triangles paired with an edge are
- * cleared; a triangle whose oldest cofacet has it as its youngest facet
- * pairs with it at once (an apparent pair: per edge the vertices joined to
- * both ends are listed once, and one wave per triangle of that value finds
- * its oldest cofacet among them); the other columns are reduced in rounds
- * as by vr_pairs_dim1.  The pairs equal those of the column algorithm on
- * the tetrahedra's boundary block.
+ * 2.2.1, Alg. 1; Section 3's bettimax = 2).  Per edge, the vertices joined
+ * to both ends by older edges and their older edges form its link: the pairs
+ * of length zero are the link's components as its edges join them, and only
+ * a link that has cycles after filling in its triangles holds tetrahedra
+ * whose columns are then reduced, on the few triangles that no such pair
+ * takes.  Past that method's limits (64 triangles of one value, 64
+ * independent edges in a link's core, 1024 such tetrahedra, 393216 triangles
+ * if there are any) the pairs are found in the way of Section 2.2.2, on the
+ * anti-transpose with clearing: the triangle columns go from the youngest
+ * triangle to the oldest, a column's pivot is its oldest cofacet, apparent
+ * pairs are taken at once and the other columns reduced in rounds.  The
+ * pairs are the same either way: those of the column algorithm on the
+ * tetrahedra's boundary block.
  * res:          a maxdim-3 build's result with its triangle and tetrahedron
  *               keys (not count-only).
  * tri_of_edge:  device, K int32: vr_pairs_dim1's output for this result.
@@ -452,9 +455,10 @@ VR_API int vr_tetra_write(const vr_result *res, const int64_t *offsets, int64_t 
  *               tet_key's order) of the tetrahedron paired with triangle t,
  *               or -1: t is paired with an edge, or else starts a class of
  *               dimension 2 that never dies.
- * Synchronises `stream` once per round.  Scratch from the library's cache:
- * 4 n^2 + 8 K + 60 T + 32 H bytes (H = 2T rounded up to a power of two)
- * plus 1 GiB, as vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a
+ * Synchronises `stream` once, and past the limits once more per round.
+ * Scratch from the library's cache: 4 n^2 + 12 K + 6 T bytes plus 17 MiB;
+ * past the limits 4 n^2 + 8 K + 60 T + 32 H bytes (H = 2T rounded up to a
+ * power of two) plus 1 GiB, as vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a
  * null argument, a result without tetrahedron keys, n > VR_MAX_POINTS or
  * T >= 2^31.  With no triangles nothing is written. */
 VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_edge, int64_t *tri_tet, void *stream);

@@ -2134,6 +2134,33 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_emit(const int32_t *ij, const l
     }
 }
 
+// The pairs of dimension 2 from the links of the edges; *done: whether the
+// limits of that method held.
+static int d2_links(const vr_result *res, const int32_t *tri_of_edge, long long *tri_tet, bool *done, hipStream_t s) {
+    const int64_t n = res->n_vertices, K = res->n_edges, T = res->n_triangles;
+    const unsigned long long *tri = (const unsigned long long *)res->tri_key;
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    size_t o = 0;
+    const size_t o_R = o; o = up(o + 4 * (size_t)n * (size_t)n);
+    const size_t o_clr = o; o = up(o + 8 * (size_t)((T + 1) / 2));
+    const size_t o_rng = o; o = up(o + 8 * (size_t)K);
+    const size_t o_lk = o; o += link_pairs_scratch(K, T);
+    char *ws = (char *)cache_get(o, s);
+    if (!ws) return VR_ENOMEM;
+    int32_t *R = (int32_t *)(ws + o_R), *clr = (int32_t *)(ws + o_clr), *rng = (int32_t *)(ws + o_rng);
+    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, R, n);
+    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, R, n, (const int32_t *)res->edge_ij, K, n);
+    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for((T + 1) / 2)), dim3(PD_BLOCK), 0, s, (unsigned long long *)clr,
+                       (T + 1) / 2);
+    hipLaunchKernelGGL(k_d2_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K, clr);
+    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (unsigned long long *)rng, K);
+    hipLaunchKernelGGL(k_d2_range, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, tri, T, rng);
+    const int st = link_pairs_dim2(R, (const int32_t *)res->edge_ij, tri, (const long long *)res->tet_off, rng, clr, n,
+                                   K, T, tri_tet, ws + o_lk, done, s);
+    cache_put(ws, s);
+    return st;
+}
+
 extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_edge, int64_t *tri_tet, void *stream) {
     if (!res) return VR_EINVAL;
     const int64_t n = res->n_vertices, K = res->n_edges, T = res->n_triangles, T3 = res->n_tetrahedra;
@@ -2142,6 +2169,14 @@ extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_
     if (!tri_tet || !tri_of_edge || !res->edge_ij || !res->tri_key || !res->tet_off || (T3 > 0 && !res->tet_key))
         return VR_EINVAL;
     const hipStream_t s = (hipStream_t)stream;
+    // from the links, within its limits (at most 64 triangles of one value,
+    // 1024 critical tetrahedra, of up to 393216 triangles); else, and for
+    // the few such results, by reducing the coboundaries below
+    {
+        bool done = false;
+        const int st = d2_links(res, tri_of_edge, (long long *)tri_tet, &done, s);
+        if (st != VR_OK || done) return st;
+    }
     long long H = 2;
     while (H < 2 * T) H <<= 1;
     const int64_t nch = (T + BC_CHUNK - 1) / BC_CHUNK;
