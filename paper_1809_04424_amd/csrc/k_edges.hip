@@ -15,7 +15,10 @@
 //                (cloud << qbits) | q, so clouds stay apart
 //   k_edges      the kept edges of every cloud in rank order, and their
 //                ranks scattered into each cloud's rank matrix
+//   k_small      all of the above for one cloud of up to 128 points
 #include "vr_device.h"
+
+#include <type_traits>
 
 // --------------------------------------------------------------- k_init ----
 __global__ __launch_bounds__(VR_BLOCK) void k_init(uint32_t *__restrict__ w, size_t words, VrCloud one,
@@ -846,4 +849,231 @@ void launch_edges(const VrDev &D, hipStream_t s) {
     if (g > 1024) g = 1024;
     if (g < 8) g = 8;  // every XCD's eighth of the edges needs a work-group
     hipLaunchKernelGGL(k_edges, dim3((unsigned)g), dim3(VR_BLOCK), 0, s, D);
+}
+
+// -------------------------------------------------------------- k_small ----
+// One cloud of few pairs: distances, threshold, sort, kept edges and rank
+// matrix by one work-group.  Such a build is bound by its launches, each a
+// few microseconds of latency with next to nothing to do: from k_init to
+// k_edges up to 13 of them took 52 us of a 64-point build, this takes 16.
+// The pairs (distance, endpoints) are sorted by stable passes of 8 bits, as
+// many as the distances have, that start from the pairs' order: wave w holds
+// pairs [64 R w, 64 R (w + 1)) in R steps of 64 and ranks each step's digits
+// by ballots; the waves' counts are scanned, and the pairs change places
+// through LDS.  (A bitonic network over the same keys is bound by LDS: a
+// 128-point build took 132 us with it, 77 with the passes.)
+#define SMALL_BLOCK 1024
+#define SMALL_WAVES (SMALL_BLOCK / VR_WAVE)
+#define SMALL_N 128           // E <= 8128: at most 8 pairs a thread
+#define SMALL_WORK (1 << 18)  // coordinate differences: above, the distances want more than one compute unit
+#define SMALL_CC 32
+
+// Pair number e < n (n - 1) / 2 of n <= 128 points.
+__device__ __forceinline__ void small_pair(int e, int n, int &i, int &j) {
+    auto start = [&](int x) { return x * (2 * n - x - 1) / 2; };
+    const float b = (float)(2 * n - 1), disc = b * b - 8.0f * (float)e;
+    int x = (int)((b - sqrtf(fmaxf(disc, 0.0f))) * 0.5f);
+    x = min(max(x, 0), n - 2);
+    while (x > 0 && start(x) > e) x--;
+    while (x < n - 2 && start(x + 1) <= e) x++;
+    i = x;
+    j = e - start(x) + x + 1;
+}
+
+template <typename T, bool MATRIX, int R>
+__global__ __launch_bounds__(SMALL_BLOCK) void k_small(VrDev D, VrCloud one, int scan_words) {
+    __shared__ uint32_t sq[SMALL_BLOCK * R];  // distances; before, the staged coordinates
+    __shared__ uint16_t sij[SMALL_BLOCK * R];
+    __shared__ __align__(16) uint16_t wh[SMALL_WAVES][VR_RADIX];
+    __shared__ uint32_t sh[4], wtot[4];
+    const int t = threadIdx.x, n = one.n, d = D.d, E = n * (n - 1) / 2;
+    const uint32_t lane = lane_id();
+    const int w = t / VR_WAVE;
+    VrCtl *ctl = D.ctl;
+    if (t < 16) ctl->ticket[t] = 0u;
+    if (t < scan_words) ((uint32_t *)D.st_scan)[t] = 0u;
+    if (t == 0) {
+        *(VrCloud *)D.cl = one;
+        D.cs[0].cand_base = 0u;
+        ctl->done = 0u;
+        ctl->n_tri = 0ull;
+        sh[0] = sh[1] = sh[2] = 0u;
+    }
+    const int e0 = w * VR_WAVE * R + (int)lane;  // pair of step r: e0 + 64 r
+    uint32_t q[R], ij[R], over = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        int i, j;
+        small_pair(min(e0 + VR_WAVE * r, E - 1), n, i, j);
+        ij[r] = (uint32_t)(i << 8 | j);
+    }
+    if constexpr (MATRIX) {
+        const int32_t *__restrict__ M = (const int32_t *)one.points;
+        int32_t v[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) v[r] = M[(ij[r] >> 8) * n + (ij[r] & 255u)];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (v[r] < 0) over = 1u;
+            q[r] = v[r] < 0 ? 0u : (uint32_t)v[r];
+        }
+    } else {
+        const T *__restrict__ pts = (const T *)one.points;
+        int32_t *xs = (int32_t *)sq;
+        // as many coordinates at a time as the array holds of n points, odd
+        const int cmax = min(SMALL_CC, ((SMALL_BLOCK * R / n - 1) | 1));
+        unsigned long long acc[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) acc[r] = 0ull;
+        for (int c0 = 0; c0 < d; c0 += cmax) {
+            const int cc = min(cmax, d - c0), ld = cc | 1;
+            __syncthreads();
+            for (int x = t; x < n * cc; x += SMALL_BLOCK) {
+                const int y = x / cc, cx = x - y * cc;
+                xs[y * ld + cx] = (int32_t)pts[(size_t)y * d + c0 + cx];
+            }
+            __syncthreads();
+            for (int cx = 0; cx < cc; cx++) {
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    long long df = (long long)xs[(int)(ij[r] >> 8) * ld + cx] - xs[(int)(ij[r] & 255u) * ld + cx];
+                    if (sizeof(T) == 4) {
+                        // |df| >= 2^16 makes df^2 >= 2^32 on its own
+                        over |= (df >= 65536 || df <= -65536) ? 1u : 0u;
+                        df = (df >= 65536 || df <= -65536) ? 0 : df;
+                    }
+                    acc[r] += (unsigned long long)(df * df);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (acc[r] > 0xFFFFFFFFull) over = 1u;
+            q[r] = acc[r] > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)acc[r];
+        }
+    }
+    __syncthreads();
+    // the bits of the distances, the overflow flag, the pairs below a distance threshold
+    const unsigned long long tau =
+        D.thr_kind != 3 ? 0ull : one.thr_num > (1ll << 32) ? (1ull << 32) : (unsigned long long)one.thr_num;
+    uint32_t any = 0, under = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (e0 + VR_WAVE * r < E) {
+            any |= q[r];
+            under += (unsigned long long)q[r] < tau ? 1u : 0u;
+        }
+    if (any) atomicOr(&sh[0], any);
+    if (over) atomicOr(&sh[1], 1u);
+    if (under) atomicAdd(&sh[2], under);
+    __syncthreads();
+    const uint32_t bits = sh[0];
+    const int K = D.thr_kind == 3 ? (int)sh[2] : (int)D.K_host;
+    if (t == 0) {
+        ctl->flags = sh[1];
+        ctl->n_cand = D.thr_kind == 3 ? (uint32_t)K : (uint32_t)E;
+        ctl->n_kept = (uint32_t)K;
+        // without triangles this is the last phase-1 kernel
+        if (!D.tri) publish_counts(D.mailbox, D.seq, sh[1], D.thr_kind == 3 ? (uint32_t)K : (uint32_t)E, (uint32_t)K, 0ull);
+    }
+    for (int shift = 0; shift < 32 && (bits >> shift) != 0; shift += 8) {
+        for (int x = t; x < SMALL_WAVES * VR_RADIX / 2; x += SMALL_BLOCK) ((uint32_t *)wh)[x] = 0u;
+        __syncthreads();
+        uint32_t at[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const bool in = e0 + VR_WAVE * r < E;
+            const uint32_t dg = (q[r] >> shift) & 255u;
+            unsigned long long same = __builtin_amdgcn_ballot_w64(in);
+#pragma unroll
+            for (int b = 0; b < 8; b++) {
+                const bool one_ = (dg >> b) & 1u;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(one_);
+                same &= one_ ? m : ~m;
+            }
+            const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            const uint32_t base = wh[w][dg];
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (in && before == 0) wh[w][dg] = (uint16_t)(base + (uint32_t)__popcll(same));
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            at[r] = base + before;
+        }
+        __syncthreads();
+        // where each wave's pairs of each digit go
+        uint32_t c[SMALL_WAVES], tot = 0;
+        if (t < VR_RADIX) {
+#pragma unroll
+            for (int x = 0; x < SMALL_WAVES; x++) {
+                c[x] = wh[x][t];
+                tot += c[x];
+            }
+        }
+        const uint32_t inc = wave_incl_scan_dpp(tot);
+        if (t < VR_RADIX && lane == VR_WAVE - 1) wtot[w] = inc;
+        __syncthreads();
+        if (t < VR_RADIX) {
+            uint32_t o = inc - tot;
+            for (int x = 0; x < w; x++) o += wtot[x];
+#pragma unroll
+            for (int x = 0; x < SMALL_WAVES; x++) {
+                wh[x][t] = (uint16_t)o;
+                o += c[x];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (e0 + VR_WAVE * r < E) {
+                const uint32_t p = wh[w][(q[r] >> shift) & 255u] + at[r];
+                sq[p] = q[r];
+                sij[p] = (uint16_t)ij[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int e = min(e0 + VR_WAVE * r, E - 1);
+            q[r] = sq[e];
+            ij[r] = sij[e];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int g = e0 + VR_WAVE * r;
+        if (g >= K) break;
+        const uint32_t i = ij[r] >> 8, j = ij[r] & 255u;
+        D.se_q[g] = q[r];
+        D.se_ij[g] = (i << 16) | j;
+        if (D.tri) {
+            const uint32_t e = (D.tag << 24) | (uint32_t)g;
+            D.star_r[i * n + j] = e;
+            D.star_r[j * n + i] = e;
+        }
+    }
+}
+
+// One cloud of 2 to 128 points (eight pairs a thread), with few enough
+// coordinates (a matrix has none).  Whole builds here and in the kernels of
+// their own, us: 64 points of 2 coordinates 48, 85, of 128 63, 84; 128 points
+// of 2 coordinates 77, 96, of 32 99, 107.
+bool small_applies(const VrDev &D) {
+    return D.C == 1 && D.maxn >= 2 && D.maxn <= SMALL_N &&
+           (D.dtype > 3 || D.E * D.d <= (long long)SMALL_WORK);
+}
+
+void launch_small(const VrDev &D, const VrCloud &one, int scan_words, hipStream_t s) {
+    auto go = [&](auto per) {
+        constexpr int R = decltype(per)::value;
+        const dim3 g(1), b(SMALL_BLOCK);
+        if (D.dtype == 1) hipLaunchKernelGGL((k_small<int8_t, false, R>), g, b, 0, s, D, one, scan_words);
+        else if (D.dtype == 2) hipLaunchKernelGGL((k_small<int16_t, false, R>), g, b, 0, s, D, one, scan_words);
+        else if (D.dtype == 3) hipLaunchKernelGGL((k_small<int32_t, false, R>), g, b, 0, s, D, one, scan_words);
+        else hipLaunchKernelGGL((k_small<int32_t, true, R>), g, b, 0, s, D, one, scan_words);
+    };
+    if (D.E <= 2 * SMALL_BLOCK) go(std::integral_constant<int, 2>());
+    else if (D.E <= 4 * SMALL_BLOCK) go(std::integral_constant<int, 4>());
+    else go(std::integral_constant<int, 8>());
 }

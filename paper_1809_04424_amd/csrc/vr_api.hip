@@ -713,29 +713,33 @@ int build_impl(const vr_request *reqs, long long count, hipStream_t s, Owner &ow
     // stream of a graph); stage events only in builds timed stage by stage,
     // which are never captured.
     auto phase1 = [&](hipStream_t st) -> bool {
-        mark(ST_DIST);
-        if (C > 1) {
-            if (hipMemcpyAsync((void *)D.cl, g_host.tab, sizeof(VrCloud) * (size_t)C, hipMemcpyHostToDevice, st) !=
-                hipSuccess)
-                return false;
-            launch_init(D, P.zero_bytes / 4, nullptr, nullptr, st);
-            launch_cloud_maps(D, st);
+        if (small_applies(D) && !timing_all) {  // timed stage by stage: the stages' own kernels
+            launch_small(D, one, (int)(2 * ((Kmax + VR_TILE - 1) / VR_TILE)), st);
         } else {
-            launch_init(D, P.zero_bytes / 4, &one, (VrCloud *)D.cl, st);
+            mark(ST_DIST);
+            if (C > 1) {
+                if (hipMemcpyAsync((void *)D.cl, g_host.tab, sizeof(VrCloud) * (size_t)C, hipMemcpyHostToDevice, st) !=
+                    hipSuccess)
+                    return false;
+                launch_init(D, P.zero_bytes / 4, nullptr, nullptr, st);
+                launch_cloud_maps(D, st);
+            } else {
+                launch_init(D, P.zero_bytes / 4, &one, (VrCloud *)D.cl, st);
+            }
+            if (gram_applies(D)) launch_gram(D, nullptr, st);
+            else launch_dist(D, nullptr, st);
+            mark(ST_SELECT);
+            if (need_hist) launch_pivot(D, st);
+            launch_select(D, st);
+            launch_hist_fold(&D.ctl->hist8[0][0][0], VR_HIST8_STRIDE, D.passes * VR_RADIX, st);
+            mark(ST_SORT);
+            {
+                const SortJob J = edge_sort_job(D);
+                for (int p = 0; p < D.passes; p++) launch_sort_pass(J, D.ntile_E, p, st);
+            }
+            mark(ST_EDGES);
+            launch_edges(D, st);
         }
-        if (gram_applies(D)) launch_gram(D, nullptr, st);
-        else launch_dist(D, nullptr, st);
-        mark(ST_SELECT);
-        if (need_hist) launch_pivot(D, st);
-        launch_select(D, st);
-        launch_hist_fold(&D.ctl->hist8[0][0][0], VR_HIST8_STRIDE, D.passes * VR_RADIX, st);
-        mark(ST_SORT);
-        {
-            const SortJob J = edge_sort_job(D);
-            for (int p = 0; p < D.passes; p++) launch_sort_pass(J, D.ntile_E, p, st);
-        }
-        mark(ST_EDGES);
-        launch_edges(D, st);
         mark(ST_STAR);
         if (want_tri) launch_rows(D, st);
         mark(ST_COUNT);

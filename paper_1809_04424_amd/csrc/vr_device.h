@@ -507,6 +507,8 @@ void launch_select(const VrDev &D, hipStream_t s);
 void launch_sort_pass(const SortJob &J, long long max_tiles, int pass, hipStream_t s);
 void launch_hist_fold(uint32_t *h0, int stride, int bins, hipStream_t s);
 void launch_edges(const VrDev &D, hipStream_t s);
+bool small_applies(const VrDev &D);
+void launch_small(const VrDev &D, const VrCloud &one, int scan_words, hipStream_t s);
 void launch_rows(const VrDev &D, hipStream_t s);
 int enum_parts_count(long long V);
 int enum_parts_write(long long V, long long C);
