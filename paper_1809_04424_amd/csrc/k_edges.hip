@@ -474,13 +474,140 @@ SortJob edge_sort_job(const VrDev &D) {
 // order (8 ballots per 64 keys), the work-group combines the waves, one
 // look-back per digit gives the tile's global offsets, and the tile is
 // scattered through LDS so equal digits leave as contiguous runs.
+// LDS of one tile's pass.
+struct SortLds {
+    uint32_t whist[VR_WAVES][VR_RADIX];
+    uint32_t tstart[VR_RADIX];
+    uint32_t gpre[VR_RADIX];
+    uint32_t key[VR_TILE];
+    uint32_t val[VR_TILE];
+    uint32_t sum[VR_WAVES];
+};
+
+// Sum of the counts of digit t before `tile`, for tiles that are all on the
+// device at once (DIRECT): the tiles come in groups of 16, whose last one
+// adds up the others' counts and publishes the group's.  A tile reads at
+// most 15 counts and one per group before its own, instead of every count
+// back to the nearest inclusive one: at 400 to 600 tiles, all started
+// together, those reads bound the pass.
+#define SORT_GROUP 16
+__device__ __forceinline__ uint32_t sort_poll(const uint32_t *p, uint32_t s) {
+    for (int nap = 1; (s >> 30) == VR_ST_NONE; nap = nap < 16 ? 2 * nap : 16) {
+        backoff(nap);
+        s = st_load32(p);
+    }
+    return s & 0x3FFFFFFFu;
+}
+__device__ __forceinline__ uint32_t sort_before(uint32_t *st, int tile, int stride, uint32_t own) {
+    const int g = tile / SORT_GROUP, i = tile % SORT_GROUP;
+    uint32_t s[SORT_GROUP], acc = 0;
+#pragma unroll
+    for (int j = 0; j < SORT_GROUP; j++)
+        s[j] = j < i ? st_load32(st + (size_t)(g * SORT_GROUP + j) * stride) : (VR_ST_AGG << 30);
+#pragma unroll
+    for (int j = 0; j < SORT_GROUP; j++) acc += sort_poll(st + (size_t)(g * SORT_GROUP + j) * stride, s[j]);
+    if (i == SORT_GROUP - 1) st_store32(st + (size_t)tile * stride, st_pack32(VR_ST_AGG, acc + own));
+    for (int h = 0; h < g; h += SORT_GROUP) {
+#pragma unroll
+        for (int j = 0; j < SORT_GROUP; j++)
+            s[j] = h + j < g ? st_load32(st + (size_t)((h + j + 1) * SORT_GROUP - 1) * stride) : (VR_ST_AGG << 30);
+#pragma unroll
+        for (int j = 0; j < SORT_GROUP; j++)
+            acc += sort_poll(st + (size_t)((h + j + 1) * SORT_GROUP - 1) * stride, s[j]);
+    }
+    return acc;
+}
+
+// One tile of a pass: rank, publish the counts and look back, scatter.  kk:
+// the thread's keys (item `it` of wave w at 64 it + lane of the wave's 512);
+// gstart: where digit t starts.
+template <bool DIRECT>
+__device__ __forceinline__ void sort_tile(SortLds &L, int tile, const uint32_t (&kk)[VR_ITEMS], uint32_t Kc,
+                                          long long cap, int shift, uint32_t gstart,
+                                          const uint32_t *__restrict__ vsrc, uint32_t *__restrict__ kdst,
+                                          uint32_t *__restrict__ vdst, uint32_t *st, uint32_t *st_next) {
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    for (int x = 0; x < VR_WAVES; x++) L.whist[x][t] = 0u;
+    __syncthreads();
+    uint32_t vv[VR_ITEMS], rk[VR_ITEMS];
+    const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
+    // values at clamped addresses, issued before the ranking (items
+    // past the count are never used)
+#pragma unroll
+    for (int it = 0; it < VR_ITEMS; it++) vv[it] = vsrc[min(base + (long long)it * VR_WAVE + lane, cap - 1)];
+#pragma unroll
+    for (int it = 0; it < VR_ITEMS; it++) {
+        const long long idx = base + (long long)it * VR_WAVE + lane;
+        const bool valid = idx < (long long)Kc;
+        const uint32_t k = kk[it];
+        const uint32_t dg = (k >> shift) & 255u;
+        unsigned long long peers = ballot64(valid);
+#pragma unroll
+        for (int b = 0; b < VR_RADIX_BITS; b++) {
+            const unsigned long long m = ballot64((dg >> b) & 1u);
+            peers &= ((dg >> b) & 1u) ? m : ~m;
+        }
+        uint32_t before = 0;
+        if (valid) before = L.whist[w][dg];
+        const uint32_t r = before + (uint32_t)__popcll(peers & lanemask_lt());
+        rk[it] = r;
+        if (valid && (peers & lanemask_lt()) == 0ull) L.whist[w][dg] = before + (uint32_t)__popcll(peers);
+        // the wave's LDS operations run in order; keep the compiler
+        // from moving the next item's read above this write
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    uint32_t wpre[VR_WAVES];
+    uint32_t tc = 0;
+#pragma unroll
+    for (int x = 0; x < VR_WAVES; x++) { wpre[x] = tc; tc += L.whist[x][t]; }
+    uint32_t ttot;
+    const uint32_t tstart = block_excl_scan<uint32_t>(tc, L.sum, &ttot);
+    L.tstart[t] = tstart;
+    uint32_t prev = 0;
+    if (DIRECT) {
+        if (tile % SORT_GROUP != SORT_GROUP - 1) st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
+        prev = sort_before(st + t, tile, VR_RADIX, tc);
+    } else if (tile == 0) {
+        st_store32(st + t, st_pack32(VR_ST_INC, tc));
+    } else {
+        st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
+        prev = lookback32(st + t, tile, VR_RADIX);
+        st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_INC, prev + tc));
+    }
+    L.gpre[t] = gstart + prev;
+    st_next[(size_t)tile * VR_RADIX + t] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < VR_WAVES; x++) L.whist[x][t] = wpre[x];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < VR_ITEMS; it++) {
+        const long long idx = base + (long long)it * VR_WAVE + lane;
+        if (idx < (long long)Kc) {
+            const uint32_t dg = (kk[it] >> shift) & 255u;
+            const uint32_t lp = L.tstart[dg] + L.whist[w][dg] + rk[it];
+            L.key[lp] = kk[it];
+            L.val[lp] = vv[it];
+        }
+    }
+    __syncthreads();
+    const uint32_t valid_n = (uint32_t)min((long long)VR_TILE, (long long)Kc - (long long)tile * VR_TILE);
+#pragma unroll
+    for (int m = 0; m < VR_ITEMS; m++) {
+        const uint32_t lp = (uint32_t)t + (uint32_t)m * VR_BLOCK;
+        if (lp < valid_n) {
+            const uint32_t k = L.key[lp];
+            const uint32_t dg = (k >> shift) & 255u;
+            const uint32_t gp = L.gpre[dg] + (lp - L.tstart[dg]);
+            kdst[gp] = k;
+            vdst[gp] = L.val[lp];
+        }
+    }
+}
+
 __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int S) {
-    __shared__ uint32_t s_whist[VR_WAVES][VR_RADIX];
-    __shared__ uint32_t s_tstart[VR_RADIX];
-    __shared__ uint32_t s_gpre[VR_RADIX];
-    __shared__ uint32_t s_key[VR_TILE];
-    __shared__ uint32_t s_val[VR_TILE];
-    __shared__ uint32_t sh_w[VR_WAVES];
+    __shared__ SortLds L;
     __shared__ uint32_t sh_nz[VR_MAX_PASSES][VR_WAVES];
     __shared__ int sh_tile;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -540,89 +667,13 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
 
     // global start of digit t
     uint32_t tot;
-    const uint32_t gstart = block_excl_scan<uint32_t>(hp, sh_w, &tot);
+    const uint32_t gstart = block_excl_scan<uint32_t>(hp, L.sum, &tot);
 
-    auto do_tile = [&](int tile, const uint32_t (&kk)[VR_ITEMS]) {
-        for (int x = 0; x < VR_WAVES; x++) s_whist[x][t] = 0u;
-        __syncthreads();
-        uint32_t vv[VR_ITEMS], rk[VR_ITEMS];
-        const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
-        // values at clamped addresses, issued before the ranking (items
-        // past the count are never used)
-#pragma unroll
-        for (int it = 0; it < VR_ITEMS; it++) vv[it] = vsrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-#pragma unroll
-        for (int it = 0; it < VR_ITEMS; it++) {
-            const long long idx = base + (long long)it * VR_WAVE + lane;
-            const bool valid = idx < (long long)Kc;
-            const uint32_t k = kk[it];
-            const uint32_t dg = (k >> shift) & 255u;
-            unsigned long long peers = ballot64(valid);
-#pragma unroll
-            for (int b = 0; b < VR_RADIX_BITS; b++) {
-                const unsigned long long m = ballot64((dg >> b) & 1u);
-                peers &= ((dg >> b) & 1u) ? m : ~m;
-            }
-            uint32_t before = 0;
-            if (valid) before = s_whist[w][dg];
-            const uint32_t r = before + (uint32_t)__popcll(peers & lanemask_lt());
-            rk[it] = r;
-            if (valid && (peers & lanemask_lt()) == 0ull) s_whist[w][dg] = before + (uint32_t)__popcll(peers);
-            // the wave's LDS operations run in order; keep the compiler
-            // from moving the next item's read above this write
-            __builtin_amdgcn_wave_barrier();
-        }
-        __syncthreads();
-        uint32_t wpre[VR_WAVES];
-        uint32_t tc = 0;
-#pragma unroll
-        for (int x = 0; x < VR_WAVES; x++) { wpre[x] = tc; tc += s_whist[x][t]; }
-        uint32_t ttot;
-        const uint32_t tstart = block_excl_scan<uint32_t>(tc, sh_w, &ttot);
-        s_tstart[t] = tstart;
-        uint32_t prev = 0;
-        if (tile == 0) {
-            st_store32(st + t, st_pack32(VR_ST_INC, tc));
-        } else {
-            st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
-            prev = lookback32(st + t, tile, VR_RADIX);
-            st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_INC, prev + tc));
-        }
-        s_gpre[t] = gstart + prev;
-        st_next[(size_t)tile * VR_RADIX + t] = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < VR_WAVES; x++) s_whist[x][t] = wpre[x];
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < VR_ITEMS; it++) {
-            const long long idx = base + (long long)it * VR_WAVE + lane;
-            if (idx < (long long)Kc) {
-                const uint32_t dg = (kk[it] >> shift) & 255u;
-                const uint32_t lp = s_tstart[dg] + s_whist[w][dg] + rk[it];
-                s_key[lp] = kk[it];
-                s_val[lp] = vv[it];
-            }
-        }
-        __syncthreads();
-        const uint32_t valid_n = (uint32_t)min((long long)VR_TILE, (long long)Kc - (long long)tile * VR_TILE);
-#pragma unroll
-        for (int m = 0; m < VR_ITEMS; m++) {
-            const uint32_t lp = (uint32_t)t + (uint32_t)m * VR_BLOCK;
-            if (lp < valid_n) {
-                const uint32_t k = s_key[lp];
-                const uint32_t dg = (k >> shift) & 255u;
-                const uint32_t gp = s_gpre[dg] + (lp - s_tstart[dg]);
-                kdst[gp] = k;
-                vdst[gp] = s_val[lp];
-            }
-        }
-    };
     if (direct) {
         uint32_t kk[VR_ITEMS];
 #pragma unroll
         for (int it = 0; it < VR_ITEMS; it++) kk[it] = (a & 1) ? kB[it] : kA[it];
-        do_tile((int)blockIdx.x, kk);
+        sort_tile<true>(L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
         return;
     }
     for (;;) {
@@ -634,7 +685,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
             const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
 #pragma unroll
             for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-            do_tile(tile, kk);
+            sort_tile<false>(L, tile, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
         }
         if ((int)gridDim.x >= ntiles) break;  // every tile went out in the first round of claims
     }
@@ -648,14 +699,10 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
 // for its first tile, publishes the inclusive prefixes of all S, and finally
 // re-reads, ranks and scatters each tile as the single-tile pass does.
 #define SORT_MULTI_MAX 16
+#define SORT_DIRECT 768  // work-groups of 43 KB of LDS that fit on the device at once (three a compute unit)
 __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pass) {
-    __shared__ uint32_t s_whist[VR_WAVES][VR_RADIX];
-    __shared__ uint32_t s_tstart[VR_RADIX];
-    __shared__ uint32_t s_gpre[VR_RADIX];
-    __shared__ uint32_t s_key[VR_TILE];
-    __shared__ uint32_t s_val[VR_TILE];
+    __shared__ SortLds L;
     __shared__ uint32_t s_cnt[SORT_MULTI_MAX][VR_RADIX];  // digit counts of the claimed tiles
-    __shared__ uint32_t sh_w[VR_WAVES];
     __shared__ int sh_tile;
     bool active = false;
     const uint32_t Kc = *J.count;
@@ -675,8 +722,22 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
     uint32_t *st_next = J.st[(a + 1) & 1];
     const int shift = VR_RADIX_BITS * pass;
     uint32_t tot;
-    const uint32_t gstart = block_excl_scan<uint32_t>(J.hist[pass * VR_RADIX + t], sh_w, &tot);
+    const uint32_t gstart = block_excl_scan<uint32_t>(J.hist[pass * VR_RADIX + t], L.sum, &tot);
 
+    // few tiles after all (the launch knows only the pairs, of which a
+    // threshold keeps a part): a tile per work-group, all of which fit on the
+    // device at once, without tickets or a count of its own.  A pass, before
+    // -> after (and with look-back to the nearest inclusive count): 0.8
+    // million edges of 8 million pairs 19 -> 13 us (15), 1.1 of 34 million
+    // 25 -> 16 (19), 1.2 of 9.7 million in 32 clouds 33 -> 20 (24).
+    if (ntiles <= min((int)gridDim.x, SORT_DIRECT)) {
+        uint32_t kk[VR_ITEMS];
+        const long long base = (long long)blockIdx.x * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
+#pragma unroll
+        for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
+        sort_tile<true>(L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+        return;
+    }
     for (;;) {
         const int t0 = claim_tiles(&J.ticket[pass], S, &sh_tile);
         if (t0 >= ntiles) break;
@@ -718,7 +779,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
         for (int j = 0; j < nt; j++) {
             const int tile = t0 + j;
             __syncthreads();  // LDS of the previous tile is reused
-            for (int x = 0; x < VR_WAVES; x++) s_whist[x][t] = 0u;
+            for (int x = 0; x < VR_WAVES; x++) L.whist[x][t] = 0u;
             __syncthreads();
             uint32_t kk[VR_ITEMS], vv[VR_ITEMS], rk[VR_ITEMS];
             const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
@@ -741,31 +802,31 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
                     peers &= ((dg >> b) & 1u) ? m : ~m;
                 }
                 uint32_t before = 0;
-                if (valid) before = s_whist[w][dg];
+                if (valid) before = L.whist[w][dg];
                 rk[it] = before + (uint32_t)__popcll(peers & lanemask_lt());
-                if (valid && (peers & lanemask_lt()) == 0ull) s_whist[w][dg] = before + (uint32_t)__popcll(peers);
+                if (valid && (peers & lanemask_lt()) == 0ull) L.whist[w][dg] = before + (uint32_t)__popcll(peers);
                 __builtin_amdgcn_wave_barrier();
             }
             __syncthreads();
             uint32_t wpre[VR_WAVES];
             uint32_t tc = 0;
 #pragma unroll
-            for (int x = 0; x < VR_WAVES; x++) { wpre[x] = tc; tc += s_whist[x][t]; }
+            for (int x = 0; x < VR_WAVES; x++) { wpre[x] = tc; tc += L.whist[x][t]; }
             uint32_t ttot;
-            s_tstart[t] = block_excl_scan<uint32_t>(tc, sh_w, &ttot);
-            s_gpre[t] = gstart + s_cnt[j][t];
+            L.tstart[t] = block_excl_scan<uint32_t>(tc, L.sum, &ttot);
+            L.gpre[t] = gstart + s_cnt[j][t];
             __syncthreads();
 #pragma unroll
-            for (int x = 0; x < VR_WAVES; x++) s_whist[x][t] = wpre[x];
+            for (int x = 0; x < VR_WAVES; x++) L.whist[x][t] = wpre[x];
             __syncthreads();
 #pragma unroll
             for (int it = 0; it < VR_ITEMS; it++) {
                 const long long idx = base + (long long)it * VR_WAVE + lane;
                 if (idx < (long long)Kc) {
                     const uint32_t dg = (kk[it] >> shift) & 255u;
-                    const uint32_t lp = s_tstart[dg] + s_whist[w][dg] + rk[it];
-                    s_key[lp] = kk[it];
-                    s_val[lp] = vv[it];
+                    const uint32_t lp = L.tstart[dg] + L.whist[w][dg] + rk[it];
+                    L.key[lp] = kk[it];
+                    L.val[lp] = vv[it];
                 }
             }
             __syncthreads();
@@ -774,10 +835,10 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
             for (int m = 0; m < VR_ITEMS; m++) {
                 const uint32_t lp = (uint32_t)t + (uint32_t)m * VR_BLOCK;
                 if (lp < valid_n) {
-                    const uint32_t k = s_key[lp];
+                    const uint32_t k = L.key[lp];
                     const uint32_t dg = (k >> shift) & 255u;
-                    kdst[s_gpre[dg] + (lp - s_tstart[dg])] = k;
-                    vdst[s_gpre[dg] + (lp - s_tstart[dg])] = s_val[lp];
+                    kdst[L.gpre[dg] + (lp - L.tstart[dg])] = k;
+                    vdst[L.gpre[dg] + (lp - L.tstart[dg])] = L.val[lp];
                 }
             }
         }
