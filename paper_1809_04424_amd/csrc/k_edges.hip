@@ -81,12 +81,37 @@ __device__ __forceinline__ void tile_of(long long t, long long nb, int *bi, int 
 // One work-group computes the 64 x 64 pairs (i in block bi, j in block bj) of
 // one cloud.  Lane l of every wave owns column j = 64*bj + l; wave w owns rows
 // i = 64*bi + w + 4m (m < 16).  Coordinates are staged through LDS 64 at a
-// time; the column operand is padded to avoid bank conflicts.  Writes of a
-// row are contiguous in pair order, so every wave stores 256 contiguous bytes.
+// time: the rows' by coordinate, a wave's 16 rows together, so that a
+// coordinate of all of them is four 16-byte reads; the columns' padded to
+// avoid bank conflicts.  Writes of a row are contiguous in pair order, so
+// every wave stores 256 contiguous bytes.
+//
+// Few coordinates leave the kernel bound by the instructions around them, so
+// the row number is a scalar and the products are 24-bit ones (a difference
+// that passes has 17 bits; four instructions where the 64-bit product and
+// its operands took about ten), and up to 8 coordinates take an eighth of the
+// LDS.  Before -> after, us: 8192 points of 3 16-bit coordinates 57 -> 44 (134
+// MB written at 3.0 TB/s), 777 of 37 20 -> 17, 32 clouds of 3 8-bit ones 37 ->
+// 35 (there the histogram's atomics).
 #define DIST_TB 64
-#define DIST_CC 64
 
+// One coordinate's squared difference added to acc.
 template <typename T>
+__device__ __forceinline__ void dist_add(unsigned long long &acc, int32_t x, int32_t y, uint32_t &over) {
+    int32_t df;
+    if constexpr (sizeof(T) == 4) {
+        df = __builtin_elementwise_sub_sat(x, y);
+        // |df| >= 2^16 makes df^2 >= 2^32 on its own
+        const bool far = (uint32_t)df + 65535u > 131070u;
+        over |= far ? 1u : 0u;
+        df = far ? 0 : df;
+    } else {
+        df = x - y;
+    }
+    acc += (uint32_t)__mul24(df, df);  // the low 32 bits: all of df^2
+}
+
+template <typename T, int CC>
 __global__ __launch_bounds__(VR_BLOCK) void k_dist(VrDev D) {
     const long long tg = blockIdx.x;
     const int c = (D.C == 1) ? 0 : (int)D.tcloud[tg];
@@ -96,11 +121,11 @@ __global__ __launch_bounds__(VR_BLOCK) void k_dist(VrDev D) {
     tile_of(tg - cl.tbase, (n + DIST_TB - 1) / DIST_TB, &bi, &bj);
     const T *__restrict__ pts = (const T *)cl.points;
     uint32_t *__restrict__ q = D.q + cl.pbase;
-    __shared__ int32_t xi[DIST_TB][DIST_CC];
-    __shared__ int32_t xj[DIST_TB][DIST_CC + 1];
+    __shared__ int4 xi[CC][DIST_TB / 4];  // row r at word 16 (r % 4) + r / 4
+    __shared__ int32_t xj[DIST_TB][CC + 1];
     __shared__ uint32_t hist[VR_NBUCKET];
     const int need_hist = D.need_hist;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int j = bj * DIST_TB + lane;
     unsigned long long acc[16];
 #pragma unroll
@@ -108,49 +133,43 @@ __global__ __launch_bounds__(VR_BLOCK) void k_dist(VrDev D) {
     uint32_t over = 0;
     if (need_hist)
         for (int b = threadIdx.x; b < VR_NBUCKET; b += VR_BLOCK) hist[b] = 0u;
-    for (int c0 = 0; c0 < d; c0 += DIST_CC) {
-        const int cc = min(DIST_CC, d - c0);
+    for (int c0 = 0; c0 < d; c0 += CC) {
+        const int cc = min(CC, d - c0);
         __syncthreads();
-        if (cc == DIST_CC) {
-            for (int x = threadIdx.x; x < DIST_TB * DIST_CC; x += VR_BLOCK) {
-                const int r = x / DIST_CC, cx = x % DIST_CC;
-                const int gi = bi * DIST_TB + r, gj = bj * DIST_TB + r;
-                xi[r][cx] = gi < n ? (int32_t)pts[(size_t)gi * d + c0 + cx] : 0;
-                xj[r][cx] = gj < n ? (int32_t)pts[(size_t)gj * d + c0 + cx] : 0;
-            }
+        auto stage = [&](int r, int cx) {
+            const int gi = bi * DIST_TB + r, gj = bj * DIST_TB + r;
+            ((int32_t *)xi[cx])[16 * (r & 3) + (r >> 2)] = gi < n ? (int32_t)pts[(size_t)gi * d + c0 + cx] : 0;
+            xj[r][cx] = gj < n ? (int32_t)pts[(size_t)gj * d + c0 + cx] : 0;
+        };
+        if (cc == CC) {
+            for (int x = threadIdx.x; x < DIST_TB * CC; x += VR_BLOCK) stage(x / CC, x % CC);
         } else {
             // a partial chunk (every chunk when d < 64): stage only the cc
             // coordinates the loop below reads
-            for (int x = threadIdx.x; x < DIST_TB * cc; x += VR_BLOCK) {
-                const int r = x / cc, cx = x - r * cc;
-                const int gi = bi * DIST_TB + r, gj = bj * DIST_TB + r;
-                xi[r][cx] = gi < n ? (int32_t)pts[(size_t)gi * d + c0 + cx] : 0;
-                xj[r][cx] = gj < n ? (int32_t)pts[(size_t)gj * d + c0 + cx] : 0;
-            }
+            for (int x = threadIdx.x; x < DIST_TB * cc; x += VR_BLOCK) stage(x / cc, x - x / cc * cc);
         }
         __syncthreads();
         for (int cx = 0; cx < cc; cx++) {
-            const long long y = xj[lane][cx];
+            const int32_t y = xj[lane][cx];
 #pragma unroll
-            for (int m = 0; m < 16; m++) {
-                long long df = (long long)xi[w + 4 * m][cx] - y;
-                if (sizeof(T) == 4) {
-                    // |df| >= 2^16 makes df^2 >= 2^32 on its own
-                    over |= (df >= 65536 || df <= -65536) ? 1u : 0u;
-                    df = (df >= 65536 || df <= -65536) ? 0 : df;
-                }
-                acc[m] += (unsigned long long)(df * df);
+            for (int m = 0; m < 16; m += 4) {
+                const int4 x = xi[cx][4 * w + m / 4];
+                dist_add<T>(acc[m], x.x, y, over);
+                dist_add<T>(acc[m + 1], x.y, y, over);
+                dist_add<T>(acc[m + 2], x.z, y, over);
+                dist_add<T>(acc[m + 3], x.w, y, over);
             }
         }
     }
 #pragma unroll
     for (int m = 0; m < 16; m++) {
         const int i = bi * DIST_TB + w + 4 * m;
+        uint32_t *__restrict__ row = q + (row_start(i, n) - i - 1);  // of pair (i, j): row[j]
         if (i < j && j < n) {
             unsigned long long v = acc[m];
             if (v > 0xFFFFFFFFull) { over = 1u; v = 0xFFFFFFFFull; }
             const uint32_t qq = (uint32_t)v;
-            q[row_start(i, n) + (j - i - 1)] = qq;
+            row[j] = qq;
             if (need_hist) atomicAdd(&hist[bucket_of(qq)], 1u);
         }
     }
@@ -217,9 +236,16 @@ __global__ __launch_bounds__(VR_BLOCK) void k_dist_mat(VrDev D) {
 void launch_dist(const VrDev &D, const void *points, hipStream_t s) {
     (void)points;
     const dim3 grid((unsigned)D.tiles);
-    if (D.dtype == 1) hipLaunchKernelGGL(k_dist<int8_t>, grid, dim3(VR_BLOCK), 0, s, D);
-    else if (D.dtype == 2) hipLaunchKernelGGL(k_dist<int16_t>, grid, dim3(VR_BLOCK), 0, s, D);
-    else if (D.dtype == 3) hipLaunchKernelGGL(k_dist<int32_t>, grid, dim3(VR_BLOCK), 0, s, D);
+    // coordinates staged at a time: up to 8 in all leave room for more
+    // work-groups on a compute unit (8192 points of 3: 49 us with 64, 44)
+    auto go = [&](auto t) {
+        using T = decltype(t);
+        if (D.d <= 8) hipLaunchKernelGGL((k_dist<T, 8>), grid, dim3(VR_BLOCK), 0, s, D);
+        else hipLaunchKernelGGL((k_dist<T, 64>), grid, dim3(VR_BLOCK), 0, s, D);
+    };
+    if (D.dtype == 1) go(int8_t());
+    else if (D.dtype == 2) go(int16_t());
+    else if (D.dtype == 3) go(int32_t());
     else hipLaunchKernelGGL(k_dist_mat, grid, dim3(VR_BLOCK), 0, s, D);  // VR_DIST
 }
 
@@ -382,37 +408,57 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_sel_scan(VrDev D) {
     if (t == 0) D.ctl->n_cand = sh_carry;
 }
 
+// The candidates are compacted in LDS first, so that they leave in whole
+// lines and only they are histogrammed: with each thread writing its own
+// eight pairs' and every pair going through the histogram's tests, a tile of
+// few candidates took as long as a full one.  Before -> after, us: 1.1
+// million of 34 million pairs 84 -> 58, 0.8 of 8 million 25 -> 18, all of
+// 0.6 million 15 -> 14.
 __global__ __launch_bounds__(VR_BLOCK) void k_sel_write(VrDev D) {
     __shared__ uint32_t sh_w[VR_WAVES];
+    __shared__ uint32_t s_key[VR_TILE];
+    __shared__ uint32_t s_val[VR_TILE];
     __shared__ uint32_t h8[VR_MAX_PASSES][VR_RADIX];
     VrCtl *ctl = D.ctl;
-    const int t = threadIdx.x, tile = (int)blockIdx.x;
+    const int t = threadIdx.x;
     for (int x = t; x < VR_MAX_PASSES * VR_RADIX; x += VR_BLOCK) (&h8[0][0])[x] = 0u;
-    // clear this tile's statuses for the first active radix pass
-    D.st_sort[0][(size_t)tile * VR_RADIX + t] = 0u;
-    SelItems I;
-    const uint32_t c = select_items(D, tile, I);
-    uint32_t tt;
-    const uint32_t ex = block_excl_scan<uint32_t>(c, sh_w, &tt);  // also orders the h8 clear
-    uint32_t p = D.st_sel[tile] + ex;
+    uint32_t some = 0;
+    for (int tile = (int)blockIdx.x; tile < (int)D.ntile_E; tile += (int)gridDim.x) {
+        // clear this tile's statuses for the first active radix pass
+        D.st_sort[0][(size_t)tile * VR_RADIX + t] = 0u;
+        SelItems I;
+        const uint32_t c = select_items(D, tile, I);
+        uint32_t tt;
+        // also orders the h8 clear, and the last tile's reads of s_key
+        const uint32_t ex = block_excl_scan<uint32_t>(c, sh_w, &tt);
+        const uint32_t base = D.st_sel[tile];
+        uint32_t p = ex;
 #pragma unroll
-    for (int m = 0; m < VR_ITEMS; m++) {
-        if (I.first[m]) D.cs[I.cc[m]].cand_base = p;
-        if (I.keep[m]) {
-            D.key[0][p] = I.kv[m];
-            D.val[0][p] = I.vv[m];
-            p++;
+        for (int m = 0; m < VR_ITEMS; m++) {
+            if (I.first[m]) D.cs[I.cc[m]].cand_base = base + p;
+            if (I.keep[m]) {
+                s_key[p] = I.kv[m];
+                s_val[p] = I.vv[m];
+                p++;
+            }
+        }
+        some |= tt;  // uniform over the work-group
+        __syncthreads();
+        // digit histograms: low digits are spread, the top one (cloud and
+        // high bits of q) takes few values
+        for (uint32_t x0 = 0; x0 < tt; x0 += VR_BLOCK) {
+            const uint32_t x = x0 + (uint32_t)t;
+            const bool in = x < tt;
+            const uint32_t k = s_key[in ? x : 0u];
+            if (in) {
+                D.key[0][base + x] = k;
+                D.val[0][base + x] = s_val[x];
+            }
+            for (int ps = 0; ps < D.passes - 1; ps++) spread_add(h8[ps], (k >> (8 * ps)) & 255u, in);
+            narrow_add<8>(h8[D.passes - 1], (k >> (8 * (D.passes - 1))) & 255u, in);
         }
     }
-    if (tt == 0) return;  // nothing to histogram (uniform over the work-group)
-    // digit histograms: low digits are spread, the top one (cloud and high
-    // bits of q) takes few values
-    for (int ps = 0; ps < D.passes - 1; ps++)
-#pragma unroll
-        for (int m = 0; m < VR_ITEMS; m++) spread_add(h8[ps], (I.kv[m] >> (8 * ps)) & 255u, I.keep[m]);
-#pragma unroll
-    for (int m = 0; m < VR_ITEMS; m++)
-        narrow_add<8>(h8[D.passes - 1], (I.kv[m] >> (8 * (D.passes - 1))) & 255u, I.keep[m]);
+    if (!some) return;  // nothing to histogram
     __syncthreads();
     uint32_t *gh = hist_copy(&ctl->hist8[0][0][0], VR_HIST8_STRIDE);
     for (int x = t; x < D.passes * VR_RADIX; x += VR_BLOCK) {
@@ -425,7 +471,9 @@ void launch_select(const VrDev &D, hipStream_t s) {
     const dim3 grid((unsigned)(D.ntile_E > 0 ? D.ntile_E : 1));
     hipLaunchKernelGGL(k_sel_count, grid, dim3(VR_BLOCK), 0, s, D);
     hipLaunchKernelGGL(k_sel_scan, dim3(1), dim3(SCAN_BLOCK), 0, s, D);
-    hipLaunchKernelGGL(k_sel_write, grid, dim3(VR_BLOCK), 0, s, D);
+    // 2048 work-groups fill the chip; with more tiles each takes several, and
+    // adds its histogram to the build's once
+    hipLaunchKernelGGL(k_sel_write, dim3(grid.x < 2048u ? grid.x : 2048u), dim3(VR_BLOCK), 0, s, D);
 }
 
 // Sum the VR_HCOPY copies of a histogram set into copy 0, which is all its
@@ -929,18 +977,6 @@ void launch_edges(const VrDev &D, hipStream_t s) {
 #define SMALL_WORK (1 << 18)  // coordinate differences: above, the distances want more than one compute unit
 #define SMALL_CC 32
 
-// Pair number e < n (n - 1) / 2 of n <= 128 points.
-__device__ __forceinline__ void small_pair(int e, int n, int &i, int &j) {
-    auto start = [&](int x) { return x * (2 * n - x - 1) / 2; };
-    const float b = (float)(2 * n - 1), disc = b * b - 8.0f * (float)e;
-    int x = (int)((b - sqrtf(fmaxf(disc, 0.0f))) * 0.5f);
-    x = min(max(x, 0), n - 2);
-    while (x > 0 && start(x) > e) x--;
-    while (x < n - 2 && start(x + 1) <= e) x++;
-    i = x;
-    j = e - start(x) + x + 1;
-}
-
 template <typename T, bool MATRIX, int R>
 __global__ __launch_bounds__(SMALL_BLOCK) void k_small(VrDev D, VrCloud one, int scan_words) {
     __shared__ uint32_t sq[SMALL_BLOCK * R];  // distances; before, the staged coordinates
@@ -965,7 +1001,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(VrDev D, VrCloud one, int
 #pragma unroll
     for (int r = 0; r < R; r++) {
         int i, j;
-        small_pair(min(e0 + VR_WAVE * r, E - 1), n, i, j);
+        pair_of(min(e0 + VR_WAVE * r, E - 1), n, &i, &j);
         ij[r] = (uint32_t)(i << 8 | j);
     }
     if constexpr (MATRIX) {
@@ -997,13 +1033,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(VrDev D, VrCloud one, int
             for (int cx = 0; cx < cc; cx++) {
 #pragma unroll
                 for (int r = 0; r < R; r++) {
-                    long long df = (long long)xs[(int)(ij[r] >> 8) * ld + cx] - xs[(int)(ij[r] & 255u) * ld + cx];
-                    if (sizeof(T) == 4) {
-                        // |df| >= 2^16 makes df^2 >= 2^32 on its own
-                        over |= (df >= 65536 || df <= -65536) ? 1u : 0u;
-                        df = (df >= 65536 || df <= -65536) ? 0 : df;
-                    }
-                    acc[r] += (unsigned long long)(df * df);
+                    dist_add<T>(acc[r], xs[(int)(ij[r] >> 8) * ld + cx], xs[(int)(ij[r] & 255u) * ld + cx], over);
                 }
             }
         }

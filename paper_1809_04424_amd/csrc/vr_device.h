@@ -343,16 +343,20 @@ __host__ __device__ __forceinline__ long long row_start(long long i, long long n
 
 // Pair index -> (i, j): solve row_start(i) <= e < row_start(i+1) with a
 // floating-point guess corrected by exact integer comparisons.
-__device__ __forceinline__ void pair_of(long long e, long long n, int *pi, int *pj) {
-    double b = 2.0 * (double)n - 1.0;
-    double disc = b * b - 8.0 * (double)e;
-    long long i = (long long)((b - sqrt(disc > 0 ? disc : 0.0)) * 0.5);
-    if (i < 0) i = 0;
-    if (i > n - 2) i = n - 2;
-    while (i > 0 && row_start(i, n) > e) i--;
-    while (i < n - 2 && row_start(i + 1, n) <= e) i++;
-    *pi = (int)i;
-    *pj = (int)(e - row_start(i, n) + i + 1);
+// (n <= 8192, so every number here is below 2^28; the estimate in single
+// precision is a row off at most and the integers correct it.  In double
+// precision, a call for each 8 of 34 million pairs, the selection took 67 us
+// instead of 58.)
+__device__ __forceinline__ void pair_of(long long e64, long long n64, int *pi, int *pj) {
+    const int e = (int)e64, n = (int)n64;
+    auto start = [&](int i) { return (int)((uint32_t)i * (uint32_t)(2 * n - i - 1) / 2u); };
+    const float b = (float)(2 * n - 1), disc = fmaf(b, b, -8.0f * (float)e);
+    int i = (int)((b - __builtin_amdgcn_sqrtf(fmaxf(disc, 0.0f))) * 0.5f);
+    i = min(max(i, 0), n - 2);
+    while (i > 0 && start(i) > e) i--;
+    while (i < n - 2 && start(i + 1) <= e) i++;
+    *pi = i;
+    *pj = e - start(i) + i + 1;
 }
 
 // Store the phase-1 results into the host-pinned mailbox (system scope; the
