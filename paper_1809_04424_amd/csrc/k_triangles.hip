@@ -159,13 +159,27 @@ __global__ __launch_bounds__(VR_BLOCK) void k_rows(VrDev D) {
     uint32_t rr[S];
 #pragma unroll
     for (int s = 0; s < S; s++) rr[s] = row[min((w * per + s) * VR_WAVE + lane, n - 1)];
-    // candidates: entries with the tag and a kept rank; rr = rank within the cloud
+    // candidates: entries with the tag and a kept rank; rr = rank within the
+    // cloud.  Up to 1024 points each is looked up in the sorted edge list at
+    // once; beyond, after compaction, and nearly always all of them are
+    // edges, else each entry of the row is looked up by itself.  At once took
+    // 133 of 213 us on 8192 points with 270 neighbours each (160 us now) and
+    // 19 of 85 on 4000 with 400 (84), but on 777 points with 230 it is
+    // faster (24 us, 26).
+    auto endpoints = [&](uint32_t k) {
+        return (k < (uint32_t)v) ? ((k << 16) | (uint32_t)v) : (((uint32_t)v << 16) | k);
+    };
     unsigned long long mk[S];  // entries taken in each step (wave-uniform)
 #pragma unroll
     for (int s = 0; s < S; s++) {
         const int k = (w * per + s) * VR_WAVE + lane;
         const uint32_t lr = rr[s] & 0xFFFFFFu;
-        mk[s] = __builtin_amdgcn_ballot_w64(s < per && k < n && k != v && (rr[s] >> 24) == D.tag && (long long)lr < Kc);
+        bool in = s < per && k < n && k != v && (rr[s] >> 24) == D.tag && (long long)lr < Kc;
+        if constexpr (S <= 4) {
+            const uint32_t ij = D.se_ij[kb + (in ? lr : 0u)];  // kept base itself when not in (se_ij has room)
+            in = in && ij == endpoints((uint32_t)k);
+        }
+        mk[s] = __builtin_amdgcn_ballot_w64(in);
         rr[s] = lr;
     }
     // sort keys: local ranks in neighbour order (entry x = x-th neighbour
@@ -201,30 +215,17 @@ __global__ __launch_bounds__(VR_BLOCK) void k_rows(VrDev D) {
         }
         __syncthreads();
     };
-    auto endpoints = [&](uint32_t k) {
-        return (k < (uint32_t)v) ? ((k << 16) | (uint32_t)v) : (((uint32_t)v << 16) | k);
-    };
-    auto look_up = [&]() {
-#pragma unroll
-        for (int s = 0; s < S; s++) {
-            const bool in = (mk[s] >> lane) & 1ull;
-            const uint32_t ij = D.se_ij[kb + (in ? rr[s] : 0u)];  // kept base itself when not in (se_ij has room)
-            mk[s] = __builtin_amdgcn_ballot_w64(in && ij == endpoints((uint32_t)((w * per + s) * VR_WAVE + lane)));
-        }
-    };
-    // Beyond 2048 points the candidates are looked up in the sorted edge list
-    // after compaction, and nearly always all of them are edges; else each
-    // entry of the row is looked up by itself, as the steps are read.  The
-    // latter took 133 of 213 us on 8192 points with 270 neighbours each (160
-    // us now) and 19 of 85 on 4000 with 400 (84), but on 1088 points with all
-    // edges, few entries a lane and each one taken, it is faster (59, 61).
-    if constexpr (S <= 8) look_up();
     compact();
-    if constexpr (S > 8) {
+    if constexpr (S > 4) {
         bool bad = false;
         for (uint32_t x = threadIdx.x; x < deg; x += VR_BLOCK) bad |= D.se_ij[kb + lds[x]] != endpoints(pk[x]);
         if (__syncthreads_or(bad)) {
-            look_up();
+#pragma unroll
+            for (int s = 0; s < S; s++) {
+                const bool in = (mk[s] >> lane) & 1ull;
+                const uint32_t ij = D.se_ij[kb + (in ? rr[s] : 0u)];
+                mk[s] = __builtin_amdgcn_ballot_w64(in && ij == endpoints((uint32_t)((w * per + s) * VR_WAVE + lane)));
+            }
             compact();
         }
     }
