@@ -521,7 +521,7 @@ __device__ __forceinline__ void stage_pos(const VrDev &D, int n, uint16_t *Pa, u
         r0 = D.star_r[pc];
         b0 = D.star_nbr[pc];
     }
-    for (int k = threadIdx.x; k < n; k += EB) Pa[k] = 0xFFFF;
+    for (int x = threadIdx.x; x < (n + 7) / 8; x += EB) ((uint4 *)Pa)[x] = make_uint4(~0u, ~0u, ~0u, ~0u);
     __syncthreads();
     if (s0 + threadIdx.x < s1) Pa[b0] = (uint16_t)threadIdx.x;
     for (uint32_t p = s0 + threadIdx.x + EB; p < s1; p += EB) Pa[D.star_nbr[p]] = (uint16_t)(p - s0);
@@ -750,8 +750,17 @@ __global__ __launch_bounds__(VR_BLOCK) void k_scan(VrDev D, int S) {
             o += c[m];
         }
     };
-    if (direct) {
-        if ((int)blockIdx.x < ntiles) do_tile((int)blockIdx.x, cd);
+    // counts fewer than the launch provides for (a distance threshold keeps an
+    // unknown part of the pairs): a tile per work-group, without the ticket
+    // (1.1 million counts of 34 million pairs: 27 us with it, 17 without)
+    if (direct || ntiles <= (int)gridDim.x) {
+        if ((int)blockIdx.x >= ntiles) return;
+        if (!direct) {
+            const long long i0 = (long long)blockIdx.x * VR_TILE + (long long)t * VR_ITEMS;
+#pragma unroll
+            for (int m = 0; m < VR_ITEMS; m++) cd[m] = D.cnt[min(i0 + m, cap - 1)];
+        }
+        do_tile((int)blockIdx.x, cd);
         return;
     }
     for (;;) {
