@@ -48,7 +48,7 @@
 // On the circle and the mixture vr_pairs_dim1 took 28.2 and 36.6 ms as a
 // reduction of the full edge columns, a work-group each: one column's chain
 // of thousands of additions.  The chains here are a few additions long, and
-// it takes 0.15 and 1.7 ms.
+// it takes 0.15 and 1.4 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -367,15 +367,15 @@ __device__ __forceinline__ bool mo_connected(const MoBufs &B, uint32_t snap, uns
 
 // A wave takes MO_EB edges.  The vertices of L(r) come from the triangles
 // of value r.  Nearly every L(r) is connected by the edges of the last
-// snapshot before r, which a few rows of 8 W bytes show: those of its first
-// vertex and of three others, then four at a time (2.4 steps of one row and
-// then four at the mixture).  The others, and the edges before the first
-// snapshot, go to k_mo_split: one in 20 there.  k* is the nearest to both
-// ends of 32 vertices, four runs of eight spread over L(r): a run's ranks
-// lie in few cache lines (32 single vertices took 1015 us at the mixture,
-// bound by 7.4 GB of lines), and the nearest of all shortens little.  Two
-// edges at a time, their loads issued together.  With exact searches in the
-// rank matrix, a line per vertex and row, it took 3890 us.
+// snapshot before r, which a few rows of 8 W bytes show: those of four of
+// its vertices, then four at a time.  The others, and the edges before the
+// first snapshot, go to k_mo_split: one in 20 at the mixture.  k* is the
+// nearest to both ends of eight vertices, two runs of four: bound by the
+// lines it reads, and a run's ranks lie in few.  At the mixture 32 single
+// vertices took 1015 us, four runs of eight 790, these 478, and the
+// replacements are followed to their ends in the same 37 us (k_mo_expand).
+// Two edges at a time, their loads issued together.  With exact searches in
+// the rank matrix, a line per vertex and row, it took 3890 us.
 template <int NW>
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
     constexpr int U = 2;
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
         unsigned long long ks[U], k0[U], k1[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            ks[u] = B.key[f[u] + (int32_t)min(((lane >> 3) & 3u) * (m[u] / 4) + (lane & 7u), m[u] - 1)];
+            ks[u] = B.key[f[u] + (int32_t)min(((lane >> 2) & 1u) * (m[u] / 2) + (lane & 3u), m[u] - 1)];
             k0[u] = B.key[f[u] + (int32_t)min(lane, m[u] - 1)];
             k1[u] = B.key[f[u] + (int32_t)min(lane + VR_WAVE, m[u] - 1)];
         }
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
             const unsigned long long *rows = B.snap + (int64_t)((r[u] >> B.sb) - 1) * B.n * B.W;
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                v[u][i] = (uint32_t)__builtin_amdgcn_readlane((int)sk[u], 8 * i);
+                v[u][i] = (uint32_t)__builtin_amdgcn_readlane((int)sk[u], 2 * i);
 #pragma unroll
                 for (int j = 0; j < NW; j++)
                     row[u][i][j] = (int)lane + j * VR_WAVE < B.W ? rows[(int64_t)v[u][i] * B.W + j * VR_WAVE + lane] : 0ull;
