@@ -1,5 +1,5 @@
 """vr_pairs_dim0's spanning forest at the edges of its stretches (2n edges,
-then as many again as came before) and batches (2048 marked edges), and on
+then three times as many as came before) and batches (2048 marked edges), and on
 chains that join one edge a round.  Bit-exact against the oracle."""
 import numpy as np
 import pytest
