@@ -577,10 +577,10 @@ def _tetra(vr, torch, reps=10):
 
 
 def _pairs_dim0(vr, torch, reps=20, workload="circle1000"):
-    """Dimension-0 persistence pairs of a build: above 512 points a spanning
-    forest in rank order (one work-group: every edge's roots found in
-    parallel, at most n - 1 serial unions), timed with HIP events on the
-    current stream around each call; the rate is kept edges per second."""
+    """Dimension-0 persistence pairs of a build: a spanning forest in rank
+    order (stretches of edges filtered by all work-groups, joined by one),
+    timed with HIP events on the current stream around each call; the rate is
+    kept edges per second."""
     c = _workload(workload)
     pts = torch.from_numpy(c.points).to("cuda:0")
     r = vr.build(pts, c.thr)

@@ -1,5 +1,5 @@
-"""vr_column_order's ways of sorting a window with a segment longer than 256
-(buckets of values, 32-bit keys, 64-bit keys) at the lines between them.
+"""vr_column_order's ways of ranking a window (counting, buckets of values, 32-bit
+keys, 64-bit keys) at the lines between them.
 Bit-exact against the oracle."""
 import numpy as np
 import pytest
@@ -21,7 +21,7 @@ def _check(orc, lens, v, label):
     assert np.array_equal(z, orc.column_order(cp, v))
 
 
-@pytest.mark.parametrize("segments", [2, 127, 128, 129, 130, 1500])
+@pytest.mark.parametrize("segments", [2, 128, 255, 256, 257, 258, 1500])
 @pytest.mark.parametrize("hi", [2, 40, 2**17, 2**31 - 1])
 def test_segments_of_a_window(orc, segments, hi):
     """One segment of 257 or more and short ones around it, twice over."""
@@ -63,3 +63,14 @@ def test_extremes(orc, nnz):
     v = g.integers(-2**31, 2**31, nnz)
     v[g.choice(nnz, 20, replace=False)] = np.repeat([-2**31, 2**31 - 1], 10)
     _check(orc, [nnz], v, f"extremes {nnz}")
+
+
+@pytest.mark.parametrize("length", [1, 8, 23, 24, 25, 26, 255, 256, 257])
+@pytest.mark.parametrize("rest", [0, 3, 254, 255, 256, 900])
+def test_counted_and_not(orc, length, rest):
+    """The longest segment around the two counting limits, with up to and more
+    than 256 segments in the window; few values, so that many are equal."""
+    g = np.random.default_rng(length + rest)
+    lens = np.concatenate([g.integers(0, min(length, 4) + 1, rest), [length], g.integers(0, 3, rest // 2)])
+    v = g.integers(-3, 4, lens.sum()) if rest % 2 else g.integers(-2**31, 2**31, lens.sum())
+    _check(orc, lens, v, f"longest {length}, {len(lens)} columns")
