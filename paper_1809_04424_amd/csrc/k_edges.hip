@@ -533,12 +533,13 @@ struct SortLds {
 };
 
 // Sum of the counts of digit t before `tile`, for tiles that are all on the
-// device at once (DIRECT): the tiles come in groups of 16, whose last one
+// device at once: the tiles come in groups of 16, whose last one
 // adds up the others' counts and publishes the group's.  A tile reads at
 // most 15 counts and one per group before its own, instead of every count
 // back to the nearest inclusive one: at 400 to 600 tiles, all started
 // together, those reads bound the pass.
 #define SORT_GROUP 16
+#define SORT_GROUPS 64  // more tiles than this look back by groups
 __device__ __forceinline__ uint32_t sort_poll(const uint32_t *p, uint32_t s) {
     for (int nap = 1; (s >> 30) == VR_ST_NONE; nap = nap < 16 ? 2 * nap : 16) {
         backoff(nap);
@@ -569,8 +570,7 @@ __device__ __forceinline__ uint32_t sort_before(uint32_t *st, int tile, int stri
 // One tile of a pass: rank, publish the counts and look back, scatter.  kk:
 // the thread's keys (item `it` of wave w at 64 it + lane of the wave's 512);
 // gstart: where digit t starts.
-template <bool DIRECT>
-__device__ __forceinline__ void sort_tile(SortLds &L, int tile, const uint32_t (&kk)[VR_ITEMS], uint32_t Kc,
+__device__ __forceinline__ void sort_tile(bool groups, SortLds &L, int tile, const uint32_t (&kk)[VR_ITEMS], uint32_t Kc,
                                           long long cap, int shift, uint32_t gstart,
                                           const uint32_t *__restrict__ vsrc, uint32_t *__restrict__ kdst,
                                           uint32_t *__restrict__ vdst, uint32_t *st, uint32_t *st_next) {
@@ -613,7 +613,7 @@ __device__ __forceinline__ void sort_tile(SortLds &L, int tile, const uint32_t (
     const uint32_t tstart = block_excl_scan<uint32_t>(tc, L.sum, &ttot);
     L.tstart[t] = tstart;
     uint32_t prev = 0;
-    if (DIRECT) {
+    if (groups) {
         if (tile % SORT_GROUP != SORT_GROUP - 1) st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
         prev = sort_before(st + t, tile, VR_RADIX, tc);
     } else if (tile == 0) {
@@ -721,7 +721,10 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
         uint32_t kk[VR_ITEMS];
 #pragma unroll
         for (int it = 0; it < VR_ITEMS; it++) kk[it] = (a & 1) ? kB[it] : kA[it];
-        sort_tile<true>(L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+        // few tiles: their counts are read in one round either way, and the
+        // group's sum would be one more (16 tiles: 9.3 us a pass, 10.1)
+        sort_tile(ntiles > SORT_GROUPS, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st,
+                  st_next);
         return;
     }
     for (;;) {
@@ -733,7 +736,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
             const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
 #pragma unroll
             for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-            sort_tile<false>(L, tile, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+            sort_tile(false, L, tile, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
         }
         if ((int)gridDim.x >= ntiles) break;  // every tile went out in the first round of claims
     }
@@ -783,7 +786,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
         const long long base = (long long)blockIdx.x * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
 #pragma unroll
         for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-        sort_tile<true>(L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+        sort_tile(true, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
         return;
     }
     for (;;) {
