@@ -646,6 +646,9 @@ __global__ __launch_bounds__(EB) void k_tri_count(VrDev D, int parts) {
 // 39 and 35 us (1000-point circle), 510 and 491 (1088 points, all edges), 42
 // and 41 (777 points); eight split by partner: 30 us against 21 with five on
 // 300 points; 2000 points: 79 with three, 84 with one of 512 threads.  Count: 21 us with four or five, 25 with eight on the circle.
+// Large clouds of 384 or more neighbours a vertex, as K edges known on the
+// host tell (else -1), write with two: 4000 points with 400, 268 us with one,
+// 251; but 2500 with 250, 89 and 92, and 8192 with 270, 277 and 316.
 // Up to 128 points seven or eight are the same (7 and 8 us).
 static int enum_parts(long long V, long long groups, long long most) {
     const long long p = groups / (V > 0 ? V : 1);
@@ -653,7 +656,11 @@ static int enum_parts(long long V, long long groups, long long most) {
     return p < 1 ? 1 : (int)(p > most ? most : p);
 }
 int enum_parts_count(long long V) { return enum_parts(V, 4096, 4); }
-int enum_parts_write(long long V, long long C) { return enum_parts(V, enum_block(V, C) == 256 ? 6144 : 3072, 5); }
+int enum_parts_write(long long V, long long C, long long K) {
+    if (enum_block(V, C) == 256) return enum_parts(V, 6144, 5);
+    const int p = enum_parts(V, 3072, 5);
+    return p < 2 && K >= 192 * V ? 2 : p;
+}
 
 // Work-group size, the default: 256 threads for small clouds (more
 // work-groups in flight), 512 for large ones (fewer chunk barriers).  What

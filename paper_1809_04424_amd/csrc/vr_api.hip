@@ -596,7 +596,7 @@ int build_impl(const vr_request *reqs, long long count, hipStream_t s, Owner &ow
     }
     const Plan P = plan_of(S);
     Sched sch{enum_block(V, C), enum_parts_count(V), enum_pieces_count(V, Khost),
-              enum_block(V, C), enum_parts_write(V, C), enum_pieces_write()};
+              enum_block(V, C), enum_parts_write(V, C, Khost), enum_pieces_write()};
     {
         Tuning &tu = tuning();
         std::lock_guard<std::mutex> g(tu.mu);

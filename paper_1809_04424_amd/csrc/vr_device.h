@@ -515,7 +515,7 @@ bool small_applies(const VrDev &D);
 void launch_small(const VrDev &D, const VrCloud &one, int scan_words, hipStream_t s);
 void launch_rows(const VrDev &D, hipStream_t s);
 int enum_parts_count(long long V);
-int enum_parts_write(long long V, long long C);
+int enum_parts_write(long long V, long long C, long long K);
 int enum_block(long long V, long long C);
 int enum_pieces_count(long long V, long long K);
 int enum_pieces_write();
