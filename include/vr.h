@@ -441,8 +441,8 @@ VR_API int vr_tetra_write(const vr_result *res, const int64_t *offsets, int64_t 
  * a link that has cycles after filling in its triangles holds tetrahedra
  * whose columns are then reduced, on the few triangles that no such pair
  * takes.  Past that method's limits (64 triangles of one value, 64
- * independent edges in a link's core, 1024 such tetrahedra, 393216 triangles
- * if there are any) the pairs are found in the way of Section 2.2.2, on the
+ * independent edges in a link's core, 1024 such tetrahedra, 393216
+ * triangles) the pairs are found in the way of Section 2.2.2, on the
  * anti-transpose with clearing: the triangle columns go from the youngest
  * triangle to the oldest, a column's pivot is its oldest cofacet, apparent
  * pairs are taken at once and the other columns reduced in rounds.  The
@@ -456,9 +456,9 @@ VR_API int vr_tetra_write(const vr_result *res, const int64_t *offsets, int64_t 
  *               or -1: t is paired with an edge, or else starts a class of
  *               dimension 2 that never dies.
  * Synchronises `stream` once, and past the limits once more per round.
- * Scratch from the library's cache: 4 n^2 + 12 K + 6 T bytes plus 17 MiB;
- * past the limits 4 n^2 + 8 K + 60 T + 32 H bytes (H = 2T rounded up to a
- * power of two) plus 1 GiB, as vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a
+ * Scratch from the library's cache: 4 n^2 + 12 K + 6 T bytes plus 17 MiB
+ * (above 393216 triangles 4 n^2 + 8 K + 4 T); past the limits 56 T + 32 H
+ * bytes more (H = 2T rounded up to a power of two) and 1 GiB, as vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a
  * null argument, a result without tetrahedron keys, n > VR_MAX_POINTS or
  * T >= 2^31.  With no triangles nothing is written. */
 VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_edge, int64_t *tri_tet, void *stream);

@@ -2136,31 +2136,37 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_emit(const int32_t *ij, const l
     }
 }
 
-// The pairs of dimension 2 from the links of the edges; *done: whether the
-// limits of that method held.
-static int d2_links(const vr_result *res, const int32_t *tri_of_edge, long long *tri_tet, bool *done, hipStream_t s) {
+// What both ways of finding the pairs of dimension 2 need: the rank matrix,
+// the triangles paired with an edge and those of each value.
+struct D2Tables {
+    char *ws;
+    int32_t *R, *clr, *rng;
+    void *links;  // scratch of link_pairs_dim2
+};
+
+static int d2_tables(const vr_result *res, const int32_t *tri_of_edge, D2Tables *t, hipStream_t s) {
     const int64_t n = res->n_vertices, K = res->n_edges, T = res->n_triangles;
-    const unsigned long long *tri = (const unsigned long long *)res->tri_key;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t o = 0;
     const size_t o_R = o; o = up(o + 4 * (size_t)n * (size_t)n);
     const size_t o_clr = o; o = up(o + 8 * (size_t)((T + 1) / 2));
     const size_t o_rng = o; o = up(o + 8 * (size_t)K);
     const size_t o_lk = o; o += link_pairs_scratch(K, T);
-    char *ws = (char *)cache_get(o, s);
-    if (!ws) return VR_ENOMEM;
-    int32_t *R = (int32_t *)(ws + o_R), *clr = (int32_t *)(ws + o_clr), *rng = (int32_t *)(ws + o_rng);
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, R, n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, R, n, (const int32_t *)res->edge_ij, K, n);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for((T + 1) / 2)), dim3(PD_BLOCK), 0, s, (unsigned long long *)clr,
+    t->ws = (char *)cache_get(o, s);
+    if (!t->ws) return VR_ENOMEM;
+    t->R = (int32_t *)(t->ws + o_R);
+    t->clr = (int32_t *)(t->ws + o_clr);
+    t->rng = (int32_t *)(t->ws + o_rng);
+    t->links = t->ws + o_lk;
+    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, t->R, n);
+    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, t->R, n, (const int32_t *)res->edge_ij, K, n);
+    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for((T + 1) / 2)), dim3(PD_BLOCK), 0, s, (unsigned long long *)t->clr,
                        (T + 1) / 2);
-    hipLaunchKernelGGL(k_d2_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K, clr);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (unsigned long long *)rng, K);
-    hipLaunchKernelGGL(k_d2_range, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, tri, T, rng);
-    const int st = link_pairs_dim2(R, (const int32_t *)res->edge_ij, tri, (const long long *)res->tet_off, rng, clr, n,
-                                   K, T, tri_tet, ws + o_lk, done, s);
-    cache_put(ws, s);
-    return st;
+    hipLaunchKernelGGL(k_d2_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K, t->clr);
+    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (unsigned long long *)t->rng, K);
+    hipLaunchKernelGGL(k_d2_range, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, (const unsigned long long *)res->tri_key, T,
+                       t->rng);
+    return VR_OK;
 }
 
 extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_edge, int64_t *tri_tet, void *stream) {
@@ -2172,23 +2178,28 @@ extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_
         return VR_EINVAL;
     const hipStream_t s = (hipStream_t)stream;
     // from the links, within its limits (at most 64 triangles of one value,
-    // 1024 critical tetrahedra, of up to 393216 triangles); else, and for
-    // the few such results, by reducing the coboundaries below
+    // 1024 critical tetrahedra, 393216 triangles); else by reducing the
+    // coboundaries below
+    D2Tables tb{};
     {
+        int st = d2_tables(res, tri_of_edge, &tb, s);
+        if (st != VR_OK) return st;
         bool done = false;
-        const int st = d2_links(res, tri_of_edge, (long long *)tri_tet, &done, s);
-        if (st != VR_OK || done) return st;
+        st = link_pairs_dim2(tb.R, (const int32_t *)res->edge_ij, (const unsigned long long *)res->tri_key,
+                             (const long long *)res->tet_off, tb.rng, tb.clr, n, K, T, (long long *)tri_tet, tb.links,
+                             &done, s);
+        if (st != VR_OK || done) {
+            cache_put(tb.ws, s);
+            return st;
+        }
     }
     long long H = 2;
     while (H < 2 * T) H <<= 1;
     const int64_t nch = (T + BC_CHUNK - 1) / BC_CHUNK;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t o = 0;
-    const size_t o_R = o; o = up(o + 4 * (size_t)n * (size_t)n);
-    const size_t o_clr = o; o = up(o + 8 * (size_t)((T + 1) / 2));
     const size_t o_col = o; o = up(o + 4 * (size_t)T);
     const size_t o_piv = o; o = up(o + 8 * (size_t)T);
-    const size_t o_rng = o; o = up(o + 8 * (size_t)K);
     const size_t o_cnt = o; o = up(o + 8 * (size_t)nch);
     const size_t o_off = o; o = up(o + 8 * (size_t)(2 * nch + 2));
     const size_t o_rem = o; o = up(o + 4 * (size_t)T);
@@ -2202,9 +2213,12 @@ extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_
     const size_t o_h1 = o; o = up(o + 4 * (size_t)T);
     const size_t o_ctl = o; o = up(o + sizeof(RdCtl));
     char *ws = (char *)cache_get(o, s);
-    if (!ws) return VR_ENOMEM;
+    if (!ws) {
+        cache_put(tb.ws, s);
+        return VR_ENOMEM;
+    }
     RdBufs B{};
-    B.R = (const int32_t *)(ws + o_R);
+    B.R = tb.R;
     B.ij = (const int32_t *)res->edge_ij;
     B.app = nullptr;
     B.rem = (const int32_t *)(ws + o_rem);
@@ -2222,22 +2236,13 @@ extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_
     B.T = T;
     const long long *toff = (const long long *)res->tet_off;
     const unsigned long long *tkey = (const unsigned long long *)res->tet_key;
-    int32_t *clr = (int32_t *)(ws + o_clr), *col = (int32_t *)(ws + o_col), *cnt = (int32_t *)(ws + o_cnt);
+    int32_t *col = (int32_t *)(ws + o_col), *cnt = (int32_t *)(ws + o_cnt);
     long long *off = (long long *)(ws + o_off);
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, (int32_t *)(ws + o_R), n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (int32_t *)(ws + o_R), n,
-                       (const int32_t *)res->edge_ij, K, n);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for((T + 1) / 2)), dim3(PD_BLOCK), 0, s, (unsigned long long *)clr,
-                       (T + 1) / 2);
     hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(RD_SLOT_WORDS * H)), dim3(PD_BLOCK), 0, s, (unsigned long long *)B.tab,
                        RD_SLOT_WORDS * H);
-    hipLaunchKernelGGL(k_d2_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K, clr);
-    int32_t *rng = (int32_t *)(ws + o_rng);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (unsigned long long *)rng, K);
-    hipLaunchKernelGGL(k_d2_range, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, B.tri, T, rng);
     unsigned long long *piv = (unsigned long long *)(ws + o_piv);
     hipLaunchKernelGGL(k_d2_first, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(D2_BLOCK), 0, s, B,
-                       (const int32_t *)rng, (const int32_t *)clr, piv, col);
+                       (const int32_t *)tb.rng, (const int32_t *)tb.clr, piv, col);
     hipLaunchKernelGGL(k_d2_app, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, B, (const unsigned long long *)piv, toff,
                        tkey, (long long *)tri_tet);
     hipLaunchKernelGGL(k_d2_count, dim3((unsigned)nch), dim3(BC_CHUNK), 0, s, (const int32_t *)col, T, cnt);
@@ -2253,6 +2258,7 @@ extern "C" VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     cache_put(ws, s);
+    cache_put(tb.ws, s);
     if (st != VR_OK) return st;
     return e == hipSuccess ? VR_OK : VR_EHIP;
 }
