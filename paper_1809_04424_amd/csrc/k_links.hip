@@ -584,9 +584,10 @@ int link_pairs_dim2(const int32_t *R, const int32_t *ij, const unsigned long lon
                     const int32_t *rng, const int32_t *clr, int64_t n, int64_t K, int64_t T, long long *tri_tet,
                     void *scratch, bool *done, hipStream_t s) {
     *done = false;
-    // Beyond: no attempt.  A cloud so large has nearly always a critical
-    // tetrahedron, and the attempt was lost time before the reduction (a
-    // circle of 1000 points, 4995121 triangles: 4.85 ms with it, 4.4 without).
+    // Beyond: no attempt.  The columns' bits do not fit, and so many triangles
+    // mostly come with links of more than 64 vertices anyway; the attempt was
+    // lost time before the reduction (a circle of 1000 points, 4995121
+    // triangles, links of up to 123: 4.85 ms with it, 4.5 without).
     if (T > LK_MAXT) return VR_OK;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     char *ws = (char *)scratch;
