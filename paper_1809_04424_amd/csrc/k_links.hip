@@ -569,9 +569,7 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_reduce(LkBufs B) {
     }
 }
 
-__global__ void k_lk_init(LkCtl *ctl) {
-    if (threadIdx.x == 0) *ctl = LkCtl{0, 0, 0, 0};
-}
+static_assert(sizeof(LkCtl) == LINK_PAIRS_ZERO, "the control words start as zeros");
 
 size_t link_pairs_scratch(int64_t K, int64_t T) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -613,7 +611,6 @@ int link_pairs_dim2(const int32_t *R, const int32_t *ij, const unsigned long lon
     B.crit = (LkCrit *)part(sizeof(LkCrit) * LK_CRIT);
     B.pool = (uint32_t *)part(4 * (size_t)LK_POOL);
     const int64_t wg = (K + LK_WPB - 1) / LK_WPB;
-    hipLaunchKernelGGL(k_lk_init, dim3(1), dim3(VR_WAVE), 0, s, B.ctl);
     hipLaunchKernelGGL(k_lk_pairs, dim3((unsigned)(wg < 2048 ? wg : 2048)), dim3(LK_BLOCK), 0, s, B);  // fills the chip
     hipLaunchKernelGGL(k_lk_cycles, dim3(1024), dim3(VR_WAVE), 0, s, B);
     const size_t lds = 4 * (size_t)((T + 31) / 32);

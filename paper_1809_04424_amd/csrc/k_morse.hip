@@ -123,9 +123,13 @@ __device__ __forceinline__ uint32_t mo_before(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Bound by reading the keys once (8 T bytes); two keys a thread.
-__global__ __launch_bounds__(MO_BLOCK) void k_mo_range(MoBufs B) {
+// Bound by reading the keys once (8 T bytes); two keys a thread.  The edges
+// enter R here too: 14.7 -> 16.4 us for 99900 edges, whose launch of their own
+// took 4.8; for 799800 177 -> 201, and 22.
+__global__ __launch_bounds__(MO_BLOCK) void k_mo_range(MoBufs B, int32_t *R) {
     const int64_t np = (B.T + 1) / 2;
+    for (int64_t r = (int64_t)blockIdx.x * MO_BLOCK + threadIdx.x; r < B.K; r += (int64_t)gridDim.x * MO_BLOCK)
+        vr_rank_edge(R, B.ij, B.n, r);
     for (int64_t p = (int64_t)blockIdx.x * MO_BLOCK + threadIdx.x; p < np; p += (int64_t)gridDim.x * MO_BLOCK) {
         const int64_t t = 2 * p;
         const bool two = t + 1 < B.T;
@@ -951,8 +955,9 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_emit(MoBufs B) {
     }
 }
 
-__global__ __launch_bounds__(MO_BLOCK) void k_mo_init(MoBufs B) {
+__global__ __launch_bounds__(MO_BLOCK) void k_mo_init(MoBufs B, int32_t *R) {
     const int64_t x = (int64_t)blockIdx.x * MO_BLOCK + threadIdx.x;
+    for (int64_t i = x; i < B.n * B.n; i += (int64_t)gridDim.x * MO_BLOCK) R[i] = vr_rank_none((uint32_t)i, B.n);
     for (int64_t i = x; i < (int64_t)(sizeof(MoCtl) / 4); i += (int64_t)gridDim.x * MO_BLOCK) ((uint32_t *)B.ctl)[i] = 0u;
     for (int64_t r = x; r < B.K; r += (int64_t)gridDim.x * MO_BLOCK) {
         B.first[r] = -1;
@@ -965,7 +970,7 @@ static unsigned mo_grid(int64_t items, int64_t most) {
     return (unsigned)(g < 1 ? 1 : g > most ? most : g);
 }
 
-int morse_pairs_dim1(const int32_t *R, const int32_t *ij, const unsigned long long *key, const int32_t *e_low,
+int morse_pairs_dim1(int32_t *R, const int32_t *ij, const unsigned long long *key, const int32_t *e_low,
                      int64_t n, int64_t K, int64_t T, int32_t *tri_of_edge, bool *done, hipStream_t s) {
     *done = false;
     MoBufs B{};
@@ -1016,8 +1021,8 @@ int morse_pairs_dim1(const int32_t *R, const int32_t *ij, const unsigned long lo
     B.mask = B.blkm + nblk;
     B.ecnt = (uint32_t *)(ws + o_ecnt);
     const int64_t wg = (nblk + MO_WPB - 1) / MO_WPB;
-    hipLaunchKernelGGL(k_mo_init, dim3(mo_grid(K, 4096)), dim3(MO_BLOCK), 0, s, B);
-    hipLaunchKernelGGL(k_mo_range, dim3(mo_grid((T + 1) / 2, 65536)), dim3(MO_BLOCK), 0, s, B);
+    hipLaunchKernelGGL(k_mo_init, dim3(mo_grid(n * n > K ? n * n : K, 4096)), dim3(MO_BLOCK), 0, s, B, R);
+    hipLaunchKernelGGL(k_mo_range, dim3(mo_grid((T + 1) / 2, 65536)), dim3(MO_BLOCK), 0, s, B, R);
     hipLaunchKernelGGL(k_mo_snap, dim3((unsigned)n), dim3(MO_BLOCK), 8 * (size_t)S * (size_t)B.W, s, B, S);
     if (B.W > VR_WAVE) hipLaunchKernelGGL(k_mo_link<2>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);
     else hipLaunchKernelGGL(k_mo_link<1>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);

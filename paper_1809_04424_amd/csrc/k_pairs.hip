@@ -24,20 +24,14 @@
 
 #define PD_BLOCK 256
 #define PD_INF 0x7FFFFFFF
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_fill(int32_t *D, int64_t m) {
-    const int64_t ld = m;
-    for (int64_t x = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; x < ld * ld; x += (int64_t)gridDim.x * PD_BLOCK)
-        D[x] = (x / ld == x % ld) ? -1 : PD_INF;
+__global__ void __launch_bounds__(PD_BLOCK) k_pd_fill(int32_t *D, int64_t n) {
+    for (int64_t x = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; x < n * n; x += (int64_t)gridDim.x * PD_BLOCK)
+        D[x] = vr_rank_none((uint32_t)x, n);
 }
 
-__global__ void __launch_bounds__(PD_BLOCK) k_pd_edges(int32_t *D, int64_t ld, const int32_t *ij, int64_t K,
-                                                      int64_t n) {
-    for (int64_t r = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; r < K; r += (int64_t)gridDim.x * PD_BLOCK) {
-        const int64_t i = ij[2 * r], j = ij[2 * r + 1];
-        if (i < 0 || j < 0 || i >= n || j >= n) continue;  // never for a library result
-        D[i * ld + j] = (int32_t)r;
-        D[j * ld + i] = (int32_t)r;
-    }
+__global__ void __launch_bounds__(PD_BLOCK) k_pd_edges(int32_t *D, const int32_t *ij, int64_t K, int64_t n) {
+    for (int64_t r = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; r < K; r += (int64_t)gridDim.x * PD_BLOCK)
+        vr_rank_edge(D, ij, n, r);
 }
 
 __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K) {
@@ -564,7 +558,7 @@ extern "C" VR_API int vr_tetra_write(const vr_result *res, const int64_t *offset
     int32_t *D = (int32_t *)cache_get((size_t)n * (size_t)n * 4, s);
     if (!D) return VR_ENOMEM;
     hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, D, n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, n, (const int32_t *)res->edge_ij, K, n);
+    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, (const int32_t *)res->edge_ij, K, n);
     hipLaunchKernelGGL(k_tet_write, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
                        n, n, (const int32_t *)res->edge_ij, K, (const long long *)offsets, (long long)total,
                        (unsigned long long *)keys);
@@ -583,7 +577,7 @@ extern "C" VR_API int vr_tetra_counts(const vr_result *res, int64_t *counts, voi
     int32_t *D = (int32_t *)cache_get((size_t)n * (size_t)n * 4, s);
     if (!D) return VR_ENOMEM;
     hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, D, n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, n, (const int32_t *)res->edge_ij, K, n);
+    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, (const int32_t *)res->edge_ij, K, n);
     hipLaunchKernelGGL(k_tet_count, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
                        n, n, (const int32_t *)res->edge_ij, K, (long long *)counts);
     const hipError_t e = hipGetLastError();
@@ -1634,8 +1628,6 @@ extern "C" VR_API int vr_pairs_dim1(const vr_result *res, const int32_t *e_low, 
     // scratch, from the library's cache
     int32_t *R = (int32_t *)cache_get(4 * (size_t)n * (size_t)n, s);
     if (!R) return VR_ENOMEM;
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, R, n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, R, n, (const int32_t *)res->edge_ij, K, n);
     bool done = false;
     const int mst = morse_pairs_dim1(R, (const int32_t *)res->edge_ij, (const unsigned long long *)res->tri_key, e_low,
                                      n, K, T, tri_of_edge, &done, s);
@@ -1966,10 +1958,32 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_clear(const int32_t *toe, int64
 #define D2_BLOCK 256
 #define D2_WAVES (D2_BLOCK / 64)
 
-// rng[2r], rng[2r + 1] = the first and one past the last triangle of value r
-// (both 0 when there is none; rng zeroed before).
-__global__ void __launch_bounds__(PD_BLOCK) k_d2_range(const unsigned long long *tri, int64_t T, int32_t *rng) {
-    for (int64_t t = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; t < T; t += (int64_t)gridDim.x * PD_BLOCK) {
+// What d2_tables holds, in two launches of 2.8 and 3.9 us for a sphere of 400
+// points, each about what one of the seven launches of single parts took:
+// the rank matrix without its edges, and zeros; then
+//   - the edges into the rank matrix;
+//   - clr[t] = 1 for the triangles paired with an edge;
+//   - rng[2r], rng[2r + 1] = the first and one past the last triangle of
+//     value r (both 0 when there is none).
+__global__ void __launch_bounds__(PD_BLOCK) k_d2_fill(int32_t *R, int64_t n, int32_t *clr, int64_t T, int32_t *rng,
+                                                     int64_t K, uint32_t *links) {
+    const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, step = (int64_t)gridDim.x * PD_BLOCK;
+    if (links && x0 < LINK_PAIRS_ZERO / 4) links[x0] = 0u;
+    for (int64_t x = x0; x < n * n; x += step) R[x] = vr_rank_none((uint32_t)x, n);
+    for (int64_t x = x0; x < T; x += step) clr[x] = 0;
+    for (int64_t x = x0; x < 2 * K; x += step) rng[x] = 0;
+}
+
+__global__ void __launch_bounds__(PD_BLOCK) k_d2_tables(int32_t *R, int64_t n, const int32_t *ij, int64_t K,
+                                                       const int32_t *toe, const unsigned long long *tri, int64_t T,
+                                                       int32_t *clr, int32_t *rng) {
+    const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, step = (int64_t)gridDim.x * PD_BLOCK;
+    for (int64_t r = x0; r < K; r += step) {
+        vr_rank_edge(R, ij, n, r);
+        const int32_t t = toe[r];
+        if (t >= 0) clr[t] = 1;
+    }
+    for (int64_t t = x0; t < T; t += step) {
         const unsigned long long v = tri[t] >> 39;
         if (t == 0 || (tri[t - 1] >> 39) != v) rng[2 * v] = (int32_t)t;
         if (t == T - 1 || (tri[t + 1] >> 39) != v) rng[2 * v + 1] = (int32_t)(t + 1);
@@ -2158,14 +2172,12 @@ static int d2_tables(const vr_result *res, const int32_t *tri_of_edge, D2Tables 
     t->clr = (int32_t *)(t->ws + o_clr);
     t->rng = (int32_t *)(t->ws + o_rng);
     t->links = t->ws + o_lk;
-    hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, t->R, n);
-    hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, t->R, n, (const int32_t *)res->edge_ij, K, n);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for((T + 1) / 2)), dim3(PD_BLOCK), 0, s, (unsigned long long *)t->clr,
-                       (T + 1) / 2);
-    hipLaunchKernelGGL(k_d2_clear, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, tri_of_edge, K, t->clr);
-    hipLaunchKernelGGL(k_rd_zero, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, (unsigned long long *)t->rng, K);
-    hipLaunchKernelGGL(k_d2_range, dim3(grid_for(T)), dim3(PD_BLOCK), 0, s, (const unsigned long long *)res->tri_key, T,
-                       t->rng);
+    const int64_t most = n * n > T ? (n * n > 2 * K ? n * n : 2 * K) : (T > 2 * K ? T : 2 * K);
+    hipLaunchKernelGGL(k_d2_fill, dim3(grid_for(most)), dim3(PD_BLOCK), 0, s, t->R, n, t->clr, T, t->rng, K,
+                       link_pairs_scratch(K, T) ? (uint32_t *)t->links : nullptr);
+    hipLaunchKernelGGL(k_d2_tables, dim3(grid_for(K > T ? K : T)), dim3(PD_BLOCK), 0, s, t->R, n,
+                       (const int32_t *)res->edge_ij, K, tri_of_edge, (const unsigned long long *)res->tri_key, T,
+                       t->clr, t->rng);
     return VR_OK;
 }
 
