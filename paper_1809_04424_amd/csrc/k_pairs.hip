@@ -490,6 +490,90 @@ __global__ void __launch_bounds__(PD_BLOCK) k_tet_write(const int32_t *D, int64_
     }
 }
 
+// The same with one wave per edge: no barrier, and the writer needs no count
+// of its own, since a wave's places follow from off[r].  Bound by the latency
+// of the chain (rows, L, pairs), which more waves in flight hide.  It is taken
+// for up to TET_WAVE_N points (L's room), from 4096 edges on (with fewer all
+// edges run at once with four waves each), and where the links, T / K vertices
+// on average, are small enough for one wave.  us with four waves / with one
+// (a list takes its count too):
+//   T / K  K       count        list
+//    12    11975    23 /  19     52 /  22    (400 points; kernels alone)
+//     9    24975    76 /  58    229 / 141    (1000 points; calls from here on)
+//    18    11212    39 /  41    125 /  98    (300)
+//    49    11175    55 /  96    223 / 246    (150, all edges)
+//    50    99900   416 / 429   1628 / 1291   (1000)
+//    57   157132   739 / 1015  3159 / 2881   (1024)
+//   133    79800   735 / 1361  4618 / 5135   (400, all edges)
+// The count's rows of pairs leave few lanes idle in long links, so four waves
+// count those faster; a writer's longest link wants many other edges beside it.
+#define TET_WAVE_N 1024
+
+static bool tet_by_wave(bool write, int64_t n, int64_t K, int64_t T) {
+    if (n > TET_WAVE_N || K < 4096) return false;
+    if (!write) return T <= 16 * K;
+    return T <= 32 * K || (T <= 64 * K && K >= 65536);
+}
+
+static __device__ __forceinline__ uint32_t tet_common(const int32_t *D, int64_t ld, int n, int64_t i, int64_t j,
+                                                     int32_t r, uint16_t *L) {
+    const int lane = threadIdx.x & 63;
+    const int32_t *Di = D + i * ld, *Dj = D + j * ld;
+    uint32_t m = 0;
+#pragma unroll 4
+    for (int x0 = 0; x0 < n; x0 += 64) {
+        const int x = min(x0 + lane, n - 1);
+        const bool in = (Di[x] < r) & (Dj[x] < r) & (x0 + lane < n);
+        const unsigned long long b = __ballot(in);
+        if (in) L[m + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0))] =
+            (uint16_t)x;
+        m += (uint32_t)__popcll(b);
+    }
+    // the wave's own entries, read by its other lanes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    return m;
+}
+
+template <bool WRITE>
+__global__ void __launch_bounds__(PD_BLOCK) k_tet_wave(const int32_t *D, int64_t ld, int64_t n, const int32_t *ij,
+                                                      int64_t K, long long *counts, const long long *off,
+                                                      long long total, unsigned long long *keys) {
+    __shared__ uint16_t LL[PD_BLOCK / 64][TET_WAVE_N];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint16_t *L = LL[wv];
+    for (int64_t r = (int64_t)blockIdx.x * (PD_BLOCK / 64) + wv; r < K; r += (int64_t)gridDim.x * (PD_BLOCK / 64)) {
+        const int64_t i = ij[2 * r], j = ij[2 * r + 1];
+        const bool ok = i >= 0 && j >= 0 && i < n && j < n;  // always for a library result
+        const uint32_t m = ok ? tet_common(D, ld, (int)n, i, j, (int32_t)r, L) : 0u;
+        const uint32_t P = m ? m * (m - 1) / 2 : 0u, vi = (uint32_t)i, vj = (uint32_t)j;
+        uint32_t a = 0, b = 1;
+        if ((uint32_t)lane < P) tet_pair(lane, m, a, b);  // once; then 64 places per step
+        long long pos = WRITE ? off[r] : 0;
+        for (uint32_t q0 = 0; q0 < P; q0 += 64) {
+            const bool live = q0 + lane < P;  // a < b < m exactly then
+            const uint32_t k = live ? L[a] : 0u, l = live ? L[b] : 0u;
+            const bool in = live && D[(int64_t)k * ld + l] < r;
+            tet_advance(a, b, 64, m);
+            const unsigned long long bm = __ballot(in);
+            if (WRITE && in) {
+                const uint32_t lo = min(vi, k), hi = max(vj, l), u = max(vi, k), v = min(vj, l);  // as in k_tet_write
+                const unsigned long long packed = ((unsigned long long)lo << 39) | ((unsigned long long)min(u, v) << 26) |
+                                                  ((unsigned long long)max(u, v) << 13) | hi;
+                const long long at =
+                    pos + __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0));
+                if (at < total) *(ulonglong2 *)(keys + 2 * at) = make_ulonglong2((unsigned long long)r, packed);
+            }
+            pos += __popcll(bm);
+        }
+        if (!WRITE && lane == 0) counts[r] = pos;
+        // the next edge's entries overwrite L only after this one's reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 __global__ void __launch_bounds__(1024) k_tet_scan(long long *v, int64_t K) {
     // exclusive scan of v[0..K) into v[0..K], v[K] = total; one work-group
     __shared__ long long wt[16];
@@ -559,7 +643,12 @@ extern "C" VR_API int vr_tetra_write(const vr_result *res, const int64_t *offset
     if (!D) return VR_ENOMEM;
     hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, D, n);
     hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, (const int32_t *)res->edge_ij, K, n);
-    hipLaunchKernelGGL(k_tet_write, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
+    if (tet_by_wave(true, n, K, res->n_triangles))
+        hipLaunchKernelGGL(k_tet_wave<true>, dim3(grid_for(64 * K)), dim3(PD_BLOCK), 0, s, (const int32_t *)D, n, n,
+                           (const int32_t *)res->edge_ij, K, nullptr, (const long long *)offsets, (long long)total,
+                           (unsigned long long *)keys);
+    else
+        hipLaunchKernelGGL(k_tet_write, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
                        n, n, (const int32_t *)res->edge_ij, K, (const long long *)offsets, (long long)total,
                        (unsigned long long *)keys);
     const hipError_t e = hipGetLastError();
@@ -578,7 +667,11 @@ extern "C" VR_API int vr_tetra_counts(const vr_result *res, int64_t *counts, voi
     if (!D) return VR_ENOMEM;
     hipLaunchKernelGGL(k_pd_fill, dim3(grid_for(n * n)), dim3(PD_BLOCK), 0, s, D, n);
     hipLaunchKernelGGL(k_pd_edges, dim3(grid_for(K)), dim3(PD_BLOCK), 0, s, D, (const int32_t *)res->edge_ij, K, n);
-    hipLaunchKernelGGL(k_tet_count, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
+    if (tet_by_wave(false, n, K, res->n_triangles))
+        hipLaunchKernelGGL(k_tet_wave<false>, dim3(grid_for(64 * K)), dim3(PD_BLOCK), 0, s, (const int32_t *)D, n, n,
+                           (const int32_t *)res->edge_ij, K, (long long *)counts, nullptr, 0ll, nullptr);
+    else
+        hipLaunchKernelGGL(k_tet_count, dim3((unsigned)(K < 65536 ? K : 65536)), dim3(PD_BLOCK), 0, s, (const int32_t *)D,
                        n, n, (const int32_t *)res->edge_ij, K, (long long *)counts);
     const hipError_t e = hipGetLastError();
     cache_put(D, s);
