@@ -458,8 +458,9 @@ VR_API int vr_tetra_write(const vr_result *res, const int64_t *offsets, int64_t 
  * Synchronises `stream` once, and past the limits once more per round.
  * Scratch from the library's cache: 4 n^2 + 12 K + 6 T bytes plus 17 MiB
  * (above 393216 triangles 4 n^2 + 8 K + 4 T); past the limits 56 T + 32 H
- * bytes more (H = 2T rounded up to a power of two) and 1 GiB, as vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a
- * null argument, a result without tetrahedron keys, n > VR_MAX_POINTS or
+ * bytes more (H = 2T rounded up to a power of two) and 1 GiB, as
+ * vr_pairs_dim1.  VR_ENOMEM when the columns outgrow it; VR_EINVAL for a null
+ * argument, a result without tetrahedron keys, n > VR_MAX_POINTS or
  * T >= 2^31.  With no triangles nothing is written. */
 VR_API int vr_pairs_dim2(const vr_result *res, const int32_t *tri_of_edge, int64_t *tri_tet, void *stream);
 
