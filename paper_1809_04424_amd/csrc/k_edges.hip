@@ -137,9 +137,11 @@ __global__ __launch_bounds__(VR_BLOCK) void k_dist(VrDev D) {
         const int cc = min(CC, d - c0);
         __syncthreads();
         auto stage = [&](int r, int cx) {
-            const int gi = bi * DIST_TB + r, gj = bj * DIST_TB + r;
-            ((int32_t *)xi[cx])[16 * (r & 3) + (r >> 2)] = gi < n ? (int32_t)pts[(size_t)gi * d + c0 + cx] : 0;
-            xj[r][cx] = gj < n ? (int32_t)pts[(size_t)gj * d + c0 + cx] : 0;
+            // past the cloud its last point again: dist_add's range test then
+            // only ever sees differences of points of the cloud
+            const int gi = min(bi * DIST_TB + r, n - 1), gj = min(bj * DIST_TB + r, n - 1);
+            ((int32_t *)xi[cx])[16 * (r & 3) + (r >> 2)] = (int32_t)pts[(size_t)gi * d + c0 + cx];
+            xj[r][cx] = (int32_t)pts[(size_t)gj * d + c0 + cx];
         };
         if (cc == CC) {
             for (int x = threadIdx.x; x < DIST_TB * CC; x += VR_BLOCK) stage(x / CC, x % CC);
