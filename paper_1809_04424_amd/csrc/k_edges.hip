@@ -534,47 +534,73 @@ struct SortLds {
     uint32_t sum[VR_WAVES];
 };
 
-// Sum of the counts of digit t before `tile`, for tiles that are all on the
-// device at once: the tiles come in groups of 16, whose last one
+// Count of digit `digit` in `tiles` whole tiles of keys, by one thread: for a
+// look-back that has waited in vain (the lanes of a wave read the same keys).
+__device__ __forceinline__ uint32_t sort_recount(const uint32_t *__restrict__ keys, int tile, int tiles, int shift,
+                                                 uint32_t digit) {
+    const uint4 *k4 = (const uint4 *)(keys + (size_t)tile * VR_TILE);
+    uint32_t c = 0;
+#pragma unroll 2
+    for (int x = 0; x < tiles * (VR_TILE / 4); x++) {
+        const uint4 k = k4[x];
+        c += (uint32_t)(((k.x >> shift) & 255u) == digit) + (uint32_t)(((k.y >> shift) & 255u) == digit) +
+             (uint32_t)(((k.z >> shift) & 255u) == digit) + (uint32_t)(((k.w >> shift) & 255u) == digit);
+    }
+    return c;
+}
+
+// Sum of the counts of digit t before `tile`, for tiles that start
+// together: the tiles come in groups of 16, whose last one
 // adds up the others' counts and publishes the group's.  A tile reads at
 // most 15 counts and one per group before its own, instead of every count
 // back to the nearest inclusive one: at 400 to 600 tiles, all started
 // together, those reads bound the pass.
 #define SORT_GROUP 16
 #define SORT_GROUPS 64  // more tiles than this look back by groups
-__device__ __forceinline__ uint32_t sort_poll(const uint32_t *p, uint32_t s) {
-    for (int nap = 1; (s >> 30) == VR_ST_NONE; nap = nap < 16 ? 2 * nap : 16) {
-        backoff(nap);
-        s = st_load32(p);
-    }
-    return s & 0x3FFFFFFFu;
-}
-__device__ __forceinline__ uint32_t sort_before(uint32_t *st, int tile, int stride, uint32_t own) {
+template <typename F>
+__device__ __forceinline__ uint32_t sort_before(uint32_t *st, int tile, int stride, uint32_t own, F recount) {
     const int g = tile / SORT_GROUP, i = tile % SORT_GROUP;
+    int left = VR_PATIENCE;
     uint32_t s[SORT_GROUP], acc = 0;
 #pragma unroll
     for (int j = 0; j < SORT_GROUP; j++)
         s[j] = j < i ? st_load32(st + (size_t)(g * SORT_GROUP + j) * stride) : (VR_ST_AGG << 30);
 #pragma unroll
-    for (int j = 0; j < SORT_GROUP; j++) acc += sort_poll(st + (size_t)(g * SORT_GROUP + j) * stride, s[j]);
+    for (int j = 0; j < SORT_GROUP; j++)
+        acc += st_wait32(st + (size_t)(g * SORT_GROUP + j) * stride, s[j], left) & 0x3FFFFFFFu;
+    // the status at p, without waiting: `tiles` tiles from `first` on
+    auto take = [&](const uint32_t *p, int first, int tiles) {
+        const uint32_t x = st_load32(p);
+        return (x >> 30) == VR_ST_NONE ? recount(first, tiles) : x & 0x3FFFFFFFu;
+    };
+    if (left <= 0) {  // some may have been left out
+        acc = 0;
+        for (int j = g * SORT_GROUP; j < tile; j++) acc += take(st + (size_t)j * stride, j, 1);
+    }
     if (i == SORT_GROUP - 1) st_store32(st + (size_t)tile * stride, st_pack32(VR_ST_AGG, acc + own));
+    const uint32_t group = acc;
     for (int h = 0; h < g; h += SORT_GROUP) {
 #pragma unroll
         for (int j = 0; j < SORT_GROUP; j++)
             s[j] = h + j < g ? st_load32(st + (size_t)((h + j + 1) * SORT_GROUP - 1) * stride) : (VR_ST_AGG << 30);
 #pragma unroll
         for (int j = 0; j < SORT_GROUP; j++)
-            acc += sort_poll(st + (size_t)((h + j + 1) * SORT_GROUP - 1) * stride, s[j]);
+            acc += st_wait32(st + (size_t)((h + j + 1) * SORT_GROUP - 1) * stride, s[j], left) & 0x3FFFFFFFu;
+    }
+    if (left <= 0) {
+        acc = group;
+        for (int h = 0; h < g; h++)
+            acc += take(st + (size_t)((h + 1) * SORT_GROUP - 1) * stride, h * SORT_GROUP, SORT_GROUP);
     }
     return acc;
 }
 
 // One tile of a pass: rank, publish the counts and look back, scatter.  kk:
 // the thread's keys (item `it` of wave w at 64 it + lane of the wave's 512);
-// gstart: where digit t starts.
+// gstart: where digit t starts; ksrc: all keys.
 __device__ __forceinline__ void sort_tile(bool groups, SortLds &L, int tile, const uint32_t (&kk)[VR_ITEMS], uint32_t Kc,
                                           long long cap, int shift, uint32_t gstart,
-                                          const uint32_t *__restrict__ vsrc, uint32_t *__restrict__ kdst,
+                                          const uint32_t *__restrict__ ksrc, const uint32_t *__restrict__ vsrc, uint32_t *__restrict__ kdst,
                                           uint32_t *__restrict__ vdst, uint32_t *st, uint32_t *st_next) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int x = 0; x < VR_WAVES; x++) L.whist[x][t] = 0u;
@@ -615,14 +641,15 @@ __device__ __forceinline__ void sort_tile(bool groups, SortLds &L, int tile, con
     const uint32_t tstart = block_excl_scan<uint32_t>(tc, L.sum, &ttot);
     L.tstart[t] = tstart;
     uint32_t prev = 0;
+    auto recount = [&](int i, int tiles = 1) { return sort_recount(ksrc, i, tiles, shift, (uint32_t)t); };
     if (groups) {
         if (tile % SORT_GROUP != SORT_GROUP - 1) st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
-        prev = sort_before(st + t, tile, VR_RADIX, tc);
+        prev = sort_before(st + t, tile, VR_RADIX, tc, recount);
     } else if (tile == 0) {
         st_store32(st + t, st_pack32(VR_ST_INC, tc));
     } else {
         st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_AGG, tc));
-        prev = lookback32(st + t, tile, VR_RADIX);
+        prev = lookback32(st + t, tile, VR_RADIX, recount);
         st_store32(st + (size_t)tile * VR_RADIX + t, st_pack32(VR_ST_INC, prev + tc));
     }
     L.gpre[t] = gstart + prev;
@@ -725,7 +752,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
         for (int it = 0; it < VR_ITEMS; it++) kk[it] = (a & 1) ? kB[it] : kA[it];
         // few tiles: their counts are read in one round either way, and the
         // group's sum would be one more (16 tiles: 9.3 us a pass, 10.1)
-        sort_tile(ntiles > SORT_GROUPS, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st,
+        sort_tile(ntiles > SORT_GROUPS, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, ksrc, vsrc, kdst, vdst, st,
                   st_next);
         return;
     }
@@ -738,7 +765,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
             const long long base = (long long)tile * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
 #pragma unroll
             for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-            sort_tile(false, L, tile, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+            sort_tile(false, L, tile, kk, Kc, J.cap, shift, gstart, ksrc, vsrc, kdst, vdst, st, st_next);
         }
         if ((int)gridDim.x >= ntiles) break;  // every tile went out in the first round of claims
     }
@@ -752,7 +779,10 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass(SortJob J, int pass, int
 // for its first tile, publishes the inclusive prefixes of all S, and finally
 // re-reads, ranks and scatters each tile as the single-tile pass does.
 #define SORT_MULTI_MAX 16
-#define SORT_DIRECT 768  // work-groups of 43 KB of LDS that fit on the device at once (three a compute unit)
+// Tiles up to which each work-group takes the one of its own index: three a
+// compute unit, of the four that 38948 bytes of LDS leave room for.  Other
+// streams' kernels may take that room; waits end all the same (VR_PATIENCE).
+#define SORT_DIRECT 768
 __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pass) {
     __shared__ SortLds L;
     __shared__ uint32_t s_cnt[SORT_MULTI_MAX][VR_RADIX];  // digit counts of the claimed tiles
@@ -778,8 +808,8 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
     const uint32_t gstart = block_excl_scan<uint32_t>(J.hist[pass * VR_RADIX + t], L.sum, &tot);
 
     // few tiles after all (the launch knows only the pairs, of which a
-    // threshold keeps a part): a tile per work-group, all of which fit on the
-    // device at once, without tickets or a count of its own.  A pass, before
+    // threshold keeps a part): a tile per work-group, without tickets or a
+    // count of its own.  A pass, before
     // -> after (and with look-back to the nearest inclusive count): 0.8
     // million edges of 8 million pairs 19 -> 13 us (15), 1.1 of 34 million
     // 25 -> 16 (19), 1.2 of 9.7 million in 32 clouds 33 -> 20 (24).
@@ -788,7 +818,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_sort_pass_multi(SortJob J, int pas
         const long long base = (long long)blockIdx.x * VR_TILE + (long long)w * (VR_TILE / VR_WAVES);
 #pragma unroll
         for (int it = 0; it < VR_ITEMS; it++) kk[it] = ksrc[min(base + (long long)it * VR_WAVE + lane, J.cap - 1)];
-        sort_tile(true, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, vsrc, kdst, vdst, st, st_next);
+        sort_tile(true, L, (int)blockIdx.x, kk, Kc, J.cap, shift, gstart, ksrc, vsrc, kdst, vdst, st, st_next);
         return;
     }
     for (;;) {
@@ -907,9 +937,8 @@ void launch_sort_pass(const SortJob &J, long long max_tiles, int pass, hipStream
         hipLaunchKernelGGL(k_sort_pass_multi, dim3((unsigned)g), dim3(VR_BLOCK), 0, s, J, pass);
         return;
     }
-    // one tile per work-group (every tile's work-group is launched and all
-    // fit on the device at once), else one tile per claim: a tile's
-    // aggregate is published as soon as it is ranked
+    // one tile per work-group (every tile's work-group is launched), else one
+    // tile per claim: a tile's aggregate is published as soon as it is ranked
     hipLaunchKernelGGL(k_sort_pass, dim3((unsigned)g), dim3(VR_BLOCK), 0, s, J, pass, max_tiles <= 1024 ? 0 : 1);
 }
 

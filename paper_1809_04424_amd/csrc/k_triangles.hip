@@ -738,7 +738,16 @@ __global__ __launch_bounds__(VR_BLOCK) void k_scan(VrDev D, int S) {
                 if (t == 0) st_store64(D.st_scan, st_pack64(VR_ST_INC, tot));
             } else {
                 if (t == 0) st_store64(D.st_scan + tile, st_pack64(VR_ST_AGG, tot));
-                prefix = lookback64_wave(D.st_scan, tile);
+                prefix = lookback64_wave(D.st_scan, tile, [&](int i) {  // a whole tile's counts
+                    const uint4 *c4 = (const uint4 *)(D.cnt + (size_t)i * VR_TILE);
+                    unsigned long long v = 0;
+#pragma unroll 2
+                    for (int x = 0; x < VR_TILE / 4; x++) {
+                        const uint4 u = c4[x];
+                        v += (unsigned long long)u.x + u.y + u.z + u.w;
+                    }
+                    return v;
+                });
                 if (t == 0) st_store64(D.st_scan + tile, st_pack64(VR_ST_INC, prefix + tot));
             }
             if (t == 0) {
@@ -786,7 +795,7 @@ __global__ __launch_bounds__(VR_BLOCK) void k_scan(VrDev D, int S) {
 
 void launch_scan(const VrDev &D, long long Kmax, hipStream_t s) {
     long long g = (Kmax + VR_TILE - 1) / VR_TILE;
-    // every tile gets its own work-group when they all fit at once, else
+    // every tile gets its own work-group when there are few, else
     // 1024 work-groups claim one tile at a time
     const int S = (g <= 1024) ? 0 : 1;
     if (g > 1024) g = 1024;

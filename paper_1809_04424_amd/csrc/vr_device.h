@@ -178,8 +178,21 @@ __device__ __forceinline__ unsigned long long st_pack64(uint32_t state, unsigned
 
 // Decoupled look-back (Merrill and Garland, "Single-pass Parallel Prefix Scan
 // with Decoupled Look-back", 2016): sum the predecessors' aggregates back to
-// the nearest inclusive prefix.  Every predecessor tile was claimed earlier by
-// a running work-group through the ticket counter, so every wait ends.
+// the nearest inclusive prefix.
+//
+// Every wait ends.  Where tiles are claimed through a ticket counter, every
+// predecessor belongs to a running work-group.  Where a tile is the
+// work-group's own index it may not: a work-group is placed on the die
+// that its index names, and when several streams run such kernels at once,
+// waiting work-groups of one can hold all places of a die that the lowest
+// tile of another needs, and the other way round on a second die.  So a
+// look-back has VR_PATIENCE polls; then it starts again without waiting, and
+// where a status is still missing the caller's `recount` takes that tile's
+// aggregate from its input, which lies complete in memory (a predecessor is
+// never the last tile, so it is a whole one).  The budget costs nothing where
+// nothing waits long: 777 points 185 us a build without it, 183 with; 1 million
+// edges of 34 million pairs 862 and 862.  (Tickets instead would be one address
+// that up to a thousand work-groups add to, about 10 ns each.)
 //
 // Status words live in memory shared by all XCDs, so each poll is a round
 // trip of a microsecond or more: the rounds are made wide, with many
@@ -189,11 +202,26 @@ __device__ __forceinline__ unsigned long long st_pack64(uint32_t state, unsigned
 // A poll that finds a predecessor unpublished sleeps before polling again,
 // longer each time (nap x 128 cycles, up to about 1 us): thousands of waves
 // polling the same few lines back to back would slow every poll down.
+#ifndef VR_PATIENCE
+#define VR_PATIENCE 64  // about 100 us; a build alone on the device waits 20 at most
+#endif
 __device__ __forceinline__ void backoff(int nap) {
     for (int i = 0; i < nap; i++) __builtin_amdgcn_s_sleep(2);
 }
 
-// Per-digit form (one thread per digit): R predecessors per round.
+// The status s last read at p, polled until it is published or `left` polls
+// are used up.
+__device__ __forceinline__ uint32_t st_wait32(const uint32_t *p, uint32_t s, int &left) {
+    for (int nap = 1; (s >> 30) == VR_ST_NONE && left > 0; nap = nap < 16 ? 2 * nap : 16) {
+        backoff(nap);
+        s = st_load32(p);
+        left--;
+    }
+    return s;
+}
+
+// Per-digit form (one thread per digit) for claimed tiles: R predecessors
+// per round.
 template <int R = 16>
 __device__ __forceinline__ uint32_t lookback32(const uint32_t *st, int tile, int stride) {
     uint32_t acc = 0;
@@ -214,68 +242,98 @@ __device__ __forceinline__ uint32_t lookback32(const uint32_t *st, int tile, int
     return acc;
 }
 
-// Wave form (all 64 lanes of one wave, same `tile`): 64 R predecessors per
-// round, predecessor tile - 1 - (lane + 64 j) in slot j of a lane; returns
-// the exclusive prefix in every lane.  T is the status word (u32 with 30
-// value bits, or u64 with 62).
-template <typename T, int R = 4>
-__device__ __forceinline__ T lookback_wave(const T *st, int tile) {
-    constexpr int SH = 8 * (int)sizeof(T) - 2;
-    constexpr T VMASK = ((T)1 << SH) - 1;
+// The same for tiles numbered by work-group.  recount(i): tile i's aggregate.
+template <int R = 16, typename F>
+__device__ __forceinline__ uint32_t lookback32(const uint32_t *st, int tile, int stride, F recount) {
+    int left = VR_PATIENCE;
+    auto sum = [&]() -> uint32_t {
+        uint32_t acc = 0;
+        for (int t = tile - 1; t >= 0; t -= R) {
+            uint32_t s[R];
+#pragma unroll
+            for (int j = 0; j < R; j++)
+                s[j] = (t - j >= 0) ? st_load32(st + (size_t)(t - j) * stride) : (VR_ST_INC << 30);
+#pragma unroll
+            for (int j = 0; j < R; j++) {
+                s[j] = st_wait32(st + (size_t)(t - j) * stride, s[j], left);
+                acc += s[j] & 0x3FFFFFFFu;
+                if ((s[j] >> 30) == VR_ST_INC) return acc;
+            }
+        }
+        return acc;
+    };
+    uint32_t acc = sum();
+    if (left <= 0) {  // some may have been left out: again, without waiting
+        acc = 0;
+        for (int i = tile - 1; i >= 0; i--) {
+            const uint32_t s = st_load32(st + (size_t)i * stride);
+            acc += (s >> 30) == VR_ST_NONE ? recount(i) : s & 0x3FFFFFFFu;
+            if ((s >> 30) == VR_ST_INC) break;
+        }
+    }
+    return acc;
+}
+
+// Wave form (all 64 lanes of one wave, same `tile`) with 64-bit words of 62
+// value bits: 64 R predecessors per round, predecessor tile - 1 - (lane +
+// 64 j) in slot j of a lane; returns the exclusive prefix in every lane.
+template <int R = 4, typename F>
+__device__ __forceinline__ unsigned long long lookback64_wave(const unsigned long long *st, int tile, F recount) {
+    constexpr unsigned long long VMASK = (1ull << 62) - 1;
     const int lane = (int)lane_id();
-    T acc = 0;
-    for (int base = tile - 1; base >= 0; base -= VR_WAVE * R) {
-        T s[R];
+    unsigned long long acc = 0;
+    int base;
+    for (base = tile - 1; base >= 0; base -= VR_WAVE * R) {
+        unsigned long long s[R];
 #pragma unroll
         for (int j = 0; j < R; j++) {
             const int i = base - lane - VR_WAVE * j;
-            s[j] = (i >= 0) ? (sizeof(T) == 4 ? (T)st_load32((const uint32_t *)st + i)
-                                              : (T)st_load64((const unsigned long long *)st + i))
-                            : ((T)VR_ST_INC << SH);
+            s[j] = (i >= 0) ? st_load64(st + i) : ((unsigned long long)VR_ST_INC << 62);
         }
-        for (int nap = 1;; nap = nap < 16 ? 2 * nap : 16) {
+        for (int nap = 1, n = 0;; nap = nap < 16 ? 2 * nap : 16, n++) {
             // nearest inclusive prefix: the smallest distance d = lane + 64 j
             int dmin = VR_WAVE * R;
 #pragma unroll
             for (int j = R - 1; j >= 0; j--) {
-                const unsigned long long inc = ballot64((s[j] >> SH) == VR_ST_INC);
+                const unsigned long long inc = ballot64((s[j] >> 62) == VR_ST_INC);
                 if (inc) dmin = VR_WAVE * j + __ffsll((long long)inc) - 1;
             }
             bool wait = false;
 #pragma unroll
             for (int j = 0; j < R; j++) {
                 const bool need = VR_WAVE * j + lane <= dmin;
-                wait |= ballot64(need && (s[j] >> SH) == VR_ST_NONE) != 0ull;
+                wait |= ballot64(need && (s[j] >> 62) == VR_ST_NONE) != 0ull;
             }
             if (wait) {
+                if (__builtin_expect(n == VR_PATIENCE, 0)) goto take;
                 backoff(nap);
 #pragma unroll
                 for (int j = 0; j < R; j++) {
                     const int i = base - lane - VR_WAVE * j;
-                    if (i >= 0 && (s[j] >> SH) == VR_ST_NONE)
-                        s[j] = sizeof(T) == 4 ? (T)st_load32((const uint32_t *)st + i)
-                                              : (T)st_load64((const unsigned long long *)st + i);
+                    if (i >= 0 && (s[j] >> 62) == VR_ST_NONE) s[j] = st_load64(st + i);
                 }
                 continue;
             }
-            T v = 0;
+            unsigned long long v = 0;
 #pragma unroll
             for (int j = 0; j < R; j++)
                 if (VR_WAVE * j + lane <= dmin) v += s[j] & VMASK;
-            acc += wave_sum<T>(v);
+            acc += wave_sum<unsigned long long>(v);
             if (dmin < VR_WAVE * R) return acc;
             break;
         }
     }
     return acc;
-}
-
-__device__ __forceinline__ uint32_t lookback32_wave(const uint32_t *st, int tile) {
-    return lookback_wave<uint32_t>(st, tile);
-}
-
-__device__ __forceinline__ unsigned long long lookback64_wave(const unsigned long long *st, int tile) {
-    return lookback_wave<unsigned long long>(st, tile);
+take:  // 64 tiles at a time, without waiting
+    for (; base >= 0; base -= VR_WAVE) {
+        const int i = base - lane;
+        const unsigned long long x = i >= 0 ? st_load64(st + i) : st_pack64(VR_ST_INC, 0ull);
+        const unsigned long long inc = ballot64((x >> 62) == VR_ST_INC);
+        const int dmin = inc ? __ffsll((long long)inc) - 1 : VR_WAVE;
+        acc += wave_sum<unsigned long long>(lane > dmin ? 0ull : (x >> 62) == VR_ST_NONE ? recount(i) : x & VMASK);
+        if (inc) break;
+    }
+    return acc;
 }
 
 // Claim the next S consecutive tiles of a persistent loop with one atomic;
