@@ -322,8 +322,9 @@ VR_API int vr_column_order_noalloc(const int64_t *colptr, int64_t ncols, const i
  *         or -1 for the smallest vertex of each final component (an
  *         infinite bar).
  * Enqueued on `stream`: a spanning forest in rank order (at most n - 1
- * unions); scratch of 4 n + K / 8 bytes and a few hundred more from the
- * library's cache.  VR_EINVAL for a null argument or n > VR_MAX_POINTS. */
+ * unions).  No scratch: the outputs hold its tables between launches, so the
+ * call allocates nothing and may be captured into a graph.  VR_EINVAL for a
+ * null argument or n > VR_MAX_POINTS. */
 VR_API int vr_pairs_dim0(const vr_result *res, int32_t *e_low, int32_t *death, void *stream);
 
 /* Apparent persistence pairs in dimension 1 (Section 2.2.1, Alg. 1 on the

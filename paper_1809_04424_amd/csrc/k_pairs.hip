@@ -65,22 +65,25 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K
 #define PF_BATCH (2 * PF_BLOCK)
 #define PF_ROUNDS 24
 
+// No memory but the outputs: between launches the tables lie in e_low, in the
+// stretch [e0, e1) to come, whose entries are all still to be written.  Its
+// first entries hold the component of each vertex (its smallest vertex, two
+// in a word) and the number of unions made, its last ones the marks, 32 in a
+// word.  A word of marks lies at an edge whose own mark is in that word or
+// a later one, so k_pf_join, which clears words as it reads them, never
+// writes a pair over one that it has still to read.  For at least n edges the two
+// do not meet from 6 points on; with fewer all edges are one stretch.
 struct PfBufs {
     const int32_t *ij;
     int64_t K, n;
-    int32_t *root;              // n: the component of each vertex, its smallest vertex
-    unsigned long long *mark;   // a bit per edge of the stretch
-    int32_t *joined;            // unions made
     int32_t *e_low, *death;
 };
+static __host__ __device__ __forceinline__ int64_t pf_head(int64_t n) { return (n + 1) / 2; }
+static __host__ __device__ __forceinline__ int64_t pf_marks(int64_t e0, int64_t e1) { return (e1 - e0 + 31) / 32; }
 
 __global__ void __launch_bounds__(PD_BLOCK) k_pf_init(PfBufs P) {
     const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, st = (int64_t)gridDim.x * PD_BLOCK;
-    if (x0 == 0) *P.joined = 0;
-    for (int64_t v = x0; v < P.n; v += st) {
-        P.root[v] = (int32_t)v;
-        P.death[v] = -1;
-    }
+    for (int64_t v = x0; v < P.n; v += st) P.death[v] = -1;
     for (int64_t r = x0; r < P.K; r += st) P.e_low[r] = -1;
 }
 
@@ -91,29 +94,48 @@ static __device__ __forceinline__ bool pf_ends(const PfBufs &P, int64_t e, int32
     return a >= 0 && b >= 0 && a < P.n && b < P.n;
 }
 
-// mark: the edges of [e0, e1) whose ends lie in different components.
+// marks: the edges of [e0, e1) whose ends lie in different components.
 __global__ void __launch_bounds__(PD_BLOCK) k_pf_filter(PfBufs P, int64_t e0, int64_t e1) {
-    if (*P.joined >= P.n - 1) return;  // k_pf_join then reads no mark
-    const int64_t len = (e1 - e0 + 63) & ~(int64_t)63;
+    const int32_t *head = P.e_low + e0;
+    if (head[pf_head(P.n)] >= P.n - 1) return;  // k_pf_join then reads no mark
+    const int64_t len = (e1 - e0 + 63) & ~(int64_t)63, words = pf_marks(e0, e1);
+    int32_t *marks = P.e_low + (e1 - words);
+    auto root = [&](int32_t v) { return ((uint32_t)head[v >> 1] >> (16 * (v & 1))) & 0xFFFFu; };
     for (int64_t x = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x; x < len; x += (int64_t)gridDim.x * PD_BLOCK) {
         int32_t a, b;
-        const bool on = e0 + x < e1 && pf_ends(P, e0 + x, a, b) && P.root[a] != P.root[b];
+        const bool on = e0 + x < e1 && pf_ends(P, e0 + x, a, b) && root(a) != root(b);
         const unsigned long long m = __ballot(on);
-        if ((threadIdx.x & 63) == 0) P.mark[x >> 6] = m;
+        if ((threadIdx.x & 31) == 0 && (x >> 5) < words) marks[x >> 5] = (int32_t)(uint32_t)(m >> (threadIdx.x & 32));
     }
 }
 
-// The marked edges of [e0, e1) (all of them when mark is null).
-__global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int64_t e1, const unsigned long long *mark) {
+// The marked edges of [e0, e1) (all of the first stretch).
+__global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int64_t e1) {
     __shared__ uint16_t par[VR_MAX_POINTS];
     __shared__ uint32_t touch[VR_MAX_POINTS];  // the first edge of the batch at each root
     __shared__ uint32_t cand[PF_BATCH];        // the batch: edges - e0
     __shared__ uint32_t wc[PF_BLOCK / 64];
     __shared__ uint32_t s_n, s_next, s_left, s_joined;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const uint32_t joined0 = (uint32_t)*P.joined;
-    if (joined0 >= (uint32_t)(P.n - 1)) return;
-    for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)P.root[v];
+    const int64_t nh = pf_head(P.n), nm = pf_marks(e0, e1);
+    int32_t *head = P.e_low + e0, *marks = P.e_low + (e1 - nm);
+    const uint32_t joined0 = e0 ? (uint32_t)head[nh] : 0u;
+    if (e0)
+        for (int64_t x = t; x < nh; x += PF_BLOCK) {
+            const uint32_t w = (uint32_t)head[x];
+            par[2 * x] = (uint16_t)w;
+            if (2 * x + 1 < P.n) par[2 * x + 1] = (uint16_t)(w >> 16);
+        }
+    else
+        for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)v;
+    __syncthreads();
+    const bool done = joined0 >= (uint32_t)(P.n - 1);  // then the stretch holds the number alone
+    if (e0)
+        for (int64_t x = t; x <= nh; x += PF_BLOCK) head[x] = -1;
+    if (done) {
+        if (t == 0 && e1 < P.K) P.e_low[e1 + nh] = (int32_t)joined0;
+        return;
+    }
     if (t == 0) s_joined = joined0;
     const uint32_t words = (uint32_t)((e1 - e0 + 63) / 64);
     // roots, shortening the paths (an entry only ever moves up its own path)
@@ -138,8 +160,10 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
         const uint32_t w = w0 + (uint32_t)t;
         unsigned long long m = 0;
         if (w < words) {
-            if (mark) m = mark[w];
-            else m = e1 - e0 - 64 * (int64_t)w >= 64 ? ~0ull : (1ull << (e1 - e0 - 64 * (int64_t)w)) - 1;
+            if (e0) {
+                m = (uint32_t)marks[2 * w];
+                if (2 * (int64_t)w + 1 < nm) m |= (unsigned long long)(uint32_t)marks[2 * w + 1] << 32;
+            } else m = e1 - e0 - 64 * (int64_t)w >= 64 ? ~0ull : (1ull << (e1 - e0 - 64 * (int64_t)w)) - 1;
         }
         const uint32_t c = (uint32_t)__popcll(m);
         uint32_t inc = c;
@@ -161,6 +185,10 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
         const unsigned long long fm = __ballot(fits);
         if (lane == 0 && fm) atomicMax(&s_next, w0 + (uint32_t)(64 * wv + 64 - __clzll((long long)fm)));
         if (fits) {
+            if (e0 && w < words) {  // read: no pairs there yet
+                marks[2 * w] = -1;
+                if (2 * (int64_t)w + 1 < nm) marks[2 * w + 1] = -1;
+            }
             if (c) atomicMax(&s_n, inc);
             uint32_t at = inc - c;
             for (; m; m &= m - 1) cand[at++] = 64 * w + (uint32_t)__builtin_ctzll(m);
@@ -246,8 +274,14 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
         for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)find((uint32_t)v);
         __syncthreads();
     }
-    for (int64_t v = t; v < P.n; v += PF_BLOCK) P.root[v] = (int32_t)find((uint32_t)v);
-    if (t == 0) *P.joined = (int32_t)s_joined;
+    if (e0)  // the marks that were not needed
+        for (int64_t x = 2 * (int64_t)w0 + t; x < nm; x += PF_BLOCK) marks[x] = -1;
+    if (e1 == P.K) return;
+    if (s_joined < (uint32_t)(P.n - 1))
+        for (int64_t x = t; x < nh; x += PF_BLOCK)
+            P.e_low[e1 + x] = (int32_t)(find((uint32_t)(2 * x)) |
+                                        (2 * x + 1 < P.n ? find((uint32_t)(2 * x + 1)) << 16 : 0u));
+    if (t == 0) P.e_low[e1 + nh] = (int32_t)s_joined;
 }
 static_assert(PF_BATCH <= VR_MAX_POINTS, "touch marks what is left of a batch");
 
@@ -279,28 +313,21 @@ extern "C" VR_API int vr_pairs_dim0(const vr_result *res, int32_t *e_low, int32_
     if ((K > 0 && (!e_low || !res->edge_ij)) || (n > 0 && !death)) return VR_EINVAL;
     if (n == 0) return VR_OK;
     const hipStream_t s = (hipStream_t)stream;
-    PfBufs P{(const int32_t *)res->edge_ij, K, n, nullptr, nullptr, nullptr, e_low, death};
     // stretches: [0, 2n), then three times as many edges as came before (as
     // many as came before: the same time joining, 36 us of filters instead of
-    // 21 at the mixture, 21 instead of 13 at the circle); marks of the longest
-    const size_t up_n = (4 * (size_t)n + 255) & ~(size_t)255;
-    char *ws = (char *)cache_get(up_n + 256 + 8 * (size_t)(K / 64 + 1), s);
-    if (!ws) return VR_ENOMEM;
-    P.root = (int32_t *)ws;
-    P.joined = (int32_t *)(ws + up_n);
-    P.mark = (unsigned long long *)(ws + up_n + 256);
+    // 21 at the mixture, 21 instead of 13 at the circle); none of fewer than n
+    // edges is left for last
+    PfBufs P{(const int32_t *)res->edge_ij, K, n, e_low, death};
     hipLaunchKernelGGL(k_pf_init, dim3(grid_for(n > K ? n : K)), dim3(PD_BLOCK), 0, s, P);
     for (int64_t e0 = 0; e0 < K;) {
-        const int64_t e1 = e0 ? (4 * e0 < K ? 4 * e0 : K) : (2 * n < K ? 2 * n : K);
+        int64_t e1 = e0 ? 4 * e0 : 2 * n;
+        if (n < 6 || K - e1 < n) e1 = K;
         if (e0)
             hipLaunchKernelGGL(k_pf_filter, dim3(grid_for(e1 - e0)), dim3(PD_BLOCK), 0, s, P, e0, e1);
-        hipLaunchKernelGGL(k_pf_join, dim3(1), dim3(PF_BLOCK), 0, s, P, e0, e1,
-                           e0 ? (const unsigned long long *)P.mark : (const unsigned long long *)nullptr);
+        hipLaunchKernelGGL(k_pf_join, dim3(1), dim3(PF_BLOCK), 0, s, P, e0, e1);
         e0 = e1;
     }
-    const hipError_t e = hipGetLastError();
-    cache_put(ws, s);
-    return e == hipSuccess ? VR_OK : VR_EHIP;
+    return hipGetLastError() == hipSuccess ? VR_OK : VR_EHIP;
 }
 
 extern "C" VR_API int vr_pairs_dim1_apparent(const vr_result *res, int32_t *tri_of_edge, void *stream) {
