@@ -54,9 +54,17 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K
 // become smaller, so the larger root is the one that dies.  Each round joins
 // every such edge (the oldest left is one), mostly half of what is left and
 // all that lead to one large component with a small root; joining only edges
-// first at both ends left most of the mixture's to the one thread.  After
-// PF_ROUNDS rounds one thread takes what is left in order (chains of edges
-// in rank order towards smaller vertices settle one edge a round).
+// first at both ends left most of the mixture's to the one thread.  Chains
+// of edges in rank order towards smaller vertices settle one edge a round.
+// When the first PF_SLOW rounds settle fewer edges than one wave settles in
+// their time (PF_FEW: a round takes 1.2 us, an edge 0.085), and after
+// PF_ROUNDS in any case, one wave takes the rest in order.  (A
+// slow round later on says little: a component that others wait for can
+// hold most edges up for some rounds, and ending the rounds there took 306 us
+// instead of 193 on 8192 points.  Paths of 64, 1025 and 8192 vertices whose
+// edges come from the far end: 30, 187 and 1460 us with one thread for all
+// unions, 71, 399 and 2831 with PF_ROUNDS in any case and one thread for the
+// rest, now 21, 101 and 725.)
 //
 // One work-group looking up every edge and one thread joining took 2270 us
 // at the 4000-point mixture and 420 us at the 1000-point circle, and the
@@ -64,6 +72,8 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K
 #define PF_BLOCK 1024
 #define PF_BATCH (2 * PF_BLOCK)
 #define PF_ROUNDS 24
+#define PF_SLOW 3
+#define PF_FEW 40
 
 // No memory but the outputs: between launches the tables lie in e_low, in the
 // stretch [e0, e1) to come, whose entries are all still to be written.  Its
@@ -194,8 +204,8 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
             for (; m; m &= m - 1) cand[at++] = 64 * w + (uint32_t)__builtin_ctzll(m);
         }
         __syncthreads();
-        const uint32_t nc = s_n;
-        w0 = s_next;
+        const uint32_t nc = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_n);
+        w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next);
         // the thread's edges of the batch: t and PF_BLOCK + t
         uint32_t A[2], Bv[2];
         bool live[2];
@@ -242,30 +252,41 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
             if (won) atomicAdd(&s_joined, won);
             if (left) atomicAdd(&s_left, left);
             __syncthreads();
-            const uint32_t rest = s_left;
+            const uint32_t rest = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_left);
             __syncthreads();  // s_left is cleared by the next round
             if (rest == 0) break;
-            if (round + 1 < PF_ROUNDS) continue;
-            // what is left, in order: marked in touch, by one thread
+            if (round + 1 < PF_ROUNDS && !(round + 1 == PF_SLOW && rest + PF_FEW > nc)) continue;
+            // what is left, in order, by one wave: 64 edges' roots at a time,
+            // in registers, where a union's effect on the others is one
+            // compare each; touch holds the roots so far
 #pragma unroll
-            for (int u = 0; u < 2; u++) touch[u * PF_BLOCK + t] = live[u] ? 1u : 0u;
+            for (int u = 0; u < 2; u++) touch[u * PF_BLOCK + t] = live[u] ? 1u << 31 | A[u] << 13 | Bv[u] : 0u;
             __syncthreads();
-            if (t == 0) {
+            if (wv == 0) {
                 uint32_t k = 0;
-                for (uint32_t i = 0; i < nc; i++) {
-                    if (!touch[i]) continue;
-                    const int64_t f = e0 + cand[i];
-                    int32_t ea, eb;
-                    (void)pf_ends(P, f, ea, eb);
-                    uint32_t a = (uint32_t)ea, b = (uint32_t)eb;
-                    while (par[a] != a) a = par[a] = par[par[a]];
-                    while (par[b] != b) b = par[b] = par[par[b]];
-                    if (a != b) {
-                        join(a, b, f);
-                        k++;
+                for (uint32_t i0 = 0; i0 < nc; i0 += 64) {
+                    const uint32_t e = touch[i0 + lane];
+                    if (!__ballot(e != 0)) continue;
+                    uint32_t a = find((e >> 13) & 0x1FFFu), b = find(e & 0x1FFFu), lo = 0, hi = 0;
+                    for (unsigned long long m = __ballot(e != 0 && a != b); m; m &= m - 1) {
+                        const int x = __builtin_ctzll(m);
+                        const uint32_t ra = (uint32_t)__builtin_amdgcn_readlane((int)a, x);
+                        const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)b, x);
+                        if (ra == rb) continue;
+                        const uint32_t l = min(ra, rb), h = max(ra, rb);
+                        a = a == h ? l : a;
+                        b = b == h ? l : b;
+                        lo = lane == x ? l : lo;
+                        hi = lane == x ? h : hi;
                     }
+                    if (hi) join(lo, hi, e0 + cand[i0 + lane]);
+                    k += (uint32_t)__popcll(__ballot(hi != 0));
+                    // the next 64 look their roots up after these unions
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                 }
-                s_joined += k;
+                if (lane == 0) s_joined += k;
             }
             break;
         }
@@ -283,7 +304,7 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
                                         (2 * x + 1 < P.n ? find((uint32_t)(2 * x + 1)) << 16 : 0u));
     if (t == 0) P.e_low[e1 + nh] = (int32_t)s_joined;
 }
-static_assert(PF_BATCH <= VR_MAX_POINTS, "touch marks what is left of a batch");
+static_assert(PF_BATCH <= VR_MAX_POINTS && VR_MAX_POINTS <= 1 << 13, "touch holds the roots of what is left of a batch");
 
 // Dimension 1, apparent pairs.  Triangles of value r are the cofacets of
 // edge r whose other two edges are older, and the writer emits them
