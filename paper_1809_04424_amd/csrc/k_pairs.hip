@@ -21,6 +21,7 @@
 #include "vr.h"
 #include "vr_cache.h"
 #include "vr_morse.h"
+#include "vr_tetra.h"
 
 #define PD_BLOCK 256
 #define PD_INF 0x7FFFFFFF
@@ -538,31 +539,7 @@ __global__ void __launch_bounds__(PD_BLOCK) k_tet_write(const int32_t *D, int64_
     }
 }
 
-// The same with one wave per edge: no barrier, and the writer needs no count
-// of its own, since a wave's places follow from off[r].  Bound by the latency
-// of the chain (rows, L, pairs), which more waves in flight hide.  It is taken
-// for up to TET_WAVE_N points (L's room), from 4096 edges on (with fewer all
-// edges run at once with four waves each), and where the links, T / K vertices
-// on average, are small enough for one wave.  us with four waves / with one
-// (a list takes its count too):
-//   T / K  K       count        list
-//    12    11975    23 /  19     52 /  22    (400 points; kernels alone)
-//     9    24975    76 /  58    229 / 141    (1000 points; calls from here on)
-//    18    11212    39 /  41    125 /  98    (300)
-//    49    11175    55 /  96    223 / 246    (150, all edges)
-//    50    99900   416 / 429   1628 / 1291   (1000)
-//    57   157132   739 / 1015  3159 / 2881   (1024)
-//   133    79800   735 / 1361  4618 / 5135   (400, all edges)
-// The count's rows of pairs leave few lanes idle in long links, so four waves
-// count those faster; a writer's longest link wants many other edges beside it.
-#define TET_WAVE_N 1024
-
-static bool tet_by_wave(bool write, int64_t n, int64_t K, int64_t T) {
-    if (n > TET_WAVE_N || K < 4096) return false;
-    if (!write) return T <= 16 * K;
-    return T <= 32 * K || (T <= 64 * K && K >= 65536);
-}
-
+// The same with one wave per edge (tet_by_wave says when).
 static __device__ __forceinline__ uint32_t tet_common(const int32_t *D, int64_t ld, int n, int64_t i, int64_t j,
                                                      int32_t r, uint16_t *L) {
     const int lane = threadIdx.x & 63;
