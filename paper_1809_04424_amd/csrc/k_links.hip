@@ -41,6 +41,7 @@
 // coboundary by one work-group, most of them to zero; these kernels take 17,
 // 10, 39 and 9 us.
 #include <hip/hip_runtime.h>
+#include <immintrin.h>
 #include <stdint.h>
 
 #include "vr.h"
@@ -85,7 +86,10 @@ struct LkBufs {
     LkCrit *crit;
     uint32_t *pool;
     LkCtl *ctl;
+    uint32_t *word;  // host: LK_FITS or LK_MANY once known, if asked for
 };
+#define LK_FITS 1u
+#define LK_MANY 2u
 
 typedef unsigned long long lk_bits;
 __device__ __forceinline__ lk_bits lk_low(uint32_t x) { return x >= 64 ? ~0ull : (1ull << x) - 1; }
@@ -164,7 +168,11 @@ __device__ __forceinline__ lk_bits lk_collapse(lk_bits row, uint32_t L, uint32_t
 __global__ __launch_bounds__(LK_BLOCK) void k_lk_pairs(LkBufs B) {
     const uint32_t lane = lane_id();
     const int64_t nw = (int64_t)gridDim.x * LK_WPB;
-    // the youngest edges first: their links are the largest, and one past the
+    const uint32_t many = B.ctl->err;  // a link has too many vertices
+    if (B.word && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(B.word, many ? LK_MANY : LK_FITS, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (many) return;
+    // the youngest edges first: their links are the largest, and one past a
     // limit ends the kernel (a wave looks after its first edge and every
     // fourth: a look is a read of one address by all)
     int it = 0;
@@ -174,10 +182,6 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_pairs(LkBufs B) {
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane(B.rng[2 * (int64_t)r]);
         const uint32_t L = (uint32_t)__builtin_amdgcn_readfirstlane(B.rng[2 * (int64_t)r + 1]) - lo;
         if (L == 0) continue;
-        if (L > VR_WAVE) {
-            if (lane == 0) st_store32(&B.ctl->err, 1u);
-            return;
-        }
         uint32_t k;
         lk_bits row;
         lk_link(B, r, lo, L, k, row);
@@ -219,7 +223,14 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_pairs(LkBufs B) {
         if (st_load32(&B.ctl->err)) return;  // before the longest step
         uint32_t rho;
         const lk_bits A = lk_collapse(row, L, rho);
-        if (__popcll(A) != __popcll(roots) && lane == 0) B.list[atomicAdd(&B.ctl->nlink, 1u)] = r;
+        if (__popcll(A) == __popcll(roots)) continue;
+        // edges outside a forest of the core, which has the link's components
+        const uint32_t ends = wave_sum<uint32_t>(((A >> lane) & 1ull) ? (uint32_t)__popcll(row & A) : 0u);
+        if (ends / 2 + (uint32_t)__popcll(roots) > 64u + (uint32_t)__popcll(A)) {
+            if (lane == 0) st_store32(&B.ctl->err, 1u);
+            return;
+        }
+        if (lane == 0) B.list[atomicAdd(&B.ctl->nlink, 1u)] = r;
     }
 }
 
@@ -251,28 +262,20 @@ __global__ __launch_bounds__(VR_WAVE) void k_lk_cycles(LkBufs B) {
         for (int j = 0; j < VR_WAVE; j++) ann[lane][j] = 0ull;
         vx[lane] = k;
         lk_wave_sync();
-        // bits of the core's edges outside a forest
+        // bits of the core's edges outside a forest: 64 at most (k_lk_pairs)
         uint32_t comp = lane, nb = 0;
-        bool over = false;
-        for (lk_bits xs = A; xs && !over; xs &= xs - 1) {
+        for (lk_bits xs = A; xs; xs &= xs - 1) {
             const uint32_t x = (uint32_t)__builtin_ctzll(xs);
             for (lk_bits ys = lk_rl64(row, x) & A & ~lk_low(x + 1); ys; ys &= ys - 1) {
                 const uint32_t y = (uint32_t)__builtin_ctzll(ys);
                 const uint32_t cx = lk_rl(comp, x), cy = lk_rl(comp, y);
                 if (cx != cy) {
                     if (comp == max(cx, cy)) comp = min(cx, cy);
-                } else if (nb == 64) {
-                    over = true;
-                    break;
                 } else {
                     if (lane == 0) ann[x][y] = ann[y][x] = 1ull << nb;
                     nb++;
                 }
             }
-        }
-        if (over) {
-            if (lane == 0) B.ctl->err = 1u;
-            return;
         }
         lk_wave_sync();
         lk_bits live = lk_low(nb);
@@ -569,7 +572,7 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_reduce(LkBufs B) {
     }
 }
 
-static_assert(sizeof(LkCtl) == LINK_PAIRS_ZERO, "the control words start as zeros");
+static_assert(sizeof(LkCtl) == LINK_PAIRS_ZERO && LINK_PAIRS_MOST == VR_WAVE, "the control words, a lane per vertex");
 
 size_t link_pairs_scratch(int64_t K, int64_t T) {
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -610,14 +613,38 @@ int link_pairs_dim2(const int32_t *R, const int32_t *ij, const unsigned long lon
     B.list = (uint32_t *)part(4 * (size_t)K);
     B.crit = (LkCrit *)part(sizeof(LkCrit) * LK_CRIT);
     B.pool = (uint32_t *)part(4 * (size_t)LK_POOL);
+    // Where a link can have too many vertices the host hears of it from the
+    // first kernel's start, and goes to the reduction without the other three.
+    // That costs nothing where none has: the others are enqueued while the first runs.
+    // Before, the reduction followed a lost attempt: 80 and 125 points, all
+    // edges, 318 and 858 us without the links, 364 and 968 then, 320 and 863 now.
+    uint32_t *word = nullptr;
+    if (n > LINK_PAIRS_MOST + 2) {
+        if (!host_word(&word, &B.word)) return VR_ENOMEM;
+        __atomic_store_n(word, 0u, __ATOMIC_RELEASE);
+    }
     const int64_t wg = (K + LK_WPB - 1) / LK_WPB;
     hipLaunchKernelGGL(k_lk_pairs, dim3((unsigned)(wg < 2048 ? wg : 2048)), dim3(LK_BLOCK), 0, s, B);  // fills the chip
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return VR_EHIP;
+    if (word) {
+        uint32_t w;
+        for (unsigned spins = 1; (w = __atomic_load_n(word, __ATOMIC_ACQUIRE)) == 0u; spins++) {
+            if (spins % 4096 == 0) {  // a failed launch must not leave the host waiting
+                e = hipStreamQuery(s);
+                if (e == hipSuccess && __atomic_load_n(word, __ATOMIC_ACQUIRE) == 0u) return VR_EHIP;
+                if (e != hipSuccess && e != hipErrorNotReady) return VR_EHIP;
+            }
+            _mm_pause();
+        }
+        if (w == LK_MANY) return VR_OK;
+    }
     hipLaunchKernelGGL(k_lk_cycles, dim3(1024), dim3(VR_WAVE), 0, s, B);
     const size_t lds = 4 * (size_t)((T + 31) / 32);
     hipLaunchKernelGGL(k_lk_expand, dim3(256), dim3(LK_BLOCK), lds, s, B);
     hipLaunchKernelGGL(k_lk_reduce, dim3(1), dim3(LK_BLOCK), lds, s, B);
     LkCtl h{};
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&h, B.ctl, sizeof(h), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return VR_EHIP;

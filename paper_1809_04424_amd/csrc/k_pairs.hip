@@ -2082,7 +2082,8 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_clear(const int32_t *toe, int64
 //   - the edges into the rank matrix;
 //   - clr[t] = 1 for the triangles paired with an edge;
 //   - rng[2r], rng[2r + 1] = the first and one past the last triangle of
-//     value r (both 0 when there is none).
+//     value r (both 0 when there is none);
+//   - links[0] = 1 when a value has more triangles than link_pairs_dim2 takes.
 __global__ void __launch_bounds__(PD_BLOCK) k_d2_fill(int32_t *R, int64_t n, int32_t *clr, int64_t T, int32_t *rng,
                                                      int64_t K, uint32_t *links) {
     const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, step = (int64_t)gridDim.x * PD_BLOCK;
@@ -2094,7 +2095,7 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_fill(int32_t *R, int64_t n, int
 
 __global__ void __launch_bounds__(PD_BLOCK) k_d2_tables(int32_t *R, int64_t n, const int32_t *ij, int64_t K,
                                                        const int32_t *toe, const unsigned long long *tri, int64_t T,
-                                                       int32_t *clr, int32_t *rng) {
+                                                       int32_t *clr, int32_t *rng, uint32_t *links) {
     const int64_t x0 = blockIdx.x * (int64_t)PD_BLOCK + threadIdx.x, step = (int64_t)gridDim.x * PD_BLOCK;
     for (int64_t r = x0; r < K; r += step) {
         vr_rank_edge(R, ij, n, r);
@@ -2103,7 +2104,10 @@ __global__ void __launch_bounds__(PD_BLOCK) k_d2_tables(int32_t *R, int64_t n, c
     }
     for (int64_t t = x0; t < T; t += step) {
         const unsigned long long v = tri[t] >> 39;
-        if (t == 0 || (tri[t - 1] >> 39) != v) rng[2 * v] = (int32_t)t;
+        if (t == 0 || (tri[t - 1] >> 39) != v) {
+            rng[2 * v] = (int32_t)t;
+            if (links && t + LINK_PAIRS_MOST < T && (tri[t + LINK_PAIRS_MOST] >> 39) == v) links[0] = 1u;
+        }
         if (t == T - 1 || (tri[t + 1] >> 39) != v) rng[2 * v + 1] = (int32_t)(t + 1);
     }
 }
@@ -2291,11 +2295,11 @@ static int d2_tables(const vr_result *res, const int32_t *tri_of_edge, D2Tables 
     t->rng = (int32_t *)(t->ws + o_rng);
     t->links = t->ws + o_lk;
     const int64_t most = n * n > T ? (n * n > 2 * K ? n * n : 2 * K) : (T > 2 * K ? T : 2 * K);
-    hipLaunchKernelGGL(k_d2_fill, dim3(grid_for(most)), dim3(PD_BLOCK), 0, s, t->R, n, t->clr, T, t->rng, K,
-                       link_pairs_scratch(K, T) ? (uint32_t *)t->links : nullptr);
+    uint32_t *links = link_pairs_scratch(K, T) ? (uint32_t *)t->links : nullptr;
+    hipLaunchKernelGGL(k_d2_fill, dim3(grid_for(most)), dim3(PD_BLOCK), 0, s, t->R, n, t->clr, T, t->rng, K, links);
     hipLaunchKernelGGL(k_d2_tables, dim3(grid_for(K > T ? K : T)), dim3(PD_BLOCK), 0, s, t->R, n,
                        (const int32_t *)res->edge_ij, K, tri_of_edge, (const unsigned long long *)res->tri_key, T,
-                       t->clr, t->rng);
+                       t->clr, t->rng, links);
     return VR_OK;
 }
 

@@ -203,6 +203,16 @@ struct HostMem {
     }
 };
 thread_local HostMem g_host;
+}  // namespace
+
+bool host_word(uint32_t **h, uint32_t **d) {
+    if (!g_host.mailbox()) return false;
+    *h = &g_host.mb_h->word;
+    *d = &g_host.mb_d->word;
+    return true;
+}
+
+namespace {
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <stdint.h>
 
 // Device memory of at least `bytes` usable on stream s in stream order
 // (nullptr when the device is out of memory even after dropping the cache).
@@ -19,3 +20,8 @@ size_t cache_trim();
 
 // Bytes held from the driver on the current device (in use plus cached).
 size_t cache_held();
+
+// A pinned word of the calling host thread that kernels can store to (*h on
+// the host, *d on the device), for one call at a time.  False when there is
+// no memory for it.
+bool host_word(uint32_t **h, uint32_t **d);

@@ -54,7 +54,8 @@ struct VrMailbox {
     uint32_t n_cand;
     uint32_t n_kept;
     unsigned long long n_tri;
-    unsigned long long pad[5];
+    uint32_t word;  // of a call that reads one word back (host_word)
+    uint32_t pad[9];
 };
 
 // ---------------------------------------------------------------- lanes ----

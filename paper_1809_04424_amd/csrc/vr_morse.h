@@ -31,11 +31,13 @@ int morse_pairs_dim1(int32_t *R, const int32_t *ij, const unsigned long long *ke
 // edges (k_links.hip) into tri_tet (T entries, device).  R: the rank matrix; rng[2r],
 // rng[2r + 1]: the triangles of value r, first and one past the last; clr: 1
 // for the triangles paired with an edge; toff: the tetrahedra's offsets by
-// value; scratch: link_pairs_scratch(K, T) bytes, device, the first
-// LINK_PAIRS_ZERO zero where there are any.  *done is false
+// value; scratch: link_pairs_scratch(K, T) bytes, device, where there are any
+// the first word 1 when a value has more than LINK_PAIRS_MOST triangles, else
+// 0, and the rest of the first LINK_PAIRS_ZERO bytes zero.  *done is false
 // when a limit of the method was passed (tri_tet is then not complete);
 // synchronises s.  Returns a vr_status.
 #define LINK_PAIRS_ZERO 16
+#define LINK_PAIRS_MOST 64
 size_t link_pairs_scratch(int64_t K, int64_t T);
 int link_pairs_dim2(const int32_t *R, const int32_t *ij, const unsigned long long *tri, const long long *toff,
                     const int32_t *rng, const int32_t *clr, int64_t n, int64_t K, int64_t T, long long *tri_tet,
