@@ -33,6 +33,10 @@
 #define CO_WAVE 64
 #define CO_SEGS 256  // segments of a window that is sorted into buckets
 #define CO_CROWD 24  // longest bucket
+#define CO_COPIES 16  // of a segment's smallest and largest value
+
+static_assert(2 * (CO_SEGS + 8) + 4 * CO_SEGS + 16 * CO_SEGS <= 2 * (CO_WIN + 2), "the segments' values fit behind their starts");
+static_assert(8 * CO_COPIES * CO_SEGS <= 8 * (CO_WIN + CO_WIN / 16), "the copies fit over the keys");
 
 static __device__ __forceinline__ int64_t clampi(int64_t x, int64_t lo, int64_t hi) {
     return x < lo ? lo : (x > hi ? hi : x);
@@ -85,44 +89,64 @@ static __device__ __forceinline__ void co_put(const KEY (&r)[CO_PER], int t, KEY
     for (int g = 0; g < CO_PER; g++) keys[co_phys(co_pos<LAY>(t, g))] = r[g];
 }
 
-// move the keys from layout cur to layout TO through LDS
+// move the keys from layout cur to layout TO through LDS.  C and S hold the
+// same 1024 positions in a wave, which then waits for itself alone (12 of the
+// sort's 21 moves).
 template <int TO, typename KEY>
 static __device__ __forceinline__ void co_to(KEY (&r)[CO_PER], int &cur, int t, KEY *keys) {
     if (cur == TO) return;  // uniform over the work-group
-    __syncthreads();        // earlier reads of the buffer are done
+    const bool wave = cur != 2 && TO != 2;
+    auto sync = [&] {
+        if (wave) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        } else {
+            __syncthreads();
+        }
+    };
+    sync();  // earlier reads of the buffer are done
     if (cur == 0) co_put<0>(r, t, keys);
     else if (cur == 1) co_put<1>(r, t, keys);
     else co_put<2>(r, t, keys);
-    __syncthreads();
+    sync();
 #pragma unroll
     for (int g = 0; g < CO_PER; g++) r[g] = keys[co_phys(co_pos<TO>(t, g))];
     cur = TO;
 }
 
-// the stages of one merge width kk on the position bits that layout LAY
+// Smaller and larger of two keys.  64-bit ones compare as doubles: a set bit
+// CO_KEY64 makes them normal numbers, ordered as the integers are, and one
+// instruction each takes the place of a comparison and four selects.
+#define CO_KEY64 (1ull << 62)
+#define CO_PAD64 0x7FEFFFFFFFFFFFFFull  // the largest finite one: pads sort last
+static __device__ __forceinline__ void co_exchange(uint32_t &x, uint32_t &y) {
+    const uint32_t lo = min(x, y), hi = max(x, y);
+    x = lo;
+    y = hi;
+}
+static __device__ __forceinline__ void co_exchange(unsigned long long &x, unsigned long long &y) {
+    const double u = __longlong_as_double((long long)x), v = __longlong_as_double((long long)y);
+    double lo, hi;
+    asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(u), "v"(v));
+    asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(u), "v"(v));
+    x = (unsigned long long)__double_as_longlong(lo);
+    y = (unsigned long long)__double_as_longlong(hi);
+}
+// The key in the opposite order, and back: all bits, or the sign.
+static __device__ __forceinline__ void co_flip(uint32_t &x, bool on) { x ^= on ? ~0u : 0u; }
+static __device__ __forceinline__ void co_flip(unsigned long long &x, bool on) { x ^= on ? 1ull << 63 : 0ull; }
+
+// the stages of one merge width on the position bits that layout LAY
 // holds in registers (bits 4*LAY .. 4*LAY+3, at most bhi), highest first
 template <int LAY, typename KEY>
-static __device__ __forceinline__ void co_stages(KEY (&r)[CO_PER], int t, int kk, int bhi) {
+static __device__ __forceinline__ void co_stages(KEY (&r)[CO_PER], int bhi) {
 #pragma unroll
     for (int gb = 3; gb >= 0; gb--) {
         if (4 * LAY + gb > bhi) continue;
-        const int j = 1 << gb;
 #pragma unroll
-        for (int g = 0; g < CO_PER; g++) {
-            if (g & j) continue;
-            const int h = g | j;
-            const bool up = (co_pos<LAY>(t, g) & kk) == 0;
-            const KEY k0 = r[g], k1 = r[h];
-            if constexpr (sizeof(KEY) == 4) {
-                const KEY lo = min(k0, k1), hi = max(k0, k1);
-                r[g] = up ? lo : hi;
-                r[h] = up ? hi : lo;
-            } else {
-                const bool sw = (k0 > k1) == up;
-                r[g] = sw ? k1 : k0;
-                r[h] = sw ? k0 : k1;
-            }
-        }
+        for (int g = 0; g < CO_PER; g++)
+            if (!(g & (1 << gb))) co_exchange(r[g], r[g | (1 << gb)]);
     }
 }
 
@@ -131,22 +155,28 @@ static __device__ __forceinline__ void co_stages(KEY (&r)[CO_PER], int t, int kk
 // thread holds 16 keys in one of three layouts, each owning four bits of the
 // position (C: bits 0-3, position 16t + g; S: bits 4-7, 256(t/16) + 16g +
 // t%16; L: bits 8-11, 256g + t), and the keys move between layouts through
-// LDS.
+// LDS.  The blocks that a merge sorts downwards hold their keys flipped, so
+// that every exchange goes the same way; that is one instruction a key and merge.
 template <typename KEY>
 static __device__ __forceinline__ void co_bitonic(KEY (&r)[CO_PER], int t, KEY *keys) {
     int cur = 2;
     for (int lk = 1; lk <= 12; lk++) {  // merge width 2^lk: stages on bits lk-1 .. 0
-        const int kk = 1 << lk;
+        if (lk == 1) co_to<0>(r, cur, t, keys);
+#pragma unroll
+        for (int g = 0; g < CO_PER; g++) {  // downwards where bit lk of the position is set
+            const int p = co_pos<0>(t, g);
+            co_flip(r[g], ((p >> lk) ^ (lk > 1 ? p >> (lk - 1) : 0)) & 1);
+        }
         if (lk - 1 >= 8) {
             co_to<2>(r, cur, t, keys);
-            co_stages<2>(r, t, kk, lk - 1);
+            co_stages<2>(r, lk - 1);
         }
         if (lk - 1 >= 4) {
             co_to<1>(r, cur, t, keys);
-            co_stages<1>(r, t, kk, lk - 1);
+            co_stages<1>(r, lk - 1);
         }
         co_to<0>(r, cur, t, keys);
-        co_stages<0>(r, t, kk, lk - 1);
+        co_stages<0>(r, lk - 1);
     }
 }
 
@@ -155,14 +185,15 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
                                                       uint32_t *vs) {
     // keys: counting path, the values with the sign bit flipped (unsigned
     // order); sorting path, the keys between layouts, then the slots
-    __shared__ unsigned long long keys[CO_WIN + CO_WIN / 16];
+    __shared__ __align__(16) unsigned long long keys[CO_WIN + CO_WIN / 16];
     uint32_t *kv = (uint32_t *)keys;
     __shared__ __align__(16) uint16_t segid[CO_WIN];  // first the segment-start flags; at last the buckets' starts
-    __shared__ uint16_t segstart[CO_WIN + 2];
+    __shared__ __align__(16) uint16_t segstart[CO_WIN + 2];
     __shared__ uint32_t wsum[CO_BLOCK / CO_WAVE];
     __shared__ uint32_t maxlen, few, longest, vbits;
-    __shared__ uint32_t smin[CO_SEGS], smax[CO_SEGS];
-    __shared__ uint4 seg[CO_SEGS];  // least value, buckets per value (float), first bucket, last bucket's index
+    // of at most CO_SEGS segments, behind their starts
+    uint32_t *smin = (uint32_t *)(segstart + CO_SEGS + 8);
+    uint4 *seg = (uint4 *)(smin + CO_SEGS);  // least value, buckets per value (float), first bucket, last bucket's index
 
     const int t = threadIdx.x, lane = t % CO_WAVE, wv = t / CO_WAVE;
     const CoWindow W = co_window(colptr, ncols, nnz, first, nwin, blockIdx.x);
@@ -179,10 +210,6 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         segid[t + m * CO_BLOCK] = 0;
     }
     if (t == 0) maxlen = few = longest = vbits = 0;
-    if (t < CO_SEGS) {
-        smin[t] = ~0u;
-        smax[t] = 0;
-    }
     __syncthreads();
     // segment starts: every column that begins strictly inside the window
     const int64_t cend = W.cl >= 0 ? W.cl : ncols - 1;
@@ -297,16 +324,22 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
     // Buckets: a segment of len entries takes len buckets, its values spread
     // over them in order (float products, which round monotonically), so an
     // entry shares its bucket with few others and its place is the bucket's
-    // start plus the smaller (value, position) there.  A bitonic sort of 4096
-    // 64-bit keys is bound by its 78 stages of compares (69 us for 2000
-    // columns of 1999 entries); the buckets take 41, with 2900 instructions a
-    // wave and half the time in waits for LDS: two work-groups fit a compute
-    // unit.  Capping the registers to fit three or four took 63 and 42 us.
+    // start plus the smaller (value, position) there.  2000 columns of 1999
+    // entries, us of this kernel: sorted by 64-bit keys 68, in buckets 36, half
+    // the time in waits for LDS: 225 registers leave two work-groups a compute
+    // unit (bounded to 168, for a third, 53 of them spilled: 53 us).
     // Where values crowd (24 or more in a bucket) the window is sorted after
-    // all, by 32-bit keys if they hold segment, value and position: 2000
-    // columns of 1000 entries and 10 values 61 -> 56 us; values so clustered
-    // that the buckets are tried in vain and the keys stay wide (twelfth
-    // powers of uniform numbers) 69 -> 80.
+    // all, by 32-bit keys if they hold segment, value and position.  It must
+    // not lose there what it had before the buckets; us of whole calls, always sorted / with
+    // buckets tried first and the sort as it was / now:
+    //                      2000 columns of 1999   4000 of 300
+    //   uniform                100 /  69 /  66     54 / 44 / 34
+    //   10 values               99 /  93 /  82     54 / 57 / 43
+    //   twelfth powers         100 / 128 /  97     55 / 75 / 49
+    //   lognormal, sigma 4      99 / 136 /  98     54 / 78 / 50
+    // The extremes took as long as the sort's half where a window has a dozen
+    // segments (CO_COPIES), crowds are seen in a quarter of the entries, and the
+    // sort's exchanges and moves cost less (co_exchange, co_to).
     if (nseg <= CO_SEGS) {
         uint32_t *cw = (uint32_t *)segid;
         uint32_t sgw[CO_PER / 4];  // the entries' segments, four in a word
@@ -320,17 +353,29 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
             for (int m = 0; m < CO_PER; m += 4)
                 sgw[m / 4] = segid[t + m * CO_BLOCK] | (uint32_t)segid[t + (m + 1) * CO_BLOCK] << 8 |
                              (uint32_t)segid[t + (m + 2) * CO_BLOCK] << 16 | (uint32_t)segid[t + (m + 3) * CO_BLOCK] << 24;
-            // smallest and largest value of each segment
+            // smallest and largest value of each segment, in CO_COPIES copies
+            // over the keys: a wave's lanes mostly share a segment, and 64
+            // atomics on one address follow one another
+            uint32_t *lows = kv, *highs = kv + CO_COPIES * CO_SEGS;
+            for (int s = t; s < CO_COPIES * nseg; s += CO_BLOCK) {
+                lows[s] = ~0u;
+                highs[s] = 0;
+            }
+            __syncthreads();
             {
+                const int copy = t % CO_COPIES;
                 uint32_t lo = ~0u, hi = 0;
                 uint32_t cs = sg(0);
+                auto out = [&] {
+                    atomicMin(&lows[CO_COPIES * cs + copy], lo);
+                    atomicMax(&highs[CO_COPIES * cs + copy], hi);
+                };
 #pragma unroll
                 for (int m = 0; m < CO_PER; m++) {
                     const uint32_t u = (uint32_t)x[m] ^ 0x80000000u;
                     if (in(m)) {
                         if (sg(m) != cs) {
-                            atomicMin(&smin[cs], lo);
-                            atomicMax(&smax[cs], hi);
+                            out();
                             cs = sg(m);
                             lo = ~0u;
                             hi = 0;
@@ -339,18 +384,23 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
                         hi = max(hi, u);
                     }
                 }
-                if (in(0)) {
-                    atomicMin(&smin[cs], lo);
-                    atomicMax(&smax[cs], hi);
-                }
+                if (in(0)) out();
             }
             __syncthreads();
             if (t < nseg) {
-                const uint32_t st = segstart[t], len = segstart[t + 1] - st, range = smax[t] - smin[t];
+                uint32_t lo = ~0u, hi = 0;
+#pragma unroll
+                for (int c = 0; c < CO_COPIES; c += 4) {
+                    const uint4 l = *(const uint4 *)&lows[CO_COPIES * t + c], h = *(const uint4 *)&highs[CO_COPIES * t + c];
+                    lo = min(lo, min(min(l.x, l.y), min(l.z, l.w)));
+                    hi = max(hi, max(max(h.x, h.y), max(h.z, h.w)));
+                }
+                const uint32_t st = segstart[t], len = segstart[t + 1] - st, range = hi - lo;
                 const float scale = (float)len / ((float)range + 1.0f);
                 atomicMax(&vbits, range ? 32u - (uint32_t)__builtin_clz(range) : 0u);
                 if (len > CO_CROWD && scale >= (float)(CO_CROWD / 2)) few = 1;  // few values: sort
-                seg[t] = make_uint4(smin[t], __float_as_uint(scale), st, len - 1);
+                smin[t] = lo;
+                seg[t] = make_uint4(lo, __float_as_uint(scale), st, len - 1);
             }
             // segid becomes the buckets' counts, two in a word
 #pragma unroll
@@ -366,13 +416,16 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
             }
             uint32_t last = 0;
 #pragma unroll
-            for (int m = 0; m < CO_PER; m++)
+            for (int m = 0; m < CO_PER; m++) {
+                // a quarter shows the worst crowds, whose lanes meet at one address
+                if (m == CO_PER / 4 && __syncthreads_or(last >= CO_CROWD)) return false;
                 if (in(m)) {
                     const uint32_t sh = (at[m] & 1) * 16;
                     const uint32_t k = (atomicAdd(&cw[at[m] >> 1], 1u << sh) >> sh) & 0xFFFFu;
                     at[m] |= k << 16;
                     last = max(last, k);
                 }
+            }
             if (last > longest) atomicMax(&longest, last);
             __syncthreads();
             const int far = (int)longest;
@@ -479,16 +532,18 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
         __syncthreads();
     }
 
-    // Bitonic sort of the keys (segment, value, position); pads sort last.
-    // The keys start in layout L, which is how the values were loaded.
+    // Bitonic sort of the keys (segment, value, position).  They start in
+    // layout L, which is how the values were loaded.
     unsigned long long r[CO_PER];
 #pragma unroll
     for (int g = 0; g < CO_PER; g++) {
         const int p = t + g * CO_BLOCK;
         const unsigned long long u = (uint32_t)x[g] ^ 0x80000000u;
-        r[g] = p < cnt ? ((unsigned long long)segid[p] << 44) | (u << 12) | (unsigned)p : ~0ull;
+        r[g] = p < cnt ? CO_KEY64 | ((unsigned long long)segid[p] << 44) | (u << 12) | (unsigned)p : CO_PAD64;
     }
     co_bitonic(r, t, keys);
+#pragma unroll
+    for (int g = 0; g < CO_PER; g++) r[g] &= ~CO_KEY64;
     const int still[CO_PER] = {};
     finish(r, still);
 }
