@@ -302,13 +302,13 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
     }
 
     // z of the thread's keys (segment << 44 | value << 12 | position), key g
-    // in sorted position CO_PER * t + g + mv[g]
-    auto finish = [&](const unsigned long long (&r)[CO_PER], const int (&mv)[CO_PER]) {
+    // in sorted position CO_PER * t + g
+    auto finish = [&](const unsigned long long (&r)[CO_PER]) {
         __syncthreads();  // every thread's last read of the keys is done
 #pragma unroll
         for (int g = 0; g < CO_PER; g++) {
             if (CO_PER * t + g < cnt) {
-                const int y = CO_PER * t + g + mv[g], sg = (int)(r[g] >> 44), idx = (int)(r[g] & 0xFFFu);
+                const int y = CO_PER * t + g, sg = (int)(r[g] >> 44), idx = (int)(r[g] & 0xFFFu);
                 keys[co_phys(idx)] = (unsigned long long)(base_of(sg) + (y - segstart[sg]));
                 if (spans(sg)) vs[a + y] = (uint32_t)(r[g] >> 12);
             }
@@ -514,14 +514,13 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
             }
             co_bitonic(r, t, kv);
             unsigned long long rl[CO_PER];
-            const int still[CO_PER] = {};
 #pragma unroll
             for (int g = 0; g < CO_PER; g++) {
                 const uint32_t s = min((r[g] >> 12) >> vb, (uint32_t)nseg - 1);
                 rl[g] = ((unsigned long long)s << 44) |
                         ((unsigned long long)(smin[s] + ((r[g] >> 12) & ((1u << vb) - 1u))) << 12) | (r[g] & 0xFFFu);
             }
-            finish(rl, still);
+            finish(rl);
             return;
         }
         // the segments again, for the keys below
@@ -544,8 +543,7 @@ __global__ void __launch_bounds__(CO_BLOCK) k_co_local(const int64_t *colptr, in
     co_bitonic(r, t, keys);
 #pragma unroll
     for (int g = 0; g < CO_PER; g++) r[g] &= ~CO_KEY64;
-    const int still[CO_PER] = {};
-    finish(r, still);
+    finish(r);
 }
 
 // Per window, for the (at most two) columns that leave it: every other
