@@ -64,6 +64,7 @@ struct LkCrit {
     uint32_t r, ne;
     uint32_t uv[VR_WAVE];  // the cycle's edges, u << 16 | v
     uint32_t start, len;   // its column in the pool
+    uint32_t top, pad;     // the column's youngest triangle + 1
 };
 
 struct LkCtl {
@@ -375,91 +376,111 @@ __device__ __forceinline__ int32_t lk_triangle(const LkBufs &B, uint32_t x, uint
     const uint32_t s0 = min(x, min(y, z)), s2 = max(x, max(y, z)), s1 = x + y + z - s0 - s2;
     const lk_bits key = ((lk_bits)(uint32_t)v << 39) | ((lk_bits)s0 << 26) | ((lk_bits)s1 << 13) | s2;
     int32_t lo = B.rng[2 * (int64_t)v], hi = B.rng[2 * (int64_t)v + 1];
-    const int32_t end = hi;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (B.tri[mid] < key) lo = mid + 1;
-        else hi = mid;
+    // eighths, not halves: the reads of one step wait together
+    while (hi - lo > 8) {
+        const int32_t part = (hi - lo) / 8;
+        int32_t below = 0;
+#pragma unroll
+        for (int32_t i = 1; i < 8; i++) below += B.tri[lo + i * part - 1] < key ? 1 : 0;
+        lo += below * part;
+        if (below < 7) hi = lo + part;
     }
-    return lo < end && B.tri[lo] == key ? lo : -1;
+    int32_t at = -1;
+#pragma unroll
+    for (int32_t i = 0; i < 8; i++)
+        if (lo + i < hi && B.tri[lo + i] == key) at = lo + i;
+    return at;
 }
 
 // One work-group per critical tetrahedron.  Its column is a bit per triangle
-// in LDS; all triangles that are not critical are replaced at once, until
-// none is left.  Each is replaced by older ones or one nearer its tree's
-// root, so that ends, in tens of rounds of dependent reads, which bound it.
+// in LDS; all triangles that are not critical are replaced, until none is
+// left.  Each is replaced by older ones or one nearer its tree's root, so
+// that ends, in tens of rounds of dependent reads, which bound it: a round
+// goes over a list of the triangles that the last one set, the bits are
+// searched only when more were set than the list holds, and four lanes share
+// a triangle, one for each that replaces it.  A grid of 8 x 8 x 8 points,
+// hundreds of columns: 375 us with the bits searched in each round and a
+// lane to a triangle, 104 so.
 __global__ __launch_bounds__(LK_BLOCK) void k_lk_expand(LkBufs B) {
-    extern __shared__ uint32_t bm[];
-    __shared__ uint32_t fr[LK_FRONT];
-    __shared__ uint32_t nf, base, stop;
+    extern __shared__ __attribute__((aligned(8))) uint32_t bm[];
+    __shared__ uint32_t fr[2][LK_FRONT], sum[3];  // the lists of two rounds; entries, of this round, the next and the one after
+    __shared__ uint32_t nf, base, stop, top;
     const uint32_t t = threadIdx.x, nw = (uint32_t)((B.T + 31) / 32);
     if (t == 0) stop = B.ctl->err;  // one read for all: other work-groups may set it
     __syncthreads();
     if (stop) return;
     const uint32_t nc = B.ctl->ncrit;
-    auto flip = [&](uint32_t x, uint32_t y, uint32_t z) {
+    auto push = [&](uint32_t q, uint32_t round) {
+        const uint32_t at = atomicAdd(&sum[round % 3], 1u);
+        if (at < LK_FRONT) fr[round & 1][at] = q;
+    };
+    auto flip = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t round) {
         const int32_t q = lk_triangle(B, x, y, z);
-        if (q >= 0) atomicXor(&bm[q >> 5], 1u << (q & 31));
-        else B.ctl->err = 1u;  // never: the vertices are joined
+        if (q < 0) B.ctl->err = 1u;  // never: the vertices are joined
+        else if (!(atomicXor(&bm[q >> 5], 1u << (q & 31)) >> (q & 31) & 1u)) push((uint32_t)q, round);
     };
     for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
         LkCrit &C = B.crit[c];
         __syncthreads();
         for (uint32_t x = t; x < nw; x += LK_BLOCK) bm[x] = 0;
-        if (t == 0) nf = 0;
+        if (t < 3) sum[t] = 0;
         __syncthreads();
-        if (t < C.ne) {
-            const uint32_t a = (uint32_t)B.ij[2 * (int64_t)C.r], b = (uint32_t)B.ij[2 * (int64_t)C.r + 1];
-            const uint32_t uv = C.uv[t];
-            flip(a, uv >> 16, uv & 0xFFFFu);
-            flip(b, uv >> 16, uv & 0xFFFFu);
+        if (t < 2 * C.ne) {
+            const uint32_t uv = C.uv[t / 2];
+            flip((uint32_t)B.ij[2 * (int64_t)C.r + t % 2], uv >> 16, uv & 0xFFFFu, 0);
         }
-        __syncthreads();
-        for (int round = 0;; round++) {
-            for (uint32_t x = t; x < nw; x += LK_BLOCK) {
-                const uint32_t v = bm[x];
-                if (!v) continue;
-                uint32_t keep = 0;
-                for (uint32_t y = v; y; y &= y - 1) {
-                    const uint32_t q = x * 32 + (uint32_t)__builtin_ctz(y), p = B.par[q];
-                    if (p == LK_ROOT && !B.clr[q]) keep |= y & (0u - y);
-                    else if (p < LK_ROOT) {
-                        const uint32_t at = atomicAdd(&nf, 1u);
-                        if (at < LK_FRONT) fr[at] = q;
-                        else keep |= y & (0u - y);  // next round
-                    }
-                }
-                bm[x] = keep;
-            }
+        bool more = false;  // bits to replace that are on no list
+        for (uint32_t round = 0;; round++) {
             __syncthreads();
-            const uint32_t f = min(nf, (uint32_t)LK_FRONT);
+            uint32_t f = sum[round % 3];
+            if (more || f > LK_FRONT) {
+                __syncthreads();
+                if (t == 0) sum[round % 3] = 0;
+                __syncthreads();
+                for (uint32_t x = t; x < nw; x += LK_BLOCK)
+                    for (uint32_t y = bm[x]; y; y &= y - 1) {
+                        const uint32_t q = x * 32 + (uint32_t)__builtin_ctz(y), p = B.par[q];
+                        if (p != LK_ROOT || B.clr[q]) push(q, round);
+                    }
+                __syncthreads();
+                f = sum[round % 3];
+                more = f > LK_FRONT;
+                f = min(f, (uint32_t)LK_FRONT);
+            }
             if (f == 0) break;
             if (round == LK_ROUNDS) {
                 if (t == 0) B.ctl->err = 1u;
                 break;
             }
-            for (uint32_t x = t; x < f; x += LK_BLOCK) {
-                const uint32_t q = fr[x], p = B.par[q];
+            if (t == 0) sum[(round + 2) % 3] = 0;
+            for (uint32_t x = t / 4; x < f; x += LK_BLOCK / 4) {
+                const uint32_t q = fr[round & 1][x], which = t & 3, p = B.par[q];
+                const uint32_t clr = B.clr[q];
                 const lk_bits key = B.tri[q];
+                if (p == LK_ROOT && !clr) continue;  // critical: it stays
+                // on the list twice if its bit was set twice: the first takes it
+                uint32_t set = which == 0 ? atomicAnd(&bm[q >> 5], ~(1u << (q & 31))) >> (q & 31) & 1u : 0u;
+                set = (uint32_t)__shfl((int)set, (int)(t & (VR_WAVE - 1) & ~3u));
+                if (!set || p >= LK_ROOT || which == 3) continue;
                 const int64_t v = (int64_t)(key >> 39);
                 const uint32_t a = (uint32_t)B.ij[2 * v], b = (uint32_t)B.ij[2 * v + 1];
                 const uint32_t m = ((uint32_t)(key >> 26) & 0x1FFFu) + ((uint32_t)(key >> 13) & 0x1FFFu) +
                                    ((uint32_t)key & 0x1FFFu) - a - b;
-                flip(a, b, p);
-                flip(a, p, m);
-                flip(b, p, m);
+                flip(which == 2 ? b : a, which == 0 ? b : p, which == 0 ? p : m, round + 1);
             }
-            __syncthreads();
-            if (t == 0) nf = 0;
-            __syncthreads();
         }
         // the column into the pool
         __syncthreads();
-        if (t == 0) nf = 0;
+        if (t == 0) nf = top = 0;
         __syncthreads();
-        uint32_t own = 0;
-        for (uint32_t x = t; x < nw; x += LK_BLOCK) own += (uint32_t)__popc(bm[x]);
+        uint32_t own = 0, mine = 0;
+        for (uint32_t x = t; x < nw; x += LK_BLOCK) {
+            const uint32_t v = bm[x];
+            own += (uint32_t)__popc(v);
+            if (v) mine = x * 32 + 32 - (uint32_t)__builtin_clz(v);
+        }
         if (own) atomicAdd(&nf, own);
+        if (mine) atomicMax(&top, mine);
         __syncthreads();
         if (t == 0) {
             base = atomicAdd(&B.ctl->ptop, nf);
@@ -467,6 +488,7 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_expand(LkBufs B) {
             else {
                 C.start = base;
                 C.len = nf;
+                C.top = top;
             }
             own = nf;
             nf = base + own > LK_POOL ? LK_POOL : 0u;  // no room: no entry is written
@@ -481,96 +503,145 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_expand(LkBufs B) {
     }
 }
 
-// The columns in the order of the tetrahedra, each reduced by those before
-// it; a column's pivot is its youngest triangle.  One work-group: there are
-// few columns, and each depends on those before.
+// The columns' reduction, by one work-group: there are few.  A column's pivot
+// is its youngest triangle.  Those that are the first (in the order of the
+// tetrahedra) with their pivot take it at once; the others are reduced one
+// by one, by the columns that hold the pivots they meet.  One that meets
+// a pivot held by a later column takes it over, and that one goes on in its
+// place (as k_mo_reduce does): all additions are of earlier columns to later
+// ones, and the pairs do not depend on which were done.
+// A grid of 8 x 8 x 8 points, 141896 triangles, has hundreds of columns and
+// few that meet: one after the other they took 638 us, now 16.
+#define LK_START 22  // log2 of the pool: a stored column's start, its place in the order above
 __global__ __launch_bounds__(LK_BLOCK) void k_lk_reduce(LkBufs B) {
-    extern __shared__ uint32_t bm[];
+    extern __shared__ __attribute__((aligned(8))) uint32_t bm[];  // first the columns' tetrahedra, then their pivots
     __shared__ uint16_t ord[LK_CRIT];
-    __shared__ uint32_t pt[LK_CRIT], ps[LK_CRIT], pn[LK_CRIT];  // a stored column's pivot, start and entries
-    __shared__ uint32_t top, hit, cnt, base;
+    __shared__ uint32_t pt[LK_CRIT], ps[LK_CRIT], pn[LK_CRIT];  // held pivots: triangle, column and its start, entries
+    __shared__ uint32_t wait[LK_CRIT / 32];  // columns to reduce
+    __shared__ uint32_t top, hit, cnt, base, np;
     const uint32_t t = threadIdx.x, nw = (uint32_t)((B.T + 31) / 32);
     if (B.ctl->err) return;
     const uint32_t nc = B.ctl->ncrit;
+    if (nc == 0) return;
+    long long *tet = (long long *)bm;
+    for (uint32_t x = t; x < nc; x += LK_BLOCK) tet[x] = B.crit[x].tet;
+    __syncthreads();
     for (uint32_t x = t; x < nc; x += LK_BLOCK) {
+        const long long own = tet[x];
         uint32_t y = 0;
-        for (uint32_t z = 0; z < nc; z++) y += B.crit[z].tet < B.crit[x].tet ? 1u : 0u;
+#pragma unroll 8
+        for (uint32_t z = 0; z < nc; z++) y += tet[z] < own ? 1u : 0u;
         ord[y] = (uint16_t)x;
     }
-    uint32_t np = 0;
+    if (t == 0) np = 0;
+    if (t < LK_CRIT / 32) wait[t] = 0;
+    __syncthreads();
+    for (uint32_t i = t; i < nc; i += LK_BLOCK) bm[i] = B.crit[ord[i]].len ? B.crit[ord[i]].top : 0u;
+    __syncthreads();
+    for (uint32_t i = t; i < nc; i += LK_BLOCK) {
+        const uint32_t own = bm[i];
+        if (!own) continue;
+        bool first = true;
+#pragma unroll 8
+        for (uint32_t j = 0; j < i; j++) first &= bm[j] != own;
+        if (first) {
+            const uint32_t at = atomicAdd(&np, 1u);
+            const LkCrit &C = B.crit[ord[i]];
+            pt[at] = own - 1;
+            ps[at] = C.start | i << LK_START;
+            pn[at] = C.len;
+        } else {
+            atomicOr(&wait[i >> 5], 1u << (i & 31));
+        }
+    }
     auto add = [&](uint32_t start, uint32_t len) {
         for (uint32_t x = t; x < len; x += LK_BLOCK) {
             const uint32_t q = B.pool[start + x];
             atomicXor(&bm[q >> 5], 1u << (q & 31));
         }
     };
-    for (uint32_t i = 0; i < nc; i++) {
+    for (uint32_t w = 0; w < LK_CRIT / 32; w++) {
         __syncthreads();
-        for (uint32_t x = t; x < nw; x += LK_BLOCK) bm[x] = 0;
-        __syncthreads();
-        const LkCrit &C = B.crit[ord[i]];
-        add(C.start, C.len);
-        bool dirty = false;
-        for (;;) {
-            if (t == 0) {
-                top = 0;
-                hit = 0xFFFFFFFFu;
-            }
-            __syncthreads();
-            uint32_t mine = 0;
-            for (uint32_t x = t; x < nw; x += LK_BLOCK) {
-                const uint32_t v = bm[x];
-                if (v) mine = x * 32 + 32 - (uint32_t)__builtin_clz(v);
-            }
-            if (mine) atomicMax(&top, mine);
-            __syncthreads();
-            if (top == 0) break;  // zero: nothing dies
-            const uint32_t q = top - 1;
-            for (uint32_t x = t; x < np; x += LK_BLOCK)
-                if (pt[x] == q) hit = x;
-            __syncthreads();
-            const uint32_t j = hit;
-            if (j != 0xFFFFFFFFu) {
-                add(ps[j], pn[j]);
-                dirty = true;
+        for (uint32_t left = wait[w]; left; left &= left - 1) {
+            uint32_t cur = 32 * w + (uint32_t)__builtin_ctz(left);
+            uint32_t st = B.crit[ord[cur]].start, len = B.crit[ord[cur]].len;
+            bool fresh = true, dirty = false;
+            for (;;) {
                 __syncthreads();
-                continue;
-            }
-            // the pivot is free: pair, and store the column
-            uint32_t st = C.start, len = C.len;
-            if (dirty) {
-                if (t == 0) cnt = 0;
-                __syncthreads();
-                uint32_t own = 0;
-                for (uint32_t x = t; x < nw; x += LK_BLOCK) own += (uint32_t)__popc(bm[x]);
-                if (own) atomicAdd(&cnt, own);
-                __syncthreads();
-                if (t == 0) base = atomicAdd(&B.ctl->ptop, cnt);
-                __syncthreads();
-                st = base;
-                len = cnt;
-                if (st + len > LK_POOL) {
-                    if (t == 0) B.ctl->err = 1u;
-                    return;
+                if (fresh) {
+                    for (uint32_t x = t; x < nw; x += LK_BLOCK) bm[x] = 0;
+                    __syncthreads();
+                    add(st, len);
+                    fresh = dirty = false;
+                }
+                if (t == 0) {
+                    top = 0;
+                    hit = 0xFFFFFFFFu;
                 }
                 __syncthreads();
-                if (t == 0) cnt = 0;
+                uint32_t mine = 0;
+                for (uint32_t x = t; x < nw; x += LK_BLOCK) {
+                    const uint32_t v = bm[x];
+                    if (v) mine = x * 32 + 32 - (uint32_t)__builtin_clz(v);
+                }
+                if (mine) atomicMax(&top, mine);
                 __syncthreads();
-                for (uint32_t x = t; x < nw; x += LK_BLOCK)
-                    for (uint32_t y = bm[x]; y; y &= y - 1)
-                        B.pool[st + atomicAdd(&cnt, 1u)] = x * 32 + (uint32_t)__builtin_ctz(y);
+                if (top == 0) break;  // zero: nothing dies
+                const uint32_t q = top - 1, held = np;
+                for (uint32_t x = t; x < held; x += LK_BLOCK)
+                    if (pt[x] == q) hit = x;
+                __syncthreads();
+                const uint32_t j = hit;
+                const uint32_t other = j == 0xFFFFFFFFu ? 0xFFFFFFFFu : ps[j] >> LK_START;
+                if (other < cur) {
+                    add(ps[j] & ((1u << LK_START) - 1), pn[j]);
+                    dirty = true;
+                    continue;
+                }
+                // the pivot is free, or a later column's: take it, with the column stored
+                if (dirty) {
+                    if (t == 0) cnt = 0;
+                    __syncthreads();
+                    uint32_t own = 0;
+                    for (uint32_t x = t; x < nw; x += LK_BLOCK) own += (uint32_t)__popc(bm[x]);
+                    if (own) atomicAdd(&cnt, own);
+                    __syncthreads();
+                    if (t == 0) base = atomicAdd(&B.ctl->ptop, cnt);
+                    __syncthreads();
+                    st = base;
+                    len = cnt;
+                    if (st + len > LK_POOL) {
+                        if (t == 0) B.ctl->err = 1u;
+                        return;
+                    }
+                    __syncthreads();
+                    if (t == 0) cnt = 0;
+                    __syncthreads();
+                    for (uint32_t x = t; x < nw; x += LK_BLOCK)
+                        for (uint32_t y = bm[x]; y; y &= y - 1)
+                            B.pool[st + atomicAdd(&cnt, 1u)] = x * 32 + (uint32_t)__builtin_ctz(y);
+                }
+                const uint32_t at = j == 0xFFFFFFFFu ? held : j;
+                const uint32_t old = j == 0xFFFFFFFFu ? 0u : ps[j], oldn = j == 0xFFFFFFFFu ? 0u : pn[j];
+                __syncthreads();
+                if (t == 0) {
+                    pt[at] = q;
+                    ps[at] = st | cur << LK_START;
+                    pn[at] = len;
+                    np = max(np, at + 1);
+                }
+                if (j == 0xFFFFFFFFu) break;
+                cur = other;  // the column that held it goes on
+                st = old & ((1u << LK_START) - 1);
+                len = oldn;
+                fresh = true;
             }
-            if (t == 0) {
-                B.tri_tet[q] = C.tet;
-                pt[np] = q;
-                ps[np] = st;
-                pn[np] = len;
-            }
-            np++;
-            break;
         }
     }
+    __syncthreads();
+    for (uint32_t x = t; x < np; x += LK_BLOCK) B.tri_tet[pt[x]] = B.crit[ord[ps[x] >> LK_START]].tet;
 }
+static_assert(LK_POOL <= 1u << LK_START && LK_CRIT <= 1u << (32 - LK_START), "a start and a column in a word");
 
 static_assert(sizeof(LkCtl) == LINK_PAIRS_ZERO && LINK_PAIRS_MOST == VR_WAVE, "the control words, a lane per vertex");
 
@@ -640,9 +711,10 @@ int link_pairs_dim2(const int32_t *R, const int32_t *ij, const unsigned long lon
         if (w == LK_MANY) return VR_OK;
     }
     hipLaunchKernelGGL(k_lk_cycles, dim3(1024), dim3(VR_WAVE), 0, s, B);
-    const size_t lds = 4 * (size_t)((T + 31) / 32);
-    hipLaunchKernelGGL(k_lk_expand, dim3(256), dim3(LK_BLOCK), lds, s, B);
-    hipLaunchKernelGGL(k_lk_reduce, dim3(1), dim3(LK_BLOCK), lds, s, B);
+    // as many columns at a time as fit the chip (256 compute units of 160 KB)
+    const size_t lds = 4 * (size_t)((T + 31) / 32), cu = (160 * 1024) / (lds + 8 * LK_FRONT + 512);
+    hipLaunchKernelGGL(k_lk_expand, dim3((unsigned)(cu < 4 ? 256 * cu : LK_CRIT)), dim3(LK_BLOCK), lds, s, B);
+    hipLaunchKernelGGL(k_lk_reduce, dim3(1), dim3(LK_BLOCK), lds > 8 * LK_CRIT ? lds : 8 * LK_CRIT, s, B);
     LkCtl h{};
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&h, B.ctl, sizeof(h), hipMemcpyDeviceToHost, s);
