@@ -38,7 +38,8 @@
 //   k_mo_link    per edge, a wave: the edges that replace it, where the
 //                snapshots show L(r) to be connected
 //   k_mo_split   the other edges: L(r)'s components, the critical triangles
-//   k_mo_order   the critical cells' places in filtration order
+//   k_mo_order   the edges whose L(r) would take long that way, from the list
+//                of edges; the critical cells' places in filtration order
 //   k_mo_expand  per critical triangle, a wave: its boundary in critical edges
 //   k_mo_scan    starts of the columns
 //   k_mo_scatter the columns' entries
@@ -82,7 +83,9 @@ struct MoCtl {
     uint32_t m;     // critical edges
     uint32_t pad0;
     unsigned long long ptop;  // pool words taken
-    uint32_t pad1[26];
+    uint32_t wide;  // edges left to k_mo_order
+    uint32_t ends;  // its work-groups that are done with them
+    uint32_t pad1[24];
     uint32_t rec[MO_REG][32];  // [i][0]: critical triangles found, in share i
     uint32_t ent[MO_REG][32];  // [i][0]: column entries, in share i
 };
@@ -100,7 +103,7 @@ struct MoBufs {
     uint32_t *blk, *blkm;           // per MO_EB edges: their critical triangles (edges), then the first's place
     uint32_t *mask;                 // per MO_EB edges: those left to k_mo_split
     uint32_t *ecnt;                 // K, for the edges left to k_mo_split: their critical triangles
-    uint32_t *crit;                 // column -> edge
+    uint32_t *crit;                 // column -> edge; before, the edges left to k_mo_order
     uint32_t *cnt, *fill;           // column -> entries, entries placed
     uint32_t *start;                // column -> its first pool word (the length, then the entries)
     uint4 *rec;                     // critical triangle as found: edge, vertex, index among the keys, place in its edge
@@ -163,6 +166,33 @@ __device__ __forceinline__ void mo_append(const MoBufs &B, uint32_t r, uint32_t 
     else B.ctl->err = 1u;
 }
 
+// Searching L(r) vertex by vertex reads a row of the rank matrix each, and
+// when it falls into many components, or into two large ones, nearly every
+// vertex has its turn: one wave took 474 ms for an edge with 8000 common
+// neighbours, no two of them joined (27 ms by the columns' reduction).  The
+// edges older than r, a work-group's pass over them, give the components in
+// 6 us and 0.1 ns an edge (k_mo_order).  A search counts half microseconds, one
+// for a vertex of up to 512 (a piece of 64 beyond) and five for a component,
+// and leaves the edge to that pass after MO_WIDE and one more per 1024 edges
+// older than r, several times what the pass takes.  (A third of that sent the 4000-point mixture's
+// few long searches there too: 24 us less here and 74 there.)
+// us of vr_pairs_dim1 on such an edge, 400, 1000, 2049 and 8000 neighbours:
+// 1386, 7615, 28403 and 474211 without the pass, 559, 888, 1498 and 5597 with
+// it (1735, 4127, 7853 and 27304 by the columns' reduction).
+#define MO_WIDE 384
+#define MO_WIDE_COMP 5
+__device__ __forceinline__ int mo_allowed(uint32_t r) { return (int)(MO_WIDE + r / 1024); }
+// No search of so few vertices gets that far.
+static bool mo_wide_may(int64_t n) { return (n - 2) * (MO_WIDE_COMP + 1) > MO_WIDE; }
+
+// Lane 0 leaves edge r to k_mo_order, `place` of its critical triangles found:
+// those of the first components, for they come in order.
+__device__ __forceinline__ void mo_defer(const MoBufs &B, uint32_t r, uint32_t place) {
+    if (lane_id() != 0) return;
+    B.ecnt[r] = place;
+    B.crit[atomicAdd(&B.ctl->wide, 1u)] = r;
+}
+
 // The critical triangles of one edge, in the order of their vertices: the
 // components come with rising first vertices but for the one the search
 // began with, which waits for its turn.
@@ -184,6 +214,7 @@ __device__ __forceinline__ int32_t mo_wave_min(int32_t x, uint32_t i, uint32_t *
 
 // L(r) of any size: its pieces read again from the keys at each step, the
 // sets as bit masks in the wave's LDS (reached, to expand, this component).
+// x < 0: the search was given up.
 __device__ int2 mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b, int32_t f0, uint32_t m,
                             unsigned long long *reach, unsigned long long *open, unsigned long long *comp,
                             uint32_t &place) {
@@ -219,11 +250,13 @@ __device__ int2 mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
     uint32_t left = m;
     bool first_comp = true;
     MoPending pend{MO_NONE, 0u};
+    int allowed = mo_allowed(r);
     while (left > 0) {
         for (uint32_t p = lane; p < np; p += VR_WAVE) open[p] = comp[p] = 0ull;
         mo_wave_sync();
         uint32_t y = seed;
         for (;;) {
+            if ((allowed -= (int)np) < 0) return make_int2(-1, -1);
             const int32_t *Ry = B.R + (int64_t)vertex(y) * B.n;
             uint32_t got = 0;
             for (uint32_t p = 0; p < np; p++) {
@@ -253,6 +286,7 @@ __device__ int2 mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
                 if (open[p]) y = p * VR_WAVE + (uint32_t)__builtin_ctzll(open[p]);
             if (y == MO_NONE) break;
         }
+        allowed -= MO_WIDE_COMP;
         // the component's first vertex; the component of vertex 0 is the apparent triangle's
         uint32_t lo = 0;
         while (!comp[lo]) lo++;
@@ -525,7 +559,8 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
         const uint32_t a = (uint32_t)B.ij[2 * (int64_t)r], b = (uint32_t)B.ij[2 * (int64_t)r + 1];
         if (m > MO_NC * VR_WAVE) {
             const int2 f = mo_link_any(B, r, a, b, f0, m, masks[w][0], masks[w][1], masks[w][2], place);
-            done(f.x, f.y);
+            if (f.x < 0) mo_defer(B, r, place);
+            else done(f.x, f.y);
             continue;
         }
         const int32_t *Ra = B.R + (int64_t)a * B.n, *Rb = B.R + (int64_t)b * B.n;
@@ -568,6 +603,8 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
         uint32_t kstar = vertex(seed);
         bool first_comp = true;
         MoPending pend{MO_NONE, 0u};
+        int allowed = mo_allowed(r);
+        bool wide = false;
         for (;;) {
             unsigned long long open[MO_NC], comp[MO_NC];
 #pragma unroll
@@ -575,6 +612,8 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
             uint32_t y = seed;
             bool more = true;
             for (;;) {
+                wide = --allowed < 0;
+                if (wide) break;
                 const int32_t *Ry = B.R + (int64_t)vertex(y) * B.n;
                 more = false;
 #pragma unroll
@@ -596,6 +635,8 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
                 if (nx == MO_NONE) break;
                 y = nx;
             }
+            if (wide) break;
+            allowed -= MO_WIDE_COMP;
             // the component's first vertex; that of vertex 0 holds the apparent triangle
             uint32_t x0 = MO_NONE;
 #pragma unroll
@@ -627,8 +668,116 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
             for (int i = MO_NC - 1; i >= 0; i--)
                 if (todo[i]) seed = (uint32_t)i * VR_WAVE + (uint32_t)__builtin_ctzll(todo[i]);
         }
+        if (wide) {
+            mo_defer(B, r, place);
+            continue;
+        }
         if (pend.x != MO_NONE) mo_append(B, r, pend.k, (uint32_t)f0 + pend.x, place++);
         done(Ra[kstar], Rb[kstar]);
+    }
+}
+
+// The nh edges left over, a work-group each: the vertices of L(r) in a
+// union-find in LDS that the edges older than r join, the smaller position the
+// root, so that a root is its component's first vertex.
+#define MO_WIDE_BLOCK 1024
+#define MO_WIDE_LOADS 8
+__device__ __forceinline__ void mo_wide(const MoBufs &B, uint32_t nh) {
+    __shared__ uint32_t par[VR_MAX_POINTS];
+    __shared__ uint16_t pos[VR_MAX_POINTS];  // vertex -> position in L(r)
+    __shared__ uint32_t wsum[MO_WIDE_BLOCK / VR_WAVE];
+    __shared__ unsigned long long near0;
+    __shared__ uint32_t s_base;
+    const uint32_t t = threadIdx.x, lane = lane_id(), w = t / VR_WAVE;
+    auto find = [&](uint32_t x) {  // an entry only ever moves up its own path
+        for (uint32_t p = par[x]; p != x; p = par[x]) {
+            const uint32_t g = par[p];
+            if (g != p) par[x] = g;
+            x = g;
+        }
+        return x;
+    };
+    for (uint32_t h = blockIdx.x; h < nh; h += gridDim.x) {
+        const uint32_t r = B.crit[h], m = (uint32_t)(B.end[r] - B.first[r]);
+        const int32_t f0 = B.first[r];
+        const uint32_t a = (uint32_t)B.ij[2 * (int64_t)r], b = (uint32_t)B.ij[2 * (int64_t)r + 1];
+        auto vertex = [&](uint32_t x) { return mo_third(B.key[f0 + x], a, b); };
+        __syncthreads();  // the last edge's reads are done
+        for (uint32_t k = t; k < (uint32_t)B.n; k += MO_WIDE_BLOCK) pos[k] = 0xFFFFu;
+        if (t == 0) near0 = ~0ull;
+        __syncthreads();
+        for (uint32_t x = t; x < m; x += MO_WIDE_BLOCK) {
+            pos[vertex(x)] = (uint16_t)x;
+            par[x] = x;
+        }
+        __syncthreads();
+        for (uint32_t e0 = t; e0 < r; e0 += MO_WIDE_LOADS * MO_WIDE_BLOCK) {
+            int2 v[MO_WIDE_LOADS];
+#pragma unroll
+            for (int u = 0; u < MO_WIDE_LOADS; u++) {
+                const int64_t e = min(e0 + u * MO_WIDE_BLOCK, r);
+                v[u] = make_int2(B.ij[2 * e], B.ij[2 * e + 1]);
+            }
+#pragma unroll
+            for (int u = 0; u < MO_WIDE_LOADS; u++) {
+                if (e0 + u * MO_WIDE_BLOCK >= r || (uint32_t)v[u].x >= (uint32_t)B.n || (uint32_t)v[u].y >= (uint32_t)B.n)
+                    continue;
+                uint32_t x = pos[v[u].x], y = pos[v[u].y];
+                if (x == 0xFFFFu || y == 0xFFFFu) continue;
+                for (;;) {
+                    x = find(x);
+                    y = find(y);
+                    if (x == y) break;
+                    const uint32_t lo = min(x, y), hi = max(x, y);
+                    if (atomicCAS(&par[hi], hi, lo) == hi) break;
+                }
+            }
+        }
+        __syncthreads();
+        // the vertex nearest both ends of the apparent triangle's component
+        for (uint32_t x = t; x < m; x += MO_WIDE_BLOCK)
+            if (find(x) == 0) {
+                const uint32_t k = vertex(x);
+                const uint32_t d = (uint32_t)max(B.R[(int64_t)a * B.n + k], B.R[(int64_t)b * B.n + k]);
+                atomicMin(&near0, ((unsigned long long)d << 32) | k);
+            }
+        // the first vertices of the others, in order, from the place-th on
+        const uint32_t found = B.ecnt[r];
+        uint32_t total = 0;
+        for (int pass = 0; pass < 2; pass++) {
+            uint32_t run = 0;
+            for (uint32_t x0 = 0; x0 < m; x0 += MO_WIDE_BLOCK) {
+                const uint32_t x = x0 + t;
+                const bool root = x > 0 && x < m && par[x] == x;
+                const unsigned long long rm = ballot64(root);
+                __syncthreads();
+                if (lane == 0) wsum[w] = (uint32_t)__popcll(rm);
+                __syncthreads();
+                uint32_t at = run + mo_before(rm);
+                for (uint32_t i = 0; i < MO_WIDE_BLOCK / VR_WAVE; i++) {
+                    if (i < w) at += wsum[i];
+                    run += wsum[i];
+                }
+                if (pass == 1 && root && at >= found && s_base != MO_NONE)
+                    B.rec[s_base + at - found] = make_uint4(r, vertex(x), (uint32_t)f0 + x, at);
+            }
+            if (pass == 1) break;
+            total = run;
+            if (t == 0) {
+                const uint32_t i = r / MO_EB % MO_REG, share = B.qcap / MO_REG, add = total - found;
+                const uint32_t q = atomicAdd(&B.ctl->rec[i][0], add);
+                const bool room = q + add <= share;
+                if (!room) B.ctl->err = 1u;
+                s_base = room ? i * share + q : MO_NONE;
+                B.ecnt[r] = total;
+                if (total) atomicAdd(&B.blk[r / MO_EB], total);
+            }
+            __syncthreads();
+        }
+        if (t == 0) {
+            const uint32_t k = (uint32_t)near0;
+            B.fg[r] = make_int2(B.R[(int64_t)a * B.n + k], B.R[(int64_t)b * B.n + k]);
+        }
     }
 }
 
@@ -670,12 +819,32 @@ __device__ __forceinline__ uint32_t mo_scan(uint32_t n, V v, P put) {
     return carry;
 }
 
-// Places: the blocks' critical triangles (work-group 0) and edges (1).
-__global__ __launch_bounds__(1024) void k_mo_order(MoBufs B) {
-    const uint32_t nb = (uint32_t)((B.K + MO_EB - 1) / MO_EB);
-    uint32_t *p = blockIdx.x == 0 ? B.blk : B.blkm;
-    const uint32_t tot = mo_scan(nb, [&](uint32_t x) { return p[x]; }, [&](uint32_t x, uint32_t s) { p[x] = s; });
-    if (threadIdx.x == 0) *(blockIdx.x == 0 ? &B.ctl->q : &B.ctl->m) = tot;
+// Places: the blocks' critical triangles (work-group 0) and edges (1).  Edges
+// left to the pass over the older ones come first, and then the last
+// work-group to end makes both sums: a launch less than with a kernel for
+// each, which cost the calls without such edges 4.5 us.
+__global__ __launch_bounds__(MO_WIDE_BLOCK) void k_mo_order(MoBufs B) {
+    __shared__ uint32_t s_end;
+    const uint32_t nb = (uint32_t)((B.K + MO_EB - 1) / MO_EB), nh = B.ctl->wide;
+    uint32_t lo = blockIdx.x, hi = lo + 1;
+    if (nh > 0) {
+        mo_wide(B, nh);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __threadfence();
+            s_end = atomicAdd(&B.ctl->ends, 1u);
+            __threadfence();
+        }
+        __syncthreads();
+        if (s_end + 1 != gridDim.x) return;
+        lo = 0;
+        hi = 2;
+    }
+    for (uint32_t i = lo; i < hi && i < 2; i++) {
+        uint32_t *p = i == 0 ? B.blk : B.blkm;
+        const uint32_t tot = mo_scan(nb, [&](uint32_t x) { return p[x]; }, [&](uint32_t x, uint32_t s) { p[x] = s; });
+        if (threadIdx.x == 0) *(i == 0 ? &B.ctl->q : &B.ctl->m) = tot;
+    }
 }
 
 // One wave per critical triangle {r, k}: the edges ak, bk and r's two
@@ -1027,7 +1196,7 @@ int morse_pairs_dim1(int32_t *R, const int32_t *ij, const unsigned long long *ke
     if (B.W > VR_WAVE) hipLaunchKernelGGL(k_mo_link<2>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);
     else hipLaunchKernelGGL(k_mo_link<1>, dim3((unsigned)wg), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_split, dim3((unsigned)nblk), dim3(MO_BLOCK), 0, s, B);
-    hipLaunchKernelGGL(k_mo_order, dim3(2), dim3(1024), 0, s, B);
+    hipLaunchKernelGGL(k_mo_order, dim3(mo_wide_may(n) ? 256 : 2), dim3(MO_WIDE_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_expand, dim3(2048), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_scan, dim3(1), dim3(1024), 0, s, B);
     hipLaunchKernelGGL(k_mo_scatter, dim3(512), dim3(MO_BLOCK), 0, s, B);
