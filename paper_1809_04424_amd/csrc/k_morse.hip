@@ -69,8 +69,8 @@
 #define MO_POOL (1ll << 26)         // words of stored columns at most
 #define MO_EB 16                    // edges a wave of k_mo_link takes, in order
 #define MO_SNAPS 32                 // ranks with a snapshot at most
-#define MO_LDS_Q (1u << 17)         // critical triangles whose bits a wave holds in LDS
-#define MO_GWAVES 256               // waves reducing with their bits in device memory
+#define MO_LDS_FEW 17               // log2 of the critical triangles whose bits a wave holds in LDS,
+#define MO_LDS_MANY 19              // by the number of triangles
 #define MO_NONE 0xFFFFFFFFu
 
 // Counters that waves all over the chip add to come MO_REG times, a cache
@@ -987,60 +987,93 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_scatter(MoBufs B) {
 // pivot to a younger edge.  (The lock-free reduction of Morozov and
 // Nigmetov, "Towards lockfree persistent homology", 2020.)
 //
-// The working column is a bit per critical triangle (in LDS up to MO_LDS_Q
-// of them, else in device memory): an addition flips the added entries'
-// bits, and the pivot is the first set bit from the last one on.  Latency
-// bounds it: an addition is two dependent reads from memory.  As sorted
-// lists merged in LDS it took 1776 us at the mixture.
+// The working column is a bit per critical triangle: an addition flips the
+// added entries' bits, and the pivot is the first set bit from the last one
+// on.  Latency bounds it: an addition is two dependent reads from memory.  As
+// sorted lists merged in LDS it took 1776 us at the mixture.
+// The bits are in LDS, 16 KB a wave where there are at most 2^17 triangles in
+// all, else 64 KB; beyond 2^19 critical ones in device memory, by as many waves as the
+// entries' array holds bits for.  us of vr_pairs_dim1 with 16 KB, then memory,
+// at 256 waves / now (by the columns' reduction): three parts of 60 vertices, all
+// edges between them in random order, 84774 / 23400 (38283); parts of 20, 20, 400
+// 34270 / 7600 (24709); 400 pairs of hubs over 1410 vertices (563600 critical
+// triangles) 175390 / 59500 (119712).  64 KB for all: 1000 points, 24975 random
+// edges, 25300 -> 29274.
 template <bool LDS>
-__device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *bits, uint32_t nw) {
+__device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *bits, unsigned long long *seen, uint32_t nw,
+                                          uint32_t nwaves) {
     const uint32_t lane = lane_id();
-    const uint32_t m = B.ctl->m;
-    // bits in device memory are flipped in L2: they are read and cleared there
-    auto get = [&](uint32_t x) { return x >= nw ? 0ull : LDS ? bits[x] : st_load64(bits + x); };
+    const uint32_t m = B.ctl->m, nc = (nw + VR_WAVE - 1) / VR_WAVE;
+    // Bits in device memory are the wave's own, and flipped, read and cleared
+    // in L2.  A bit of `seen` (LDS) for each of their words says that the column
+    // has touched it: only those are read.
+    auto get = [&](uint32_t x) -> unsigned long long {
+        if (x >= nw) return 0ull;
+        if (LDS) return bits[x];
+        return (seen[x / VR_WAVE] >> (x % VR_WAVE)) & 1ull
+                   ? __hip_atomic_load(bits + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                   : 0ull;
+    };
     auto clear = [&](uint32_t x) {
         if (LDS) bits[x] = 0ull;
-        else st_store64(bits + x, 0ull);
+        else __hip_atomic_store(bits + x, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // the 64 words to look at from word x on: in memory, whole words of `seen`
+    auto from = [&](uint32_t x) -> uint32_t {
+        if (LDS) return x;
+        for (uint32_t c = x / VR_WAVE; c < nc; c += VR_WAVE) {
+            const unsigned long long any = ballot64(c + lane < nc && seen[c + lane] != 0ull);
+            if (any) return VR_WAVE * (c + (uint32_t)__builtin_ctzll(any));
+        }
+        return nc * VR_WAVE;
     };
     auto sync = [&] {
         if (LDS) mo_wave_sync();
-        else __threadfence();
+        else __threadfence_block();
     };
     for (uint32_t x = lane; x < nw; x += VR_WAVE) clear(x);
     sync();
-    auto flip = [&](const uint32_t *e, uint32_t len) {
-        for (uint32_t x = lane; x < len; x += VR_WAVE) {
-            const uint32_t q = e[x];
+    auto flip1 = [&](uint32_t q) {
+        if (LDS) {
             atomicXor(&bits[q >> 6], 1ull << (q & 63));
+        } else {
+            (void)__hip_atomic_fetch_xor(&bits[q >> 6], 1ull << (q & 63), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            atomicOr(&seen[q >> 12], 1ull << ((q >> 6) & 63));
         }
+    };
+    auto flip = [&](const uint32_t *e, uint32_t len) {
+        for (uint32_t x = lane; x < len; x += VR_WAVE) flip1(e[x]);
     };
     // a column stored from pool word p: its length and first entries in one read
     auto add = [&](uint32_t p) {
         const uint32_t e = p + lane < B.pcap ? B.pool[p + lane] : 0u;
         const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)e);
-        if (lane > 0 && lane <= len) atomicXor(&bits[e >> 6], 1ull << (e & 63));
+        if (lane > 0 && lane <= len) flip1(e);
         if (len >= VR_WAVE) flip(B.pool + p + VR_WAVE, len - (VR_WAVE - 1));
     };
-    const uint32_t nwaves = LDS ? gridDim.x : MO_GWAVES;
     for (uint32_t nx = blockIdx.x; nx < m; nx += nwaves) {
         const uint32_t c = m - 1 - nx;
         uint32_t r = B.crit[c], pub = B.start[c];
         uint32_t wi = 0;  // no bit is set before this word
         bool dirty = false;
+        if (!LDS) {
+            for (uint32_t x = lane; x < nc; x += VR_WAVE) seen[x] = 0ull;
+            sync();
+        }
         add(pub);
         for (;;) {
             sync();
             // the pivot: the first set bit
             uint32_t q = MO_NONE;
-            for (; wi < nw; wi += VR_WAVE) {
+            for (wi = from(wi); wi < nw; wi = from(wi + VR_WAVE)) {
                 const unsigned long long v = get(wi + lane);
                 const unsigned long long any = ballot64(v != 0ull);
                 if (any) {
                     const int src = __builtin_ctzll(any);
                     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, src);
                     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), src);
-                    wi += (uint32_t)src;
-                    q = wi * 64 + (lo ? (uint32_t)__builtin_ctz(lo) : 32u + (uint32_t)__builtin_ctz(hi));
+                    q = (wi + (uint32_t)src) * 64 + (lo ? (uint32_t)__builtin_ctz(lo) : 32u + (uint32_t)__builtin_ctz(hi));
+                    if (LDS) wi += (uint32_t)src;
                     break;
                 }
             }
@@ -1055,7 +1088,7 @@ __device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *b
             }
             if (dirty) {  // store the column
                 uint32_t len = 0;
-                for (uint32_t x = wi; x < nw; x += VR_WAVE)
+                for (uint32_t x = wi; x < nw; x = from(x + VR_WAVE))
                     len += (uint32_t)__popcll(get(x + lane));
                 len = wave_sum<uint32_t>(len);
                 unsigned long long p = 0;
@@ -1069,7 +1102,7 @@ __device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *b
                 pub = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
                 if (lane == 0) B.pool[pub] = len;
                 uint32_t at = pub + 1;
-                for (uint32_t x = wi; x < nw; x += VR_WAVE) {
+                for (uint32_t x = wi; x < nw; x = from(x + VR_WAVE)) {
                     unsigned long long v = get(x + lane);
                     const uint32_t pc = (uint32_t)__popcll(v), inc = wave_incl_scan_dpp(pc);
                     uint32_t o = at + inc - pc;
@@ -1093,7 +1126,8 @@ __device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *b
             }
             won = (uint32_t)__builtin_amdgcn_readfirstlane((int)won);
             if (!won) continue;  // the owner changed: look again
-            for (uint32_t x = wi + lane; x < nw; x += VR_WAVE) clear(x);
+            for (uint32_t x = wi; x < nw; x = from(x + VR_WAVE))
+                if (x + lane < nw) clear(x + lane);
             if (whi == 0) break;
             // the displaced column goes on from its stored entries
             r = whi - 1;
@@ -1105,15 +1139,20 @@ __device__ __forceinline__ void mo_reduce(const MoBufs &B, unsigned long long *b
     }
 }
 
+template <int LOG>
 __global__ __launch_bounds__(VR_WAVE) void k_mo_reduce(MoBufs B) {
-    __shared__ unsigned long long bits[MO_LDS_Q / 64];
+    __shared__ unsigned long long bits[(1u << LOG) / 64];
     if (B.ctl->err) return;
     const uint32_t nq = B.ctl->q, nw = (nq + 63) / 64;
-    if (nq <= MO_LDS_Q) mo_reduce<true>(B, bits, nw);
-    else if (blockIdx.x < MO_GWAVES)  // the entries' array is free by now
-        mo_reduce<false>(B, (unsigned long long *)B.ent + (size_t)blockIdx.x * (MO_QCAP / 64), nw);
+    if (nq <= 1u << LOG) {
+        mo_reduce<true>(B, bits, nullptr, nw, gridDim.x);
+    } else {  // the entries' array is free by now
+        const uint32_t most = min(gridDim.x, (uint32_t)MO_ENT / nw);
+        if (blockIdx.x < most) mo_reduce<false>(B, (unsigned long long *)B.ent + (size_t)blockIdx.x * nw, bits, nw, most);
+    }
 }
-static_assert(8 * MO_ENT >= MO_GWAVES * (MO_QCAP / 8), "the bits of k_mo_reduce's waves fit the entries' array");
+static_assert((1 << MO_LDS_FEW) / 64 >= MO_QCAP / 64 / VR_WAVE, "a bit of `seen` per word");
+static_assert(MO_ENT / (MO_QCAP / 64) >= 256, "the bits of many of k_mo_reduce's waves fit the entries' array");
 
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_emit(MoBufs B) {
     if (B.ctl->err) return;
@@ -1200,7 +1239,8 @@ int morse_pairs_dim1(int32_t *R, const int32_t *ij, const unsigned long long *ke
     hipLaunchKernelGGL(k_mo_expand, dim3(2048), dim3(MO_BLOCK), 0, s, B);
     hipLaunchKernelGGL(k_mo_scan, dim3(1), dim3(1024), 0, s, B);
     hipLaunchKernelGGL(k_mo_scatter, dim3(512), dim3(MO_BLOCK), 0, s, B);
-    hipLaunchKernelGGL(k_mo_reduce, dim3(1280), dim3(VR_WAVE), 0, s, B);
+    if (T <= 1 << MO_LDS_FEW) hipLaunchKernelGGL(k_mo_reduce<MO_LDS_FEW>, dim3(1280), dim3(VR_WAVE), 0, s, B);
+    else hipLaunchKernelGGL(k_mo_reduce<MO_LDS_MANY>, dim3(1280), dim3(VR_WAVE), 0, s, B);
     hipLaunchKernelGGL(k_mo_emit, dim3(256), dim3(MO_BLOCK), 0, s, B);
     uint32_t err = 0;
     hipError_t e = hipGetLastError();
