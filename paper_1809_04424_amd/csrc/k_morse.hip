@@ -81,7 +81,7 @@ struct MoCtl {
     uint32_t err;   // a limit was passed
     uint32_t q;     // critical triangles
     uint32_t m;     // critical edges
-    uint32_t pad0;
+    uint32_t any;   // there are critical edges
     unsigned long long ptop;  // pool words taken
     uint32_t wide;  // edges left to k_mo_order
     uint32_t ends;  // its work-groups that are done with them
@@ -324,11 +324,18 @@ __device__ int2 mo_link_any(const MoBufs &B, uint32_t r, uint32_t a, uint32_t b,
 // per vertex: the row's ranks set bits by the snapshot they first appear in,
 // and the snapshots are the running unions.  Bound by writing them: 4 n^2
 // bytes at 32 snapshots.
+// Critical edges are looked for here too.  Where there is none (ultrametrics,
+// trees) every triangle that pairs is apparent, and the kernels that follow
+// have nothing to do: 512 points of an ultrametric, 22238720 triangles,
+// 312 us of vr_pairs_dim1 with them, 104 now (222 by the columns' reduction).
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_snap(MoBufs B, int S) {
     extern __shared__ uint32_t sbits[];  // S x 2 W
     const int64_t v = blockIdx.x;
     const int32_t *row = B.R + v * B.n;
     const int w2 = 2 * B.W;
+    bool any = false;
+    for (int64_t r = v * MO_BLOCK + threadIdx.x; r < B.K; r += B.n * MO_BLOCK) any |= B.first[r] < 0 && B.e_low[r] < 0;
+    if (any) B.ctl->any = 1u;
     for (int x = threadIdx.x; x < S * w2; x += MO_BLOCK) sbits[x] = 0u;
     __syncthreads();
     for (int64_t k = threadIdx.x; k < B.n; k += MO_BLOCK) {
@@ -421,7 +428,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_link(MoBufs B) {
     const uint32_t lane = lane_id(), w = threadIdx.x / VR_WAVE;
     const int64_t blk = (int64_t)blockIdx.x * MO_WPB + w;
     const int64_t r0 = blk * MO_EB;
-    if (r0 >= B.K) return;
+    if (r0 >= B.K || !B.ctl->any) return;
     // the block's edges, one a lane
     const int64_t rl = r0 + lane;
     const bool in = lane < MO_EB && rl < B.K;
@@ -542,6 +549,7 @@ __global__ __launch_bounds__(MO_BLOCK) void k_mo_split(MoBufs B) {
     __shared__ unsigned long long masks[MO_WPB][3][MO_GEN];
     const uint32_t lane = lane_id(), w = threadIdx.x / VR_WAVE;
     const int64_t blk = blockIdx.x;
+    if (!B.ctl->any) return;
     uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.mask[blk]), turn = 0;
     for (; left; left &= left - 1, turn++) {
         if (turn % MO_WPB != w) continue;
@@ -825,6 +833,7 @@ __device__ __forceinline__ uint32_t mo_scan(uint32_t n, V v, P put) {
 // each, which cost the calls without such edges 4.5 us.
 __global__ __launch_bounds__(MO_WIDE_BLOCK) void k_mo_order(MoBufs B) {
     __shared__ uint32_t s_end;
+    if (!B.ctl->any) return;
     const uint32_t nb = (uint32_t)((B.K + MO_EB - 1) / MO_EB), nh = B.ctl->wide;
     uint32_t lo = blockIdx.x, hi = lo + 1;
     if (nh > 0) {
@@ -959,7 +968,7 @@ __global__ __launch_bounds__(1024) void k_mo_scan(MoBufs B) {
 }
 
 __global__ __launch_bounds__(MO_BLOCK) void k_mo_scatter(MoBufs B) {
-    if (B.ctl->err) return;
+    if (B.ctl->err || !B.ctl->any) return;
     const uint32_t x0 = blockIdx.x * MO_BLOCK + threadIdx.x;
     const uint32_t i = blockIdx.x % MO_REG, ne = B.ctl->ent[i][0];
     const uint2 *ent = B.ent + (size_t)i * (B.ecap / MO_REG);
