@@ -67,6 +67,13 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K
 // unions, 71, 399 and 2831 with PF_ROUNDS in any case and one thread for the
 // rest, now 21, 101 and 725.)
 //
+// The marks say what joined two components before the stretch.  Where hardly
+// any edge of a batch does (less than one in PF_IDLE) and many marks follow
+// (all edges between two halves, say, of which the first joins them), the
+// next 65536 edges are looked up again, in 30 us, and those left out that
+// join nothing or what the edge before them joins; a batch of 2048 takes 10.
+// 512 points of an ultrametric: 341 us without that, 198 now.
+//
 // One work-group looking up every edge and one thread joining took 2270 us
 // at the 4000-point mixture and 420 us at the 1000-point circle, and the
 // (min, max) closure of the rank matrix 210 us at 400 points.
@@ -75,6 +82,8 @@ __global__ void __launch_bounds__(PD_BLOCK) k_pd_clear(int32_t *e_low, int64_t K
 #define PF_ROUNDS 24
 #define PF_SLOW 3
 #define PF_FEW 40
+#define PF_IDLE 16
+#define PF_DENSE 4
 
 // No memory but the outputs: between launches the tables lie in e_low, in the
 // stretch [e0, e1) to come, whose entries are all still to be written.  Its
@@ -166,7 +175,9 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
     };
     uint32_t w0 = 0;  // the next word of marks
     __syncthreads();
+    bool idle = false;  // few edges of the last batch joined two components
     while (w0 < words && s_joined < (uint32_t)(P.n - 1)) {
+        const uint32_t before = s_joined;
         // the next words whose marks fit the batch, their edges in order
         const uint32_t w = w0 + (uint32_t)t;
         unsigned long long m = 0;
@@ -176,16 +187,54 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
                 if (2 * (int64_t)w + 1 < nm) m |= (unsigned long long)(uint32_t)marks[2 * w + 1] << 32;
             } else m = e1 - e0 - 64 * (int64_t)w >= 64 ? ~0ull : (1ull << (e1 - e0 - 64 * (int64_t)w)) - 1;
         }
-        const uint32_t c = (uint32_t)__popcll(m);
-        uint32_t inc = c;
+        uint32_t c, inc, total;
+        auto sum = [&] {
+            c = inc = (uint32_t)__popcll(m);
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += y;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += y;
+            }
+            if (lane == 63) wc[wv] = inc;
+            __syncthreads();
+            total = 0;
+            for (int x = 0; x < PF_BLOCK / 64; x++) {
+                if (x == wv) inc += total;
+                total += wc[x];
+            }
+        };
+        sum();
+        if (idle && total > PF_DENSE * PF_BATCH) {
+            // every wave looks the edges of its words up again, a word at a
+            // time; one that joins what the edge before it joins is left out too
+            for (int x0 = 0; x0 < 64; x0 += 4) {
+                int32_t a[4], b[4];
+                bool on[4];
+#pragma unroll
+                for (int x = 0; x < 4; x++) {
+                    const unsigned long long mx = __shfl(m, x0 + x, 64);
+                    on[x] = ((mx >> lane) & 1) && pf_ends(P, e0 + 64 * (int64_t)(w0 + 64 * wv + x0 + x) + lane, a[x], b[x]);
+                }
+#pragma unroll
+                for (int x = 0; x < 4; x++) {
+                    uint32_t both = ~0u;  // the components, or none
+                    if (on[x]) {
+                        const uint32_t ra = find((uint32_t)a[x]), rb = find((uint32_t)b[x]);
+                        if (ra != rb) both = min(ra, rb) << 16 | max(ra, rb);
+                    }
+                    const uint32_t last = __shfl_up(both, 1, 64);
+                    const unsigned long long mx = __ballot(both != ~0u && (lane == 0 || both != last));
+                    if (lane == x0 + x) m = mx;
+                }
+            }
+            if (e0 && w < words) {
+                marks[2 * w] = (int32_t)(uint32_t)m;
+                if (2 * (int64_t)w + 1 < nm) marks[2 * w + 1] = (int32_t)(m >> 32);
+            }
+            idle = false;
+            __syncthreads();
+            sum();
         }
-        if (lane == 63) wc[wv] = inc;
-        __syncthreads();
-        for (int x = 0; x < wv; x++) inc += wc[x];
         if (t == 0) {
             s_n = 0;
             s_next = w0;
@@ -292,6 +341,7 @@ __global__ void __launch_bounds__(PF_BLOCK) k_pf_join(PfBufs P, int64_t e0, int6
             break;
         }
         __syncthreads();
+        idle = PF_IDLE * (s_joined - before) < nc;
         // shorter paths for the next batch (a root stays a root)
         for (int64_t v = t; v < P.n; v += PF_BLOCK) par[v] = (uint16_t)find((uint32_t)v);
         __syncthreads();
