@@ -645,10 +645,19 @@ __global__ __launch_bounds__(EB) void k_tri_count(VrDev D, int parts) {
 // small, each with work enough for its setup.  Write, four and five a vertex:
 // 39 and 35 us (1000-point circle), 510 and 491 (1088 points, all edges), 42
 // and 41 (777 points); eight split by partner: 30 us against 21 with five on
-// 300 points; 2000 points: 79 with three, 84 with one of 512 threads.  Count: 21 us with four or five, 25 with eight on the circle.
-// Large clouds of 384 or more neighbours a vertex, as K edges known on the
-// host tell (else -1), write with two: 4000 points with 400, 268 us with one,
-// 251; but 2500 with 250, 89 and 92, and 8192 with 270, 277 and 316.
+// 300 points; 2000 points: 79 with three, 84 with one of 512 threads.  Count:
+// 21 us with four or five, 25 with eight on the circle.
+// Larger clouds of many neighbours, as K edges known on the host tell (else
+// -1), write with two, the more the points the later: a short launch is left
+// with its heaviest vertices, a long one is not.  One and two, us, points
+// evenly in the cube: 2500 points with 270, 320 and 420 neighbours 105 and
+// 105, 133 and 130, 199 and 179; 4000 with 320, 384, 420 and 700 185 and
+// 186, 238 and 241, 277 and 268, 723 and 645; 6000 with 384, 420 and 500 326
+// and 339, 379 and 383, 518 and 493; 8192 with 384, 420, 500 and 700 433 and
+// 454, 505 and 517, 691 and 667, 1318 and 1250; batches of 2 and of 4 of 2500,
+// 400 and 500 302 and 303, 448 and 407; 543 and 565, 787 and 766.  In six
+// dimensions two are better from about 50 neighbours less on.  The mixture's
+// 4000 points with 400: 268 and 251.
 // Up to 128 points seven or eight are the same (7 and 8 us).
 static int enum_parts(long long V, long long groups, long long most) {
     const long long p = groups / (V > 0 ? V : 1);
@@ -659,7 +668,7 @@ int enum_parts_count(long long V) { return enum_parts(V, 4096, 4); }
 int enum_parts_write(long long V, long long C, long long K) {
     if (enum_block(V, C) == 256) return enum_parts(V, 6144, 5);
     const int p = enum_parts(V, 3072, 5);
-    return p < 2 && K >= 192 * V ? 2 : p;
+    return p < 2 && 2 * K >= V * (250 + (V < 8192 ? V : 8192) / 32) ? 2 : p;
 }
 
 // Work-group size, the default: 256 threads for small clouds (more
@@ -671,8 +680,12 @@ int enum_block(long long V, long long C) { return V <= 2048 * C ? 256 : 512; }
 
 // Pieces loaded at a time, the defaults.  Count: its candidates are rank
 // prefixes, often short: 4, or 8 where K edges are known to give 768
-// neighbours a vertex (1088 points, all edges: 149 us with 8, 166 with 4;
-// 4000 points, 400 neighbours: 109 and 100).  Write (prefix lists): 8.
+// neighbours a vertex.  4 and 8, us: 800 points with 600, 768 and all edges
+// 57 and 59, 76 and 73, 77 and 74; 1088 with 600, 768 and all 80 and 79, 110
+// and 100, 166 and 149; 2048 with 400, 768 and 1400 82 and 82, 231 and 191,
+// 605 and 493; 4000 evenly in the cube with 400, 768 and 1000 134 and 128,
+// 423 and 352, 710 and 591, but the mixture's 400 100 and 109.  Write (prefix
+// lists): 8.
 int enum_pieces_count(long long V, long long K) { return K >= 384 * V ? 8 : 4; }
 int enum_pieces_write() { return 8; }
 
