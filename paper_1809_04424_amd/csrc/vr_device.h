@@ -403,9 +403,10 @@ __host__ __device__ __forceinline__ long long row_start(long long i, long long n
 // Pair index -> (i, j): solve row_start(i) <= e < row_start(i+1) with a
 // floating-point guess corrected by exact integer comparisons.
 // (n <= 8192, so every number here is below 2^28; the estimate in single
-// precision is a row off at most and the integers correct it.  In double
-// precision, a call for each 8 of 34 million pairs, the selection took 67 us
-// instead of 58.)
+// precision is a row off at most, for the first and the last pair of every
+// row of every n also with the root two units off, and the integers correct
+// it.  In double precision, a call for each 8 of 34 million pairs, the
+// selection took 67 us instead of 58.)
 __device__ __forceinline__ void pair_of(long long e64, long long n64, int *pi, int *pj) {
     const int e = (int)e64, n = (int)n64;
     auto start = [&](int i) { return (int)((uint32_t)i * (uint32_t)(2 * n - i - 1) / 2u); };
