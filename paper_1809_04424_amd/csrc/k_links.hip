@@ -54,7 +54,7 @@
 #define LK_CRIT 1024          // critical tetrahedra at most
 #define LK_POOL (1u << 22)    // entries of their columns at most
 #define LK_MAXT (384 * 1024)  // triangles whose bits k_lk_expand holds in LDS
-#define LK_FRONT 2048         // triangles replaced at a time
+#define LK_FRONT 1536         // triangles replaced at a time
 #define LK_ROUNDS (1 << 16)
 #define LK_DROP 0xFFFFu       // first triangle of its value
 #define LK_ROOT 0xFFFEu       // first triangle of a further component
@@ -643,6 +643,8 @@ __global__ __launch_bounds__(LK_BLOCK) void k_lk_reduce(LkBufs B) {
 }
 static_assert(LK_POOL <= 1u << LK_START && LK_CRIT <= 1u << (32 - LK_START), "a start and a column in a word");
 
+// bits and the rest of a work-group's LDS (k_lk_expand, k_lk_reduce) in 64 KB, what a launch may ask for
+static_assert(LK_MAXT / 8 + 8 * LK_FRONT + 64 <= 65536 && LK_MAXT / 8 + 14 * LK_CRIT + LK_CRIT / 8 + 64 <= 65536, "LDS");
 static_assert(sizeof(LkCtl) == LINK_PAIRS_ZERO && LINK_PAIRS_MOST == VR_WAVE, "the control words, a lane per vertex");
 
 size_t link_pairs_scratch(int64_t K, int64_t T) {
